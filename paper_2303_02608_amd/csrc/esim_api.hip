@@ -23,7 +23,9 @@ struct esim_plan_s {
   int64_t npix = 0;
   int64_t nblk = 0;
   int64_t wl_capacity = 0;
-  int64_t dense_groups[5] = {0, 0, 0, 0, 0};
+  int64_t dense_groups[6] = {0, 0, 0, 0, 0, 0};   // [5]: tiles
+  int tile_last = 0;       // see RegressArgs
+  int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles (0: a clip's windows do not fit)
   int lanes_dense = 1;     // lanes per regression item, dense launches
   int lanes_list = 16;     // lanes per regression item, work-list launches
   int blocks_per_cu = 4;   // persistent grid: 256 CUs x this many blocks
@@ -32,14 +34,13 @@ struct esim_plan_s {
   esim::DeviceShape shape;       // compute units and XCDs of the plan's device
   // work buffers of esim_step (allocated with the plan)
   void* step_mem = nullptr;
-  int64_t* xcd_bounds = nullptr;  // [5 lane counts][kMaxXcds + 1] dense group bounds per XCD (device)
+  int64_t* xcd_bounds = nullptr;  // [5 lane counts, tiles][kMaxXcds + 1] dense group bounds per XCD (device)
   int64_t* step_wl = nullptr;     // [wl_capacity]
   int32_t* step_count = nullptr;  // [4] (two segments of a split work list)
   // esim_step's split work list: clips whose windows fit 16 columns (the
   // one-pass list instance) in the first segment, wider ones from split_seg
-  // on (-1: one segment); the largest r of each segment
+  // on (-1: one segment)
   int64_t split_seg = -1;
-  int split_r[2] = {0, 0};
   float* step_alpha = nullptr;    // [npix]
   float* step_beta = nullptr;     // [F + 2][npix] (explicit thresholds only)
   int thr = ESIM_THRESHOLD_CLOSED;
@@ -86,19 +87,29 @@ namespace {
 
 int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count,
                         int64_t n_out, float* alpha, float* beta, float* resid, float* kappa,
-                        bool update_state, hipStream_t stream, int max_r = -1) {
+                        bool update_state, hipStream_t stream, int seg = -1) {
   // the condition estimate of the FP64 Gram comes from a one-lane instance
   const bool kappa_f64 = kappa && pl->host[0].precision == ESIM_GRAM_F64;
   const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : pl->lanes_dense;
   if (!esim::regress_supports(pl->F, L, pl->host[0].precision))
     return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
+  int max_r = 0, max_tr = 0;           // over the clips (of the segment)
+  for (const auto& c : pl->host)
+    if (seg < 0 || c.list_class == seg) {
+      max_r = std::max(max_r, static_cast<int>(c.r));
+      max_tr = std::max(max_tr, static_cast<int>(c.tr));
+    }
   esim::RegressArgs a{};
   a.clips = pl->dev;
   a.nclips = pl->nclips;
   a.t = t;
   a.items = worklist;
   a.count = count;
-  a.n_dense_groups = pl->dense_groups[esim::lanes_index(L)];
+  const bool tiles = !worklist && !kappa && L == 1 && pl->tile_units && pl->host[0].precision == ESIM_GRAM_F64;
+  const int dense = tiles ? 5 : esim::lanes_index(L);
+  a.tile_units = tiles ? pl->tile_units : 0;
+  a.tile_last = pl->tile_last;
+  a.n_dense_groups = pl->dense_groups[dense];
   const int G = esim::kWave / L;
   a.max_groups = worklist ? (std::max<int64_t>(n_out, 1) + G - 1) / G : a.n_dense_groups;
   a.n_out = n_out;
@@ -107,13 +118,12 @@ int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const 
   a.resid = resid;
   a.kappa = kappa;
   a.update_state = update_state ? 1 : 0;
-  a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * esim::lanes_index(L)
+  a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * dense
                                                 : nullptr;
   a.nxcd = pl->shape.xcds;
-  if (max_r < 0)
-    for (const auto& c : pl->host) max_r = std::max(max_r, static_cast<int>(c.r));
+  a.single = max_r <= 7 && max_tr <= 1 ? 1 : 0;
   return hip_check(esim::launch_regress(a, pl->F, pl->f16, pl->host[0].precision, L, pl->blocks_per_cu,
-                                        max_r, pl->shape, stream),
+                                        pl->shape, stream),
                    "regress");
 }
 
@@ -202,8 +212,10 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->nclips = nclips;
     pl->F = clips[0].F;
     pl->f16 = clips[0].feat_dtype == ESIM_F16;
-    int64_t pix = 0, blk = 0, grp[5] = {0, 0, 0, 0, 0};
+    int64_t pix = 0, blk = 0, grp[6] = {0, 0, 0, 0, 0, 0};
     int64_t wl = 0;
+    int tile_units = 0, tile_last = 0;
+    bool tiles_fit = true;
     for (int c = 0; c < nclips; ++c) {
       const esim_clip& k = clips[c];
       const esim_params& p = params[c];
@@ -294,6 +306,25 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
         cd.grp_off[q] = grp[q];
         grp[q] += (cd.HW + (esim::kWave / Ls[q]) - 1) / (esim::kWave / Ls[q]);
       }
+      {
+        // tiles of 64, 32 or 16 columns: the one that covers the image with the
+        // fewest pixels (the widest of equal ones)
+        int64_t best = -1;
+        for (int lw = 6; lw >= 4; --lw) {
+          const int64_t tw = 1 << lw, th = esim::kWave >> lw;
+          const int64_t n = ((k.W + tw - 1) / tw) * ((k.H + th - 1) / th);
+          if (best < 0 || n < best) {
+            best = n;
+            cd.tile_lw = lw;
+          }
+        }
+        cd.grp_off[5] = grp[5];
+        grp[5] += best;
+        // a row of the ring is loaded in at most two turns of the wave's lanes
+        tiles_fit = tiles_fit && (1 << cd.tile_lw) + 2 * p.r <= 2 * esim::kWave;
+        tile_last = std::max(tile_last, esim::tile_last_units(k.F, p.tr));
+        tile_units = std::max(tile_units, esim::tile_wave_units(k.F, p.r, p.tr, cd.tile_lw));
+      }
       cd.C = p.C;
       cd.h = p.h;
       cd.ridge = p.ridge;
@@ -342,16 +373,17 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
         cd.list_class = 2 * cd.r + 1 > 16 ? 1 : 0;
         if (cd.list_class) {
           wide = true;
-          pl->split_r[1] = std::max(pl->split_r[1], static_cast<int>(cd.r));
         } else {
           narrow = true;
           seg += cd.HW;
-          pl->split_r[0] = std::max(pl->split_r[0], static_cast<int>(cd.r));
         }
       }
       pl->split_seg = narrow && wide ? seg : -1;
     }
-    for (int q = 0; q < 5; ++q) pl->dense_groups[q] = grp[q];
+    for (int q = 0; q < 6; ++q) pl->dense_groups[q] = grp[q];
+    const size_t tile_block = (static_cast<size_t>(tile_units) * 4u * esim::regress_waves_per_simd(pl->F, false) + tile_last) * 16u;
+    pl->tile_last = tile_last;
+    pl->tile_units = tiles_fit && tile_block <= esim::kMaxTileLds ? tile_units : 0;
 
     // device memory: descriptors + workspace
     const size_t clip_bytes = sizeof(esim::ClipDev) * nclips;
@@ -364,7 +396,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     const size_t o_chunk = off;
     off = align(off + sizeof(int64_t) * ((blk + esim::kChunkBlocks - 1) / esim::kChunkBlocks));
     const size_t o_xcd = off;
-    off = align(off + sizeof(int64_t) * 5 * (esim::kMaxXcds + 1));
+    off = align(off + sizeof(int64_t) * 6 * (esim::kMaxXcds + 1));
     const size_t o_flags = off;
     off = align(off + sizeof(uint64_t) * blk * esim::kWavesPerBlock);
     const size_t o_pol = off;
@@ -388,8 +420,8 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     // by work (window size x groups per clip) rather than by count, since a
     // clip's items cost in proportion to its window.
     const int nx = pl->shape.xcds;
-    std::vector<int64_t> xb(5 * (esim::kMaxXcds + 1), 0);
-    for (int q = 0; q < 5; ++q) {
+    std::vector<int64_t> xb(6 * (esim::kMaxXcds + 1), 0);
+    for (int q = 0; q < 6; ++q) {
       int64_t* row = xb.data() + q * (esim::kMaxXcds + 1);
       double total = 0.0;
       std::vector<double> wc(nclips);
@@ -617,11 +649,11 @@ int esim_step(esim_plan pl, int32_t t, int32_t mode, float* dl, esim_events_buf*
       if (rc != ESIM_OK) return rc;
       if (split) {
         rc = launch_plan_regress(pl, t, pl->step_wl, pl->step_count, pl->split_seg, nullptr, nullptr, nullptr,
-                                 nullptr, true, s, pl->split_r[0]);
+                                 nullptr, true, s, 0);
         if (rc != ESIM_OK) return rc;
         return launch_plan_regress(pl, t, pl->step_wl + pl->split_seg, pl->step_count + 2,
                                    pl->wl_capacity - pl->split_seg, nullptr, nullptr, nullptr, nullptr, true, s,
-                                   pl->split_r[1]);
+                                   1);
       }
       if (pl->thr == ESIM_THRESHOLD_CLOSED)
         return launch_plan_regress(pl, t, pl->step_wl, pl->step_count, pl->wl_capacity, nullptr, nullptr,

@@ -30,7 +30,7 @@ struct ClipDev {
   int64_t pix_off;         // first pixel in the concatenated pixel range
   int64_t blk_off;         // first kBlock-pixel block of the flag/scatter grid
   int64_t nblk;            // kBlock-pixel blocks of this clip
-  int64_t grp_off[5];      // first dense wave-group, per lanes-per-item 1,2,4,8,16
+  int64_t grp_off[6];      // first dense wave-group, per lanes-per-item 1,2,4,8,16; [5]: first tile
   double C, h, ridge, kappa_fp64;
   double c2[ESIM_MAX_D];   // 1 / (h b_j)^2
   double sf[ESIM_MAX_D];   // 1 / (h b_j)
@@ -39,6 +39,7 @@ struct ClipDev {
   float* st_rmom;          // [2][HW] R and mean residual of the stored plane (nullable)
   int32_t thr;             // esim_threshold
   double dt;               // time between frames (event times t * dt)
+  int32_t tile_lw;         // log2 of the width of the clip's dense tiles (tiles of 256 pixels)
   int32_t list_class;      // 1: esim_step's split work list puts this clip's items in its second
                            // segment (windows wider than 16 columns), 0 otherwise
 };
@@ -99,6 +100,20 @@ __device__ __forceinline__ float ld_feat(__amdgpu_buffer_rsrc_t r, uint32_t voff
   else return ld_f32(r, voff, soff);
 }
 
+// Value of the first active lane, for values that every lane holds alike but that
+// the compiler may keep in vector registers (descriptor fields loaded where it
+// cannot rule out a store to them): buffer resources and loop bounds stay scalar.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uni(uint64_t v) {
+  return (static_cast<uint64_t>(static_cast<uint32_t>(uni(static_cast<int>(v >> 32)))) << 32) |
+         static_cast<uint32_t>(uni(static_cast<int>(v & 0xFFFFFFFFu)));
+}
+__device__ __forceinline__ double uni(double v) { return __builtin_bit_cast(double, uni(__builtin_bit_cast(uint64_t, v))); }
+template <class T>
+__device__ __forceinline__ T* uni(T* p) {
+  return reinterpret_cast<T*>(uni(static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p))));
+}
+
 // Lane-group sum with DPP.  After dpp_sum<L>(v) every lane of each aligned
 // group of L lanes (L in 1, 2, 4, 8, 16) holds the group's sum:
 //   quad_perm [1,0,3,2] and [2,3,0,1] give quad sums; row_half_mirror maps
@@ -148,6 +163,22 @@ __device__ __forceinline__ int item_clip(int64_t it) { return static_cast<int>((
 __device__ __forceinline__ int64_t item_pixel(int64_t it) { return it & 0xFFFFFFFFll; }
 __device__ __forceinline__ int item_frame(int64_t it) { return static_cast<int>(it >> 44); }
 
+// Tiles of a dense launch with one lane per pixel (esim_wlr.h): 64 pixels of 2^lw
+// columns, each wave with its own LDS.
+constexpr int tile_quads(int F) { return (F + 4) / 4; }                            // 16-byte units of F + 1 channels
+constexpr int tile_units(int F, int frames) { return (frames * tile_quads(F)) | 1; }   // of a pixel's record
+constexpr int kMaxTileFrames = 5;                                                  // walked at a time
+// 16-byte units of a wave's LDS for windows of radius r (the ring of rows), and
+// of the record behind a block's last wave that the look-ahead of a row's walk
+// may read.
+constexpr int tile_last_units(int F, int tr) {
+  return tile_units(F, 2 * tr + 1 < kMaxTileFrames ? 2 * tr + 1 : kMaxTileFrames);
+}
+constexpr int tile_wave_units(int F, int r, int tr, int lw) {
+  return tile_last_units(F, tr) * ((1 << lw) + 2 * r) * (kWave >> lw);
+}
+constexpr size_t kMaxTileLds = 160 * 1024 - 64;      // of a block (one per CU): the CU's LDS less the queue
+
 // ---- launchers (host) -----------------------------------------------------
 
 struct RegressArgs {
@@ -166,23 +197,32 @@ struct RegressArgs {
   int32_t update_state;     // write each item's model into its clip state (Sec. 2.2)
   const int64_t* xcd_bounds;  // dense multi-clip launches: [nxcd + 1] group bounds per XCD (device)
   int32_t nxcd;               // XCDs of the device (group-to-XCD mapping)
+  int32_t single;             // every item's window has at most 16 columns and three frames
+  int32_t tile_units;         // dense tiles: 16-byte units of a wave's LDS (0: groups of lanes, no tiles)
+  int32_t tile_last;          // and of the record behind the block's last wave
 };
 
 // Regression launcher: picks the kernel instance for (F, dtype, precision)
 // and the lanes-per-item L; returns hipSuccess or the launch error.
 using KernelFn = void (*)(RegressArgs);
 
-// Regression kernels of one feature count: general [lanes 1, 2, 4, 8, 16][f16],
-// one-pass [f16], compensated FP32 [lanes 4, 16][f16] (null where not compiled).
+// FP64 instances up to 8 features keep their sums within half the register file
+// and run two waves per SIMD (a wave's scalar and memory instructions then issue
+// beside the other wave's FMAs); larger F, and the compensated-FP32 variant, run
+// one.
+constexpr int regress_waves_per_simd(int F, bool c32) { return (!c32 && F <= 8) ? 2 : 1; }
+// Regression kernels of one feature count: FP64 Gram [lanes 1, 2, 4, 8, 16][f16],
+// compensated FP32 [lanes 4, 16][f16] (null where not compiled).
 struct RegressTable {
   KernelFn general[5][2] = {};
-  KernelFn onepass[2] = {};
+  KernelFn single[2] = {};     // 16 lanes per item, each with a single column of at most three frames
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item
+  KernelFn tile[2] = {};       // FP64 Gram, one lane per item, dense, windows in LDS
 };
 
 hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, int lanes,
-                          int blocks_per_cu, int max_r, const DeviceShape& dev, hipStream_t s);
+                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
 int regress_supported_lanes(int F);
 bool regress_supports(int F, int lanes, int precision);
 

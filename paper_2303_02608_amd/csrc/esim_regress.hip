@@ -1,5 +1,6 @@
 // Dispatch of the regression kernels (templates in esim_regress_impl.h, one
 // translation unit per feature count).
+#include <algorithm>
 #include <mutex>
 
 #include "esim_internal.h"
@@ -40,11 +41,6 @@ KernelFn pick(int F, int lanes, bool f16) {
   return (t && li >= 0) ? t->general[li][f16] : nullptr;
 }
 
-KernelFn pick_onepass(int F, bool f16) {
-  const RegressTable* t = table(F);
-  return t ? t->onepass[f16] : nullptr;
-}
-
 KernelFn pick_c32(int F, int lanes, bool f16) {
   const RegressTable* t = table(F);
   const int li = lanes == 4 ? 0 : lanes == 16 ? 1 : -1;
@@ -61,20 +57,34 @@ bool regress_supports(int F, int lanes, int precision) {
 }
 
 hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, int lanes,
-                          int blocks_per_cu, int max_r, const DeviceShape& dev, hipStream_t s) {
+                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s) {
   // the condition estimate (FP64 Gram) has an instance of its own, one lane
   // per item (the caller sizes the groups for one lane)
   const RegressTable* tab = table(F);
-  KernelFn fn = precision == ESIM_GRAM_F32C ? pick_c32(F, lanes, f16)
-                : a.kappa ? (tab ? tab->kappa[f16] : nullptr)
-                : (lanes == 16 && 2 * max_r + 1 <= 16) ? pick_onepass(F, f16)
-                                                       : pick(F, lanes, f16);
+  const bool c32 = precision == ESIM_GRAM_F32C;
+  KernelFn fn = c32          ? pick_c32(F, lanes, f16)
+                : a.kappa    ? (tab ? tab->kappa[f16] : nullptr)
+                : a.tile_units ? (tab ? tab->tile[f16] : nullptr)
+                : lanes == 16 && a.single ? (tab ? tab->single[f16] : nullptr)
+                             : pick(F, lanes, f16);
   if (!fn) return hipErrorInvalidValue;
-  int64_t blocks = (a.max_groups + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int64_t cap = static_cast<int64_t>(dev.cus) * blocks_per_cu;
+  // Tiles and the instances of 4 lanes and more take one block per CU that fills
+  // it, and hand out their groups themselves (GroupQueue); the others stride over
+  // the groups with the resident blocks (more would only start when those end).
+  const int resident = regress_waves_per_simd(F, c32);
+  const bool queue = a.tile_units || (!c32 && !a.kappa && lanes >= 4);
+  const int waves = queue ? 4 * resident : kWavesPerBlock;
+  int64_t blocks = queue ? a.max_groups : (a.max_groups + waves - 1) / waves;
+  const int64_t cap = static_cast<int64_t>(dev.cus) * (queue ? 1 : std::min(blocks_per_cu, resident));
   if (blocks > cap) blocks = cap;
+  if (blocks < 1) blocks = 1;
   blocks = (blocks + dev.xcds - 1) / dev.xcds * dev.xcds;   // a multiple of the XCDs (see GroupIter)
-  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, s, a);
+  const size_t lds = a.tile_units ? (static_cast<size_t>(a.tile_units) * waves + a.tile_last) * 16u : 0;
+  if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         static_cast<int>(lds)) != hipSuccess)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(static_cast<unsigned>(kWave * waves)),
+                     lds, s, a);
   return hipGetLastError();
 }
 

@@ -17,16 +17,18 @@ void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   t.general[0][1] = regress_kernel<F, 1, true, false>;
   t.general[1][0] = regress_kernel<F, 2, false, false>;
   t.general[1][1] = regress_kernel<F, 2, true, false>;
-  t.general[2][0] = regress_kernel<F, 4, false, false>;
-  t.general[2][1] = regress_kernel<F, 4, true, false>;
-  t.general[3][0] = regress_kernel<F, 8, false, false>;
-  t.general[3][1] = regress_kernel<F, 8, true, false>;
-  t.general[4][0] = regress_kernel<F, 16, false, false>;
-  t.general[4][1] = regress_kernel<F, 16, true, false>;
-  t.onepass[0] = regress_kernel<F, 16, false, false, true>;
-  t.onepass[1] = regress_kernel<F, 16, true, false, true>;
-  t.kappa[0] = regress_kernel<F, 1, false, false, false, true>;
-  t.kappa[1] = regress_kernel<F, 1, true, false, false, true>;
+  t.general[2][0] = regress_list_kernel<F, 4, false>;
+  t.general[2][1] = regress_list_kernel<F, 4, true>;
+  t.general[3][0] = regress_list_kernel<F, 8, false>;
+  t.general[3][1] = regress_list_kernel<F, 8, true>;
+  t.general[4][0] = regress_list_kernel<F, 16, false>;
+  t.general[4][1] = regress_list_kernel<F, 16, true>;
+  t.single[0] = regress_list_kernel<F, 16, false, true>;
+  t.single[1] = regress_list_kernel<F, 16, true, true>;
+  t.tile[0] = regress_tile_kernel<F, false>;
+  t.tile[1] = regress_tile_kernel<F, true>;
+  t.kappa[0] = regress_kernel<F, 1, false, false, true>;
+  t.kappa[1] = regress_kernel<F, 1, true, false, true>;
   // the compensated-FP32 variant is compiled for the feature counts of the
   // workloads (7 and 10) and for the default lane counts
 #if ESIM_REGRESS_F == 7 || ESIM_REGRESS_F == 10

@@ -293,6 +293,461 @@ __device__ __forceinline__ void window_loop_ring(const ItemGeom<F, F16, double>&
   }
 }
 
+// ---- the column walk of the FP64 regression -------------------------------
+//
+// One lane owns one column of an item's window at a time and walks its rows
+// from dy = -r to r, the frames of a row innermost, so that both coordinates
+// are constant over the 2 tr + 1 samples of a cell (dx, dy).  No entry with a
+// coordinate factor is summed per sample:
+//   v_y  the running column sums C_k of (w, w y, w f) after cell k are added up
+//        once per cell, P = sum_k C_k; a cell at dy is then counted r + 1 - dy
+//        times, so sum dy s = (r + 1) C - P, and with PP = sum_k P_k
+//        sum dy^2 s = (r + 1)^2 C - (2 r + 3) P + 2 PP;
+//   v_x  constant in the column: a factor of the column's sums.
+// A cell at tr = 1 spends 10 adds there, where one row of samples at a time
+// spent 11 fused multiply-adds and a multiply per sample.  The sums grow to
+// 2 r + 1 times the totals, so the differences keep an error of the order of
+// 2^-53 in the W-normalised, bandwidth-scaled system.
+//
+// Samples outside the image read the nearest pixel inside it, which lies in
+// the window too (so a NaN there counts where it counts anyway), and get
+// weight 0 through an exponent of kDropped.  Frames outside the clip are not
+// walked: the caller passes lanes whose items share dt_lo and nt.
+
+constexpr double kDropped = -65536.0;    // exponent (base 2) of a sample of weight 0
+
+// Sums of one column (the last line: of all columns of a lane).
+template <int F>
+struct ColumnSums {
+  static constexpr int NA = F * (F + 1) / 2;
+  double W, g, f[F];               // running column sums of w, w y, w f
+  double PW, Pg, Pf[F], PPW;       // their sums over the cells, and the sums of PW
+  double Syy, gf[F], Aff[NA];
+
+  __device__ __forceinline__ void zero() {
+    W = g = PW = Pg = PPW = Syy = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) f[k] = Pf[k] = gf[k] = 0;
+#pragma unroll
+    for (int k = 0; k < NA; ++k) Aff[k] = 0;
+  }
+  __device__ __forceinline__ void add(double w, double yd, const double (&v)[F]) {
+    const double wy = w * yd;
+    W += w;
+    g += wy;
+    Syy = fma(wy, yd, Syy);
+    int q = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+      const double wz = w * v[k];
+      f[k] += wz;
+      gf[k] = fma(wz, yd, gf[k]);
+#pragma unroll
+      for (int e = k; e < F; ++e) {
+        Aff[q] = fma(wz, v[e], Aff[q]);
+        ++q;
+      }
+    }
+  }
+  __device__ __forceinline__ void end_cell() {
+    PW += W;
+    PPW += PW;
+    Pg += g;
+#pragma unroll
+    for (int k = 0; k < F; ++k) Pf[k] += f[k];
+  }
+};
+
+// What the finished columns of a lane add up to, and their sums times v_x.
+template <int F>
+struct LaneSums {
+  double W, g, f[F], PW, PPW, Pg, Pf[F];
+  double XW, Xg, Xf[F], XX, XPW;
+
+  __device__ __forceinline__ void zero() {
+    W = g = PW = PPW = Pg = XW = Xg = XX = XPW = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) f[k] = Pf[k] = Xf[k] = 0;
+  }
+  // Takes over the column at v_x and clears its part of c (the sums without a
+  // coordinate factor stay in c).
+  __device__ __forceinline__ void end_column(ColumnSums<F>& c, double vx) {
+    W += c.W;
+    XW = fma(vx, c.W, XW);
+    XX = fma(vx * vx, c.W, XX);
+    XPW = fma(vx, c.PW, XPW);
+    g += c.g;
+    Xg = fma(vx, c.g, Xg);
+    PW += c.PW;
+    PPW += c.PPW;
+    Pg += c.Pg;
+    c.W = c.g = c.PW = c.PPW = c.Pg = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+      f[k] += c.f[k];
+      Xf[k] = fma(vx, c.f[k], Xf[k]);
+      Pf[k] += c.Pf[k];
+      c.f[k] = c.Pf[k] = 0;
+    }
+  }
+};
+
+// Geometry of the column walk of one lane's item.
+template <int F, bool F16>
+struct WalkGeom {
+  static constexpr uint32_t ES = F16 ? 2u : 4u;
+  __amdgpu_buffer_rsrc_t ry, rf;
+  uint32_t HW;
+  uint32_t vf0, vy0;               // byte offsets of (frame tt + dt_lo, row max(py - r, 0), column 0)
+  int W, H, r, nt, px, py;
+  bool active;
+  double sf[F], xcs[F];
+  double vx_step, vy_step;
+};
+
+// Fills the geometry of the item at (pix, tt) of clip C, whose window holds the
+// nt frames from tt + dt_lo on.  f0/f1 are the frames the buffer resources cover
+// (a uniform frame's window, or the whole clip).
+template <int F, bool F16>
+__device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C, int64_t pix, int tt, int dt_lo,
+                                          int nt, int f0, int f1, bool active) {
+  constexpr uint32_t ES = WalkGeom<F, F16>::ES;
+  g.W = uni(C.W);
+  g.H = uni(C.H);
+  g.r = uni(C.r);
+  g.nt = nt;
+  g.HW = static_cast<uint32_t>(uni(static_cast<int>(C.HW)));
+  g.active = active;
+  g.ry = make_rsrc(uni(C.y) + static_cast<uint64_t>(f0) * g.HW, static_cast<uint64_t>(f1 - f0) * g.HW * 4u);
+  g.rf = make_rsrc(static_cast<const char*>(uni(C.feat)) + static_cast<uint64_t>(f0) * F * g.HW * ES,
+                   static_cast<uint64_t>(f1 - f0) * F * g.HW * ES);
+  const uint32_t up = static_cast<uint32_t>(pix), uw = static_cast<uint32_t>(g.W);
+  g.py = static_cast<int>(up / uw);
+  g.px = static_cast<int>(up - static_cast<uint32_t>(g.py) * uw);
+  const uint32_t fc = static_cast<uint32_t>(tt - f0);
+  const uint32_t fl = static_cast<uint32_t>(tt + dt_lo - f0);
+  const uint32_t row0 = static_cast<uint32_t>(max(g.py - g.r, 0)) * uw;
+  g.vf0 = (fl * F * g.HW + row0) * ES;
+  g.vy0 = (fl * g.HW + row0) * 4u;
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    g.sf[f] = uni(C.sf[2 + f]);
+    g.xcs[f] = static_cast<double>(ld_feat<F16>(g.rf, (fc * F * g.HW + up) * ES, f * g.HW * ES)) * g.sf[f];
+  }
+  g.vx_step = C.sf[0] / g.r;
+  g.vy_step = C.sf[1] / g.r;
+}
+
+// Walks R consecutive frames, the first k0 frames after dt_lo, of the column dx
+// of the lane's item (dx > r: an idle column, weight 0), adding their samples to
+// c.  DEPTH (1 or 2) cells of samples are loaded ahead: a sample's registers are
+// reloaded as soon as it is used.
+template <int F, bool F16, int R, int DEPTH = 1>
+__device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, ColumnSums<F>& c) {
+  constexpr uint32_t ES = WalkGeom<F, F16>::ES;
+  constexpr double K = kHalfLog2e;
+  const int r = g.r;
+  const int col = g.px + dx;
+  const bool col_ok = g.active && dx <= r && static_cast<uint32_t>(col) < static_cast<uint32_t>(g.W);
+  const uint32_t cc = static_cast<uint32_t>(min(max(g.px + min(dx, r), 0), g.W - 1));
+  const double vx = static_cast<double>(dx) * g.vx_step;
+  const double kx = col_ok ? K * vx * vx : kDropped;
+  const double kyy = K * g.vy_step * g.vy_step;
+  const uint32_t WES = static_cast<uint32_t>(g.W) * ES, W4 = static_cast<uint32_t>(g.W) * 4u;
+  const uint32_t HES = g.HW * ES, FES = static_cast<uint32_t>(F) * HES, HW4 = g.HW * 4u;
+  const uint32_t sof = static_cast<uint32_t>(k0) * FES, soy = static_cast<uint32_t>(k0) * HW4;   // uniform
+  uint32_t vf = g.vf0 + cc * ES, vy = g.vy0 + cc * 4u;         // offsets of the next row to load
+  float ys[DEPTH][R], fs[DEPTH][R][F];
+  auto load = [&](int d, int i) {
+    ys[d][i] = ld_f32(g.ry, vy, soy + i * HW4);
+#pragma unroll
+    for (int f = 0; f < F; ++f) fs[d][i][f] = ld_feat<F16>(g.rf, vf, sof + i * FES + f * HES);
+  };
+  auto next_row = [&](int dy) {            // a step down where rows dy and dy + 1 are in the image
+    const bool down = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H - 1);
+    vf += down ? WES : 0u;
+    vy += down ? W4 : 0u;
+  };
+  auto cell = [&](int d, int dy) {
+    next_row(dy + DEPTH - 1);
+    const double e = fma(kyy, static_cast<double>(dy * dy), kx);
+    const double base = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H) ? e : kDropped;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      double v[F], s0 = 0, s1 = 0;
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        v[f] = fma(static_cast<double>(fs[d][i][f]), g.sf[f], -g.xcs[f]);
+        if (f & 1) s1 = fma(v[f], v[f], s1);
+        else s0 = fma(v[f], v[f], s0);
+      }
+      const double arg = fma(s0 + s1, K, base);
+      const double w = static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(arg)));
+      const double yd = static_cast<double>(ys[d][i]);
+      load(d, i);
+      c.add(w, yd, v);
+    }
+    c.end_cell();
+  };
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) load(d, i);
+    if (d + 1 < DEPTH) next_row(d - r);
+  }
+  if constexpr (DEPTH == 1) {
+#pragma unroll 1
+    for (int dy = -r; dy <= r; ++dy) cell(0, dy);
+  } else {
+    // 2 r + 1 rows: pairs, and the last one
+#pragma unroll 1
+    for (int dy = -r; dy < r; dy += 2) {
+      cell(0, dy);
+      cell(1, dy + 1);
+    }
+    cell(0, r);
+  }
+}
+
+// The columns j, j + L, ... of the lane's item, up to three frames at a time
+// (three rows of loads in flight); the totals go to c (entries without a
+// coordinate) and ls.
+template <int F, int L, bool F16>
+__device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, ColumnSums<F>& c, LaneSums<F>& ls) {
+  c.zero();
+  ls.zero();
+#pragma unroll 1
+  for (int d0 = -g.r; d0 <= g.r; d0 += L) {
+    const double vx = static_cast<double>(d0 + j) * g.vx_step;
+#pragma unroll 1
+    for (int k0 = 0; k0 < g.nt; k0 += 3) {
+      const int n = g.nt - k0;
+      if (n >= 3) walk_frames<F, F16, 3>(g, d0 + j, k0, c);
+      else if (n == 2) walk_frames<F, F16, 2>(g, d0 + j, k0, c);
+      else walk_frames<F, F16, 1>(g, d0 + j, k0, c);
+      ls.end_column(c, vx);
+    }
+  }
+}
+
+// ---- dense windows from LDS ------------------------------------------------
+//
+// Every pixel of a frame, one lane per pixel: a wave owns a tile of 64 pixels
+// (64 x 1, 32 x 2 or 16 x 4) and keeps the rows of the window that its pixels are
+// reading in its own LDS, one record of all channels per pixel: (frames of a
+// cell) x (features and y), single precision, in 16-byte units.  A lane walks its
+// window row by row, so a step of the walk is one record further; the walked
+// coordinate of ColumnSums is v_x here and the lines' one is v_y.  The rows are a
+// ring as high as the tile; a new row replaces the one that left.
+//
+// Read straight from memory, a sample is 8 loads at F = 7, and 64 lanes' window
+// rows do not stay in the L1: every column pass fetched its 90 KB from L2 again,
+// 12 cycles a load of the CU's one vector memory path, so that the four SIMDs' 32
+// loads a sample took longer than the 87 VALU instructions beside them.  From LDS a
+// sample is two 16-byte reads, and memory is read once per row.  Records have an
+// odd number of units, so that neighbouring lanes' reads fall on different banks.
+//
+// The tile is a wave's and not a block's so that no wave waits at a barrier: a
+// SIMD issues its older wave first, which takes three of four issue slots, and
+// the younger one the rest.  Waves that keep step at barriers, or that are given
+// equal shares, leave the younger ones to run alone for half of the launch, at the
+// 5.5 cycles a VALU instruction that one wave reaches; waves that fetch their next
+// tile when they are done fill the slots to the end (see GroupQueue).
+
+// One tile of one clip at frame tt.
+template <int F, bool F16>
+struct TileGeom {
+  static constexpr uint32_t ES = F16 ? 2u : 4u;
+  __amdgpu_buffer_rsrc_t ry, rf;
+  uint32_t HW;
+  int W, H, r, nt, lw;             // tile width 2^lw
+  int x0, y0;                      // the tile's first pixel
+  int px, py;                      // this lane's pixel (may lie outside the image)
+  double sf[F], xcs[F];
+  double vx_step, vy_step;
+};
+
+template <int F, bool F16>
+__device__ __forceinline__ void make_tile(TileGeom<F, F16>& g, const ClipDev& C, int tile, int tt) {
+  constexpr uint32_t ES = TileGeom<F, F16>::ES;
+  const int lane = threadIdx.x & (kWave - 1);
+  g.W = uni(C.W);
+  g.H = uni(C.H);
+  g.r = uni(C.r);
+  g.lw = uni(C.tile_lw);
+  g.HW = static_cast<uint32_t>(uni(static_cast<int>(C.HW)));
+  const int tr = uni(C.tr), T = uni(C.T);
+  const int f0 = max(0, tt - tr), f1 = min(T, tt + tr + 1);
+  g.nt = f1 - f0;
+  g.ry = make_rsrc(uni(C.y) + static_cast<uint64_t>(f0) * g.HW, static_cast<uint64_t>(f1 - f0) * g.HW * 4u);
+  g.rf = make_rsrc(static_cast<const char*>(uni(C.feat)) + static_cast<uint64_t>(f0) * F * g.HW * ES,
+                   static_cast<uint64_t>(f1 - f0) * F * g.HW * ES);
+  const int ntx = (g.W + (1 << g.lw) - 1) >> g.lw;
+  const int ty = tile / ntx;
+  g.x0 = (tile - ty * ntx) << g.lw;
+  g.y0 = ty * (kWave >> g.lw);
+  g.px = g.x0 + (lane & ((1 << g.lw) - 1));
+  g.py = g.y0 + (lane >> g.lw);
+  const uint32_t cen = static_cast<uint32_t>(min(g.py, g.H - 1)) * static_cast<uint32_t>(g.W) +
+                       static_cast<uint32_t>(min(g.px, g.W - 1));
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    g.sf[f] = uni(C.sf[2 + f]);
+    g.xcs[f] = static_cast<double>(ld_feat<F16>(g.rf, (static_cast<uint32_t>(tt - f0) * F * g.HW + cen) * ES,
+                                                f * g.HW * ES)) * g.sf[f];
+  }
+  g.vx_step = C.sf[0] / g.r;
+  g.vy_step = C.sf[1] / g.r;
+}
+
+// Orders a wave's LDS accesses before and after it (between lanes of the wave:
+// the hardware runs a wave's LDS instructions in order, the compiler must too).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Row y of the image on its way to a ring slot: frames k0 .. k0 + R - 1 of the
+// window, columns x0 - r .. x0 + 2^lw + r - 1 (at most 2 kWave), row and columns
+// clamped to the image.  load issues the loads of turn h of the wave's lanes,
+// store writes them to LDS.
+template <int F, bool F16, int R>
+struct RowLoads {
+  static constexpr uint32_t ES = TileGeom<F, F16>::ES;
+  static constexpr int NQ = tile_quads(F), U = tile_units(F, R);
+  float v[R][4 * NQ];
+
+  __device__ __forceinline__ void load(const TileGeom<F, F16>& g, int h, int y, int k0) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t row = static_cast<uint32_t>(min(max(y, 0), g.H - 1)) * static_cast<uint32_t>(g.W);
+    const uint32_t x = static_cast<uint32_t>(min(max(g.x0 - g.r + lane + h * kWave, 0), g.W - 1));
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
+      for (int c = 0; c < 4 * NQ; ++c) {
+        if (c < F)
+          v[i][c] = ld_feat<F16>(g.rf, x * ES, (static_cast<uint32_t>((k0 + i) * F + c) * g.HW + row) * ES);
+        else
+          v[i][c] = c == F ? ld_f32(g.ry, x * 4u, (static_cast<uint32_t>(k0 + i) * g.HW + row) * 4u) : 0.0f;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(const TileGeom<F, F16>& g, float4* lds, int h, int slot) const {
+    const int p = static_cast<int>(threadIdx.x & (kWave - 1)) + h * kWave;
+    const int rowpx = (1 << g.lw) + 2 * g.r;
+    if (p < rowpx) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          lds[(slot * rowpx + p) * U + i * NQ + q] =
+              make_float4(v[i][4 * q], v[i][4 * q + 1], v[i][4 * q + 2], v[i][4 * q + 3]);
+    }
+  }
+};
+
+template <int F, bool F16, int R>
+__device__ __forceinline__ void stage_row(const TileGeom<F, F16>& g, float4* lds, int slot, int y, int k0) {
+  for (int h = 0; h * kWave < (1 << g.lw) + 2 * g.r; ++h) {
+    RowLoads<F, F16, R> in;
+    in.load(g, h, y, k0);
+    in.store(g, lds, h, slot);
+  }
+}
+
+// Walks R frames (from the window's k0-th on) of the windows of the wave's pixels.
+template <int F, bool F16, int R>
+__device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* lds, int k0, ColumnSums<F>& c,
+                                            LaneSums<F>& ls) {
+  constexpr double K = kHalfLog2e;
+  constexpr int NQ = tile_quads(F), U = tile_units(F, R);
+  // A wave alone on its SIMD loads the next row while it walks this one; where
+  // two share it, the other one walks meanwhile and the registers are short.
+  constexpr bool AHEAD = regress_waves_per_simd(F, false) == 1;
+  const int r = g.r, TH = kWave >> g.lw, rowpx = (1 << g.lw) + 2 * r;
+  wave_lds_order();                                            // after the reads of an earlier walk
+  for (int s = 0; s + 1 < TH; ++s) stage_row<F, F16, R>(g, lds, s, g.y0 - r + s, k0);
+  const double kxx = K * g.vx_step * g.vx_step;
+  const float4* base = lds + static_cast<int>(threadIdx.x & ((1u << g.lw) - 1u)) * U;
+  int slot = g.py - g.y0;                                      // of this lane's row
+  int next = TH - 1;                                           // of the row to stage
+  RowLoads<F, F16, R> in[2];
+  if constexpr (AHEAD) {
+    in[0].load(g, 0, g.y0 - r + TH - 1, k0);
+    in[1].load(g, 1, g.y0 - r + TH - 1, k0);
+  }
+#pragma unroll 1
+  for (int dy = -r; dy <= r; ++dy) {
+    if constexpr (AHEAD) {
+      in[0].store(g, lds, 0, next);
+      in[1].store(g, lds, 1, next);
+      in[0].load(g, 0, g.y0 + dy + TH, k0);                    // past the last row: never stored
+      in[1].load(g, 1, g.y0 + dy + TH, k0);
+    } else {
+      stage_row<F, F16, R>(g, lds, next, g.y0 + dy + TH - 1, k0);
+    }
+    wave_lds_order();
+    const double vy = static_cast<double>(dy) * g.vy_step;
+    const double ky = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H) ? K * vy * vy : kDropped;
+    const float4* at = base + slot * (rowpx * U);
+    float4 q[NQ];                                              // the next sample
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) q[k] = at[k];
+#pragma unroll 1
+    for (int dx = -r; dx <= r; ++dx) {
+      const double e = fma(kxx, static_cast<double>(dx * dx), ky);
+      const double cell = static_cast<uint32_t>(g.px + dx) < static_cast<uint32_t>(g.W) ? e : kDropped;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        float ch[4 * NQ];
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+          ch[4 * k] = q[k].x;
+          ch[4 * k + 1] = q[k].y;
+          ch[4 * k + 2] = q[k].z;
+          ch[4 * k + 3] = q[k].w;
+        }
+        double v[F], s0 = 0, s1 = 0;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          v[f] = fma(static_cast<double>(ch[f]), g.sf[f], -g.xcs[f]);
+          if (f & 1) s1 = fma(v[f], v[f], s1);
+          else s0 = fma(v[f], v[f], s0);
+        }
+        const double arg = fma(s0 + s1, K, cell);
+        const double w = static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(arg)));
+        const double yd = static_cast<double>(ch[F]);
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) q[k] = at[(i + 1 < R ? (i + 1) * NQ : U) + k];
+        c.add(w, yd, v);
+      }
+      at += U;
+      c.end_cell();
+    }
+    ls.end_column(c, vy);
+    wave_lds_order();
+    next = next + 1 == TH ? 0 : next + 1;
+    slot = slot + 1 == TH ? 0 : slot + 1;
+  }
+}
+
+// The whole window of the lane's pixel.
+template <int F, bool F16>
+__device__ __forceinline__ void tile_window(const TileGeom<F, F16>& g, float4* lds, ColumnSums<F>& c,
+                                            LaneSums<F>& ls) {
+  c.zero();
+  ls.zero();
+#pragma unroll 1
+  for (int k0 = 0; k0 < g.nt; k0 += kMaxTileFrames) {
+    const int n = g.nt - k0;
+    if (n == 3) tile_frames<F, F16, 3>(g, lds, k0, c, ls);
+    else if (n >= 5) tile_frames<F, F16, 5>(g, lds, k0, c, ls);
+    else if (n == 4) tile_frames<F, F16, 4>(g, lds, k0, c, ls);
+    else if (n == 2) tile_frames<F, F16, 2>(g, lds, k0, c, ls);
+    else tile_frames<F, F16, 1>(g, lds, k0, c, ls);
+  }
+}
+
 // Normal equations of one item, accumulated per lane.  Within a column pass
 // v_x is constant in a lane, so the entries with a v_x factor are not summed
 // per sample: they are v_x times sums of the first-row entries (formed once per
@@ -375,6 +830,29 @@ struct Gram {
 #pragma unroll
     for (int f = 0; f < F; ++f) Axf[f] = fma(vx, A0f[f] - qF[f], Axf[f]);
   }
+  // Calls fn on every total, in a fixed order.
+  template <class Fn>
+  __device__ __forceinline__ void each(Fn&& fn) {
+    fn(SW);
+    fn(A0y);
+    fn(g0);
+    fn(A0x);
+    fn(Axx);
+    fn(Axy);
+    fn(gx);
+    fn(Ayy);
+    fn(gy);
+    fn(Syy);
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      fn(A0f[f]);
+      fn(Axf[f]);
+      fn(Ayf[f]);
+      fn(gf[f]);
+    }
+#pragma unroll
+    for (int k = 0; k < NA; ++k) fn(Aff[k]);
+  }
   // Applies one DPP butterfly step to every total; the steps run in sequence
   // over all totals (step-major), so consecutive DPP reads never depend on
   // the previous instruction.
@@ -409,6 +887,134 @@ struct Gram {
     if constexpr (L >= 16) dpp_step<0x140>();
   }
 };
+
+// Totals of the lane's part of its item from its walk: along columns (v_y is the
+// walked coordinate, steps of s, and v_x the lines' one) or, ROWS, along rows.
+template <int F, bool ROWS = false>
+__device__ __forceinline__ void gram_of_lane(const ColumnSums<F>& c, const LaneSums<F>& l, double s, int r,
+                                             Gram<F, double>& G) {
+  const double r1 = static_cast<double>(r + 1);
+  const double first = s * fma(r1, l.W, -l.PW);
+  const double second = s * s * fma(r1 * r1, l.W, fma(-static_cast<double>(2 * r + 3), l.PW, 2.0 * l.PPW));
+  const double gwalk = s * fma(r1, l.g, -l.Pg);
+  G.SW = l.W;
+  G.g0 = l.g;
+  G.Syy = c.Syy;
+  G.A0x = ROWS ? first : l.XW;
+  G.A0y = ROWS ? l.XW : first;
+  G.Axx = ROWS ? second : l.XX;
+  G.Ayy = ROWS ? l.XX : second;
+  G.gx = ROWS ? gwalk : l.Xg;
+  G.gy = ROWS ? l.Xg : gwalk;
+  G.Axy = s * fma(r1, l.XW, -l.XPW);
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    const double fwalk = s * fma(r1, l.f[f], -l.Pf[f]);
+    G.A0f[f] = l.f[f];
+    G.gf[f] = c.gf[f];
+    G.Axf[f] = ROWS ? fwalk : l.Xf[f];
+    G.Ayf[f] = ROWS ? l.Xf[f] : fwalk;
+  }
+#pragma unroll
+  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
+}
+
+// The same for a lane with a single column, at v_x.
+template <int F>
+__device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx, double s, int r,
+                                               Gram<F, double>& G) {
+  const double r1 = static_cast<double>(r + 1);
+  G.SW = c.W;
+  G.g0 = c.g;
+  G.Syy = c.Syy;
+  G.A0x = vx * c.W;
+  G.Axx = vx * G.A0x;
+  G.gx = vx * c.g;
+  G.A0y = s * fma(r1, c.W, -c.PW);
+  G.Ayy = s * s * fma(r1 * r1, c.W, fma(-static_cast<double>(2 * r + 3), c.PW, 2.0 * c.PPW));
+  G.Axy = vx * G.A0y;
+  G.gy = s * fma(r1, c.g, -c.Pg);
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    G.A0f[f] = c.f[f];
+    G.gf[f] = c.gf[f];
+    G.Axf[f] = vx * c.f[f];
+    G.Ayf[f] = s * fma(r1, c.f[f], -c.Pf[f]);
+  }
+#pragma unroll
+  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
+}
+
+// ---- lane sums that leave each total in one lane ---------------------------
+//
+// A step halves both the lanes that share a value and the values a lane holds:
+// partners exchange a pair (a, b), one keeps a's sum and the other b's.  The L
+// lanes of an item lie in all four rows of 16 lanes (item_slot, item_lane), so
+// the first two steps are row swaps: two swaps and an add for each of the 33 and
+// 17 pairs at F = 7.  With the two steps inside a quad that is 250 instructions
+// for the 66 totals over 16 lanes, where summing every total in every lane takes
+// 12 per total.  (Loads do not mind the spread: the vector memory path returns
+// eight lanes a cycle whether 64, 16 or 4 neighbouring lanes read one line.)
+
+// Item of the wave (64 / L of them) and lane of the item, from the wave's lane.
+template <int L>
+__device__ __forceinline__ int item_slot(int lane) { return (lane & 15) / (L / 4); }
+template <int L>
+__device__ __forceinline__ int item_lane(int lane) { return (lane >> 4) * (L / 4) + (lane & (L / 4 - 1)); }
+
+// Partners in the other half of the wave (ROWS = 2) or in the neighbouring row
+// of each half (ROWS = 1): the lower one keeps the sum of a, the upper one b's.
+template <int ROWS>
+__device__ __forceinline__ double row_sum(double a, double b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+  uint32_t lo[2] = {static_cast<uint32_t>(x), static_cast<uint32_t>(y)};
+  uint32_t hi[2] = {static_cast<uint32_t>(x >> 32), static_cast<uint32_t>(y >> 32)};
+  if constexpr (ROWS == 2) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo[0], lo[1], false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi[0], hi[1], false, false);
+    lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo[0], lo[1], false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi[0], hi[1], false, false);
+    lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+  }
+  return __builtin_bit_cast(double, static_cast<uint64_t>(hi[0]) << 32 | lo[0]) +
+         __builtin_bit_cast(double, static_cast<uint64_t>(hi[1]) << 32 | lo[1]);
+}
+
+// Partners at lane distance D inside a quad.
+template <int D>
+__device__ __forceinline__ double quad_sum(double a, double b, int lane) {
+  const bool up = (lane & D) != 0;
+  const double keep = up ? b : a, send = up ? a : b;
+  return keep + dpp_d<D == 2 ? 0x4E : 0xB1>(send);     // quad_perm [2,3,0,1], [1,0,3,2]
+}
+
+// Sums s over the L lanes of each item; afterwards value e is register
+// total_pos(e) / L of the item's lane total_pos(e) % L.
+template <int L, int N, int STEP = 0>
+__device__ __forceinline__ void scatter_sum(double (&s)[N], int lane) {
+  constexpr int M = (N + 1) / 2;
+  double t[M];
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    const double a = s[2 * k], b = 2 * k + 1 < N ? s[2 * k + 1] : 0.0;
+    if constexpr (STEP == 0) t[k] = row_sum<2>(a, b);
+    else if constexpr (STEP == 1) t[k] = row_sum<1>(a, b);
+    else t[k] = quad_sum<(L >> (STEP + 1))>(a, b, lane);
+  }
+  if constexpr ((L >> (STEP + 1)) > 1) scatter_sum<L, M, STEP + 1>(t, lane);
+#pragma unroll
+  for (int k = 0; k < M; ++k) s[k] = t[k];
+}
+
+template <int L>
+__host__ __device__ constexpr int total_pos(int e) {
+  int low = 0;
+  for (int b = 1, m = L >> 1; b < L; b <<= 1, m >>= 1)
+    if (e & b) low |= m;
+  return e / L * L + low;
+}
 
 // Neumaier-compensated accumulation: (hi, lo) += x.
 __device__ __forceinline__ void neumaier(float& hi, float& lo, float x) {
@@ -532,7 +1138,7 @@ struct GroupIter {
   int64_t g, end, step;
   __device__ __forceinline__ GroupIter(int64_t ngroups, int nxcd, const int64_t* xb = nullptr) {
     const int64_t nblk = gridDim.x;
-    const int64_t wib = threadIdx.x / kWave;            // wave in block
+    const int64_t wib = uni(static_cast<int>(threadIdx.x) / kWave);   // wave in block
     const int64_t wpb = blockDim.x / kWave;
     const int64_t nx = nxcd;
     if (nx > 1 && nblk >= nx && nblk % nx == 0) {
@@ -561,6 +1167,38 @@ struct GroupIter {
     g += step;
     return true;
   }
+};
+
+// The groups of a launch of one block per CU: each block gets an equal share and
+// its waves fetch one after the other from a counter in LDS, so that a wave that
+// is issued less often (or that waits longer for memory) gets fewer.  Which wave
+// runs a group does not matter to its results.  One clip: a share is a run of
+// consecutive groups (neighbouring pixels in the CU's L1), the XCDs' blocks side
+// by side.  Several clips, whose groups cost in proportion to their windows:
+// every nblk-th group.
+struct GroupQueue {
+  int64_t first, step, count;      // the block's groups: first + k step, k < count
+  int* taken;                      // LDS: groups handed out
+
+  __device__ __forceinline__ GroupQueue(int64_t ngroups, int nclips, int nxcd, int* counter) : taken(counter) {
+    const int64_t nblk = gridDim.x, nx = nblk % nxcd == 0 ? nxcd : 1;
+    const int64_t b = static_cast<int64_t>(blockIdx.x % nx) * (nblk / nx) + blockIdx.x / nx;
+    first = nclips == 1 ? b * ngroups / nblk : b;
+    step = nclips == 1 ? 1 : nblk;
+    count = nclips == 1 ? (b + 1) * ngroups / nblk - first : ngroups > b ? (ngroups - b + nblk - 1) / nblk : 0;
+    if (threadIdx.x == 0) *taken = static_cast<int>(blockDim.x / kWave);
+    __syncthreads();
+  }
+  // The wave's first group, as its index k in the block's share: waves side by
+  // side lie on different SIMDs, so that a share of a few groups spreads over them.
+  __device__ __forceinline__ int64_t start() const { return uni(static_cast<int>(threadIdx.x) / kWave); }
+  // The wave's next group (uniform over the wave); from `count` on there is none.
+  __device__ __forceinline__ int64_t next() const {
+    int k = 0;
+    if ((threadIdx.x & (kWave - 1)) == 0) k = atomicAdd(taken, 1);
+    return uni(k);
+  }
+  __device__ __forceinline__ int64_t group(int64_t k) const { return first + k * step; }
 };
 
 // Hardware estimates of 1/sqrt(x) and 1/x.
