@@ -85,14 +85,10 @@ bool query_device_shape(DeviceShape& out) {
 
 namespace {
 
-int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count,
-                        int64_t n_out, float* alpha, float* beta, float* resid, float* kappa,
-                        bool update_state, hipStream_t stream, int seg = -1) {
-  // the condition estimate of the FP64 Gram comes from a one-lane instance
-  const bool kappa_f64 = kappa && pl->host[0].precision == ESIM_GRAM_F64;
-  const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : pl->lanes_dense;
-  if (!esim::regress_supports(pl->F, L, pl->host[0].precision))
-    return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
+// Arguments of a regression launch with L lanes per item; seg: the clips of one
+// segment of a split work list only (-1: all).
+esim::RegressArgs regress_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
+                               int L, bool kappa, int seg = -1) {
   int max_r = 0, max_tr = 0;           // over the clips (of the segment)
   for (const auto& c : pl->host)
     if (seg < 0 || c.list_class == seg) {
@@ -113,15 +109,26 @@ int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const 
   const int G = esim::kWave / L;
   a.max_groups = worklist ? (std::max<int64_t>(n_out, 1) + G - 1) / G : a.n_dense_groups;
   a.n_out = n_out;
+  a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * dense : nullptr;
+  a.nxcd = pl->shape.xcds;
+  a.single = max_r <= 7 && max_tr <= 1 ? 1 : 0;
+  return a;
+}
+
+int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count,
+                        int64_t n_out, float* alpha, float* beta, float* resid, float* kappa,
+                        bool update_state, hipStream_t stream, int seg = -1) {
+  // the condition estimate of the FP64 Gram comes from a one-lane instance
+  const bool kappa_f64 = kappa && pl->host[0].precision == ESIM_GRAM_F64;
+  const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : pl->lanes_dense;
+  if (!esim::regress_supports(pl->F, L, pl->host[0].precision))
+    return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
+  esim::RegressArgs a = regress_args(pl, t, worklist, count, n_out, L, kappa != nullptr, seg);
   a.alpha = alpha;
   a.beta = beta;
   a.resid = resid;
   a.kappa = kappa;
   a.update_state = update_state ? 1 : 0;
-  a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * dense
-                                                : nullptr;
-  a.nxcd = pl->shape.xcds;
-  a.single = max_r <= 7 && max_tr <= 1 ? 1 : 0;
   return hip_check(esim::launch_regress(a, pl->F, pl->f16, pl->host[0].precision, L, pl->blocks_per_cu,
                                         pl->shape, stream),
                    "regress");
@@ -719,20 +726,16 @@ int esim_wlr_regress_bandwidth(esim_plan pl, int32_t t, const int64_t* worklist,
       a.h[k] = hs[k];
       a.scale[k] = hc.h / hs[k];
     }
-    a.clip = pl->dev;
-    a.t = t;
-    a.items = worklist;
-    a.count = count;
-    a.n_out = n_out;
+    a.reg = regress_args(pl, t, worklist, count, worklist ? std::min(n_out, pl->wl_capacity) : n_out,
+                         worklist ? 16 : 1, false);
+    a.reg.n_out = n_out;
+    a.reg.alpha = alpha;
+    a.reg.beta = beta;
     a.vy = vy;
     a.K = K;
-    a.alpha = alpha;
-    a.beta = beta;
     a.hsel = hsel;
     a.sure = sure;
-    return hip_check(esim::launch_bandwidth(a, pl->F, pl->f16, worklist ? std::min(n_out, pl->wl_capacity)
-                                                                         : pl->npix,
-                                            hc.r, static_cast<hipStream_t>(stream)),
+    return hip_check(esim::launch_bandwidth(a, pl->F, pl->f16, pl->shape, static_cast<hipStream_t>(stream)),
                      "regress_bandwidth");
   } catch (...) {
     return fail(ESIM_E_HIP, "exception");

@@ -205,6 +205,8 @@ struct RegressArgs {
 // Regression launcher: picks the kernel instance for (F, dtype, precision)
 // and the lanes-per-item L; returns hipSuccess or the launch error.
 using KernelFn = void (*)(RegressArgs);
+struct BandwidthArgs;
+using BandwidthFn = void (*)(BandwidthArgs);
 
 // FP64 instances up to 8 features keep their sums within half the register file
 // and run two waves per SIMD (a wave's scalar and memory instructions then issue
@@ -218,11 +220,19 @@ struct RegressTable {
   KernelFn single[2] = {};     // 16 lanes per item, each with a single column of at most three frames
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item
+  BandwidthFn bandwidth[4][2] = {};   // dense tiles, dense from memory, lists (single column), lists
   KernelFn tile[2] = {};       // FP64 Gram, one lane per item, dense, windows in LDS
 };
 
 hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, int lanes,
                           int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
+const RegressTable* regress_table(int F);   // null outside 1..ESIM_MAX_F
+// Launches a kernel over the groups of a (args: its one argument, which holds
+// a): `queue` with one block per CU of 4 waves_per_simd waves that hand out their
+// share of the groups (GroupQueue), else blocks of four waves, at most
+// blocks_per_cu a CU, that stride over them.
+hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int waves_per_simd, bool queue,
+                         int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
 int regress_supported_lanes(int F);
 bool regress_supports(int F, int lanes, int precision);
 

@@ -22,7 +22,7 @@ void regress_table_12(RegressTable&);
 
 namespace {
 
-const RegressTable* table(int F) {
+const RegressTable* make_table(int F) {
   static RegressTable tabs[ESIM_MAX_F + 1];
   static std::once_flag once;
   std::call_once(once, [] {
@@ -35,14 +35,20 @@ const RegressTable* table(int F) {
   return (F >= 1 && F <= ESIM_MAX_F) ? &tabs[F] : nullptr;
 }
 
+}  // namespace
+
+const RegressTable* regress_table(int F) { return make_table(F); }
+
+namespace {
+
 KernelFn pick(int F, int lanes, bool f16) {
-  const RegressTable* t = table(F);
+  const RegressTable* t = regress_table(F);
   const int li = lanes == 1 ? 0 : lanes == 2 ? 1 : lanes == 4 ? 2 : lanes == 8 ? 3 : lanes == 16 ? 4 : -1;
   return (t && li >= 0) ? t->general[li][f16] : nullptr;
 }
 
 KernelFn pick_c32(int F, int lanes, bool f16) {
-  const RegressTable* t = table(F);
+  const RegressTable* t = regress_table(F);
   const int li = lanes == 4 ? 0 : lanes == 16 ? 1 : -1;
   return (t && li >= 0) ? t->c32[li][f16] : nullptr;
 }
@@ -60,7 +66,7 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
                           int blocks_per_cu, const DeviceShape& dev, hipStream_t s) {
   // the condition estimate (FP64 Gram) has an instance of its own, one lane
   // per item (the caller sizes the groups for one lane)
-  const RegressTable* tab = table(F);
+  const RegressTable* tab = regress_table(F);
   const bool c32 = precision == ESIM_GRAM_F32C;
   KernelFn fn = c32          ? pick_c32(F, lanes, f16)
                 : a.kappa    ? (tab ? tab->kappa[f16] : nullptr)
@@ -68,24 +74,31 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
                 : lanes == 16 && a.single ? (tab ? tab->single[f16] : nullptr)
                              : pick(F, lanes, f16);
   if (!fn) return hipErrorInvalidValue;
-  // Tiles and the instances of 4 lanes and more take one block per CU that fills
-  // it, and hand out their groups themselves (GroupQueue); the others stride over
-  // the groups with the resident blocks (more would only start when those end).
+  // Tiles and the instances of 4 lanes and more hand out their groups themselves;
+  // the others stride over them with the resident blocks (more would only start
+  // when those end).
   const int resident = regress_waves_per_simd(F, c32);
-  const bool queue = a.tile_units || (!c32 && !a.kappa && lanes >= 4);
-  const int waves = queue ? 4 * resident : kWavesPerBlock;
+  return launch_groups(reinterpret_cast<const void*>(fn), const_cast<RegressArgs*>(&a), a, resident,
+                       a.tile_units || (!c32 && !a.kappa && lanes >= 4), std::min(blocks_per_cu, resident), dev, s);
+}
+
+hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int waves_per_simd, bool queue,
+                         int blocks_per_cu, const DeviceShape& dev, hipStream_t s) {
+  const int waves = queue ? 4 * waves_per_simd : kWavesPerBlock;
   int64_t blocks = queue ? a.max_groups : (a.max_groups + waves - 1) / waves;
-  const int64_t cap = static_cast<int64_t>(dev.cus) * (queue ? 1 : std::min(blocks_per_cu, resident));
+  const int64_t cap = static_cast<int64_t>(dev.cus) * (queue ? 1 : blocks_per_cu);
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
-  blocks = (blocks + dev.xcds - 1) / dev.xcds * dev.xcds;   // a multiple of the XCDs (see GroupIter)
+  blocks = (blocks + dev.xcds - 1) / dev.xcds * dev.xcds;   // a multiple of the XCDs (see GroupIter, GroupQueue)
   const size_t lds = a.tile_units ? (static_cast<size_t>(a.tile_units) * waves + a.tile_last) * 16u : 0;
-  if (lds > 65536 && hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(lds)) != hipSuccess)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(static_cast<unsigned>(kWave * waves)),
-                     lds, s, a);
-  return hipGetLastError();
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (e != hipSuccess) return e;
+  }
+  void* argv[] = {args};
+  const hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)),
+                                       dim3(static_cast<unsigned>(kWave * waves)), argv, lds, s);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace esim

@@ -147,14 +147,14 @@ __device__ __forceinline__ void write_item(const RegressArgs& a, const ClipDev& 
 }
 
 // The items of one wave's group: calls fn(C, active, pix, t, got) with the
-// window sums `got` of the lane's part of its item (FP64 Gram; the columns j,
+// window sums `got` (weights to the power wscale) of the lane's part of its item (FP64 Gram; the columns j,
 // j + L, ... of the window; SINGLE: at most one column of at most three frames).
 // Rounds over the (clip, first
 // frame, frame count) present in the wave, so that those are uniform in the
 // walk: nearly always one round.
 template <int F, int L, bool F16, bool SINGLE, class Fn>
 __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, int my_cl, int64_t my_pix, int my_t,
-                                             int j, Fn&& fn) {
+                                             int j, Fn&& fn, double wscale = 1.0) {
   uint64_t todo = __ballot(valid);
   while (todo != 0) {
     const int src = __ffsll(static_cast<unsigned long long>(todo)) - 1;
@@ -175,7 +175,7 @@ __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, i
     const int f0 = a.t >= 0 ? max(0, a.t - tr) : 0;
     const int f1 = a.t >= 0 ? min(T, a.t + tr + 1) : T;
     WalkGeom<F, F16> geo;
-    make_walk(geo, C, pix, t, lo, hi - lo + 1, f0, f1, active);
+    make_walk(geo, C, pix, t, lo, hi - lo + 1, f0, f1, active, wscale);
     ColumnSums<F> c;
     Gram<F, double> got;
     if constexpr (SINGLE) {

@@ -1,5 +1,6 @@
-// Instantiates the regression kernels of one feature count (ESIM_REGRESS_F,
+// Instantiates the regression and bandwidth kernels of one feature count (ESIM_REGRESS_F,
 // set by the build) and fills its dispatch table.
+#include "esim_bandwidth_impl.h"
 #include "esim_regress_impl.h"
 
 #ifndef ESIM_REGRESS_F
@@ -27,6 +28,14 @@ void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   t.single[1] = regress_list_kernel<F, 16, true, true>;
   t.tile[0] = regress_tile_kernel<F, false>;
   t.tile[1] = regress_tile_kernel<F, true>;
+  t.bandwidth[0][0] = bandwidth_tile_kernel<F, false>;
+  t.bandwidth[0][1] = bandwidth_tile_kernel<F, true>;
+  t.bandwidth[1][0] = bandwidth_dense_kernel<F, false>;
+  t.bandwidth[1][1] = bandwidth_dense_kernel<F, true>;
+  t.bandwidth[2][0] = bandwidth_list_kernel<F, false, true>;
+  t.bandwidth[2][1] = bandwidth_list_kernel<F, true, true>;
+  t.bandwidth[3][0] = bandwidth_list_kernel<F, false, false>;
+  t.bandwidth[3][1] = bandwidth_list_kernel<F, true, false>;
   t.kappa[0] = regress_kernel<F, 1, false, false, true>;
   t.kappa[1] = regress_kernel<F, 1, true, false, true>;
   // the compensated-FP32 variant is compiled for the feature counts of the

@@ -403,14 +403,16 @@ struct WalkGeom {
   bool active;
   double sf[F], xcs[F];
   double vx_step, vy_step;
+  double kexp;                     // the exponent (base 2) of a weight is kexp |v|^2
 };
 
 // Fills the geometry of the item at (pix, tt) of clip C, whose window holds the
 // nt frames from tt + dt_lo on.  f0/f1 are the frames the buffer resources cover
-// (a uniform frame's window, or the whole clip).
+// (a uniform frame's window, or the whole clip).  wscale scales the weights'
+// exponent.
 template <int F, bool F16>
 __device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C, int64_t pix, int tt, int dt_lo,
-                                          int nt, int f0, int f1, bool active) {
+                                          int nt, int f0, int f1, bool active, double wscale = 1.0) {
   constexpr uint32_t ES = WalkGeom<F, F16>::ES;
   g.W = uni(C.W);
   g.H = uni(C.H);
@@ -436,6 +438,7 @@ __device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C,
   }
   g.vx_step = C.sf[0] / g.r;
   g.vy_step = C.sf[1] / g.r;
+  g.kexp = kHalfLog2e * wscale;
 }
 
 // Walks R consecutive frames, the first k0 frames after dt_lo, of the column dx
@@ -445,7 +448,7 @@ __device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C,
 template <int F, bool F16, int R, int DEPTH = 1>
 __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, ColumnSums<F>& c) {
   constexpr uint32_t ES = WalkGeom<F, F16>::ES;
-  constexpr double K = kHalfLog2e;
+  const double K = g.kexp;
   const int r = g.r;
   const int col = g.px + dx;
   const bool col_ok = g.active && dx <= r && static_cast<uint32_t>(col) < static_cast<uint32_t>(g.W);
@@ -565,10 +568,12 @@ struct TileGeom {
   int px, py;                      // this lane's pixel (may lie outside the image)
   double sf[F], xcs[F];
   double vx_step, vy_step;
+  double kexp;                     // the exponent (base 2) of a weight is kexp |v|^2
 };
 
 template <int F, bool F16>
-__device__ __forceinline__ void make_tile(TileGeom<F, F16>& g, const ClipDev& C, int tile, int tt) {
+__device__ __forceinline__ void make_tile(TileGeom<F, F16>& g, const ClipDev& C, int tile, int tt,
+                                          double wscale = 1.0) {
   constexpr uint32_t ES = TileGeom<F, F16>::ES;
   const int lane = threadIdx.x & (kWave - 1);
   g.W = uni(C.W);
@@ -598,6 +603,7 @@ __device__ __forceinline__ void make_tile(TileGeom<F, F16>& g, const ClipDev& C,
   }
   g.vx_step = C.sf[0] / g.r;
   g.vy_step = C.sf[1] / g.r;
+  g.kexp = kHalfLog2e * wscale;
 }
 
 // Orders a wave's LDS accesses before and after it (between lanes of the wave:
@@ -659,7 +665,7 @@ __device__ __forceinline__ void stage_row(const TileGeom<F, F16>& g, float4* lds
 template <int F, bool F16, int R>
 __device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* lds, int k0, ColumnSums<F>& c,
                                             LaneSums<F>& ls) {
-  constexpr double K = kHalfLog2e;
+  const double K = g.kexp;
   constexpr int NQ = tile_quads(F), U = tile_units(F, R);
   // A wave alone on its SIMD loads the next row while it walks this one; where
   // two share it, the other one walks meanwhile and the registers are short.
