@@ -761,7 +761,8 @@ int esim_wlr_backward(esim_plan pl, const int64_t* items, int64_t n, const float
       return fail(ESIM_E_UNSUPPORTED, "backward supports window radii up to 25");
     const size_t need = esim::backward_scratch_bytes(pl->host[0], n);
     if (!scratch || scratch_bytes < need) return fail(ESIM_E_CAPACITY, "scratch too small");
-    esim::BackwardArgs a{pl->dev, &pl->host[0], items, n, g_alpha, g_y, g_b, scratch, scratch_bytes, pl->shape};
+    esim::BackwardArgs a{pl->dev, &pl->host[0], regress_args(pl, -1, items, nullptr, n, 16, false), n, g_alpha, g_y, g_b,
+                         scratch, scratch_bytes, pl->shape};
     return hip_check(esim::launch_backward(a, static_cast<hipStream_t>(stream)), "backward");
   } catch (...) {
     return fail(ESIM_E_HIP, "exception");

@@ -10,9 +10,9 @@
 //
 // Kernels, all deterministic (no atomics on values):
 //   fill_map / map_items  a dense (frame, pixel) -> item index map
-//   adjoint_kernel        per item: the window's Gram, Cholesky, theta and v
-//                         (the window is recomputed, not stored by the forward
-//                         pass); writes the item's record c = g_alpha v / W,
+//   adjoint_kernel        (esim_backward_impl.h) per item: the window's Gram,
+//                         Cholesky, theta and v (the window is recomputed, not
+//                         stored by the forward pass); writes the item's record c = g_alpha v / W,
 //                         theta, q = g_alpha v^T Lambda theta / W
 //   gather_kernel         per input sample (frame, pixel): for every item whose
 //                         window holds it, in a fixed order, recomputes the
@@ -23,30 +23,19 @@
 //                         items staged in LDS one at a time, every lane reading
 //                         the same record (a broadcast); per-block partials
 //   reduce_gb_*           fixed-order two-level sum of the per-block partials
+#include "esim_backward.h"
 #include "esim_wlr.h"
 
 namespace esim {
 namespace {
 
-constexpr int kAdjLanes = 4;        // lanes per item, windows wider than 16 columns
-constexpr int kAdjLanesWide = 16;   // lanes per item, windows of at most 16 columns
 constexpr int kRedBlocks = 256;
-constexpr int kAdjRing = 3;      // rows of window loads in flight in the interior loop
 constexpr int kGatherTile = 16;     // input pixels of a gather block: 16 x 16, four waves of 8 x 8
 constexpr int kGatherThreads = 256;
 constexpr int kGatherWaves = kGatherThreads / kWave;
 constexpr size_t kGatherLdsBudget = 40960;    // four blocks per CU
 constexpr int kGatherSlots = 4;              // region slots per thread and step of the gather's scan
 constexpr size_t kGatherCountBytes = sizeof(int32_t) * 2 * kGatherSlots * kGatherWaves;
-
-struct BwdDev {
-  int32_t* item_map;   // [T*HW]
-  double* rec;         // [n][2P + 1] per-item records (c, theta, q)
-  double* gbpart;      // [npart][D] per-gather-block bandwidth partials
-  double* gbblk;       // [kRedBlocks][D]
-  int64_t n;
-  int64_t npart;
-};
 
 __global__ void __launch_bounds__(256) fill_map_kernel(int32_t* m, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -70,89 +59,6 @@ map_items_kernel(const ClipDev* __restrict__ clips, const int64_t* __restrict__ 
     int64_t pix;
     int t;
     if (item_ok(C, items[i], g_alpha, i, pix, t)) item_map[static_cast<int64_t>(t) * C.HW + pix] = static_cast<int32_t>(i);
-  }
-}
-
-template <int F, int L, bool F16, bool ONE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F <= 8 ? 2 : 1)))
-adjoint_kernel(const ClipDev* __restrict__ clips, const int64_t* __restrict__ items,
-               const float* __restrict__ g_alpha, BwdDev bd, int nxcd) {
-  constexpr int P = F + 3;
-  constexpr int R = 2 * P + 1;
-  constexpr int G = kWave / L;
-  const ClipDev& C = clips[0];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int slot = lane / L;
-  const int j = lane % L;
-  const int64_t ngroups = (bd.n + G - 1) / G;
-  GroupIter it_groups(ngroups, nxcd);
-  int64_t g;
-  while (it_groups.next(g)) {
-    const int64_t i = g * G + slot;
-    int64_t pix = 0;
-    int t = 0;
-    const bool active = i < bd.n && item_ok(C, items[i], g_alpha, i, pix, t);
-    const uint64_t act = __ballot(active);
-    if (act == 0) continue;
-    // Interior waves (every item's window inside the image and the clip) of
-    // the one-column-per-lane instance run the window loop without per-row
-    // validity tests; lanes without an item then take the first item's
-    // geometry with weight 0.
-    const int prow = static_cast<int>(pix / C.W), pcol = static_cast<int>(pix - static_cast<int64_t>(prow) * C.W);
-    const bool inside = prow >= C.r && prow + C.r < C.H && pcol >= C.r && pcol + C.r < C.W &&
-                        t - C.tr >= 0 && t + C.tr < C.T;
-    const bool full = ONE && __ballot(active && !inside) == 0;
-    int64_t gpix = active ? pix : 0;
-    int gt = active ? t : 0;
-    if (full) {
-      const int src = __ffsll(static_cast<unsigned long long>(act)) - 1;
-      const int64_t p0 = __shfl(pix, src);
-      const int t0 = __shfl(t, src);
-      if (!active) {
-        gpix = p0;
-        gt = t0;
-      }
-    }
-    ItemGeom<F, F16, double> geo;
-    make_geom(geo, C, gpix, gt, 0, C.T, active);
-
-    Gram<F, double> gm;
-    auto add = [&](double w, double yd, const double (&v)[F], double vy, int, int, int, bool) {
-      gm.add_onepass(w, yd, v, vy);
-    };
-    if constexpr (ONE) {
-      // every lane owns one column of the window (2r + 1 <= L, checked by the launcher)
-      gm.zero_onepass();
-      if (full)
-        window_loop_ring<F, L, F16, kAdjRing>(geo, j, [&](double) {}, add,
-                                              [&](double vx) { gm.fold_onepass(vx); });
-      else
-        window_loop<F, L, F16, double>(geo, j, [&](double) {}, add, [&](double vx) { gm.fold_onepass(vx); });
-    } else {
-      gm.zero_snap();
-      window_loop<F, L, F16, double>(geo, j, [&](double) { gm.pass_begin_snap(); }, add,
-                                     [&](double vx) { gm.pass_end_snap(vx); });
-    }
-    gm.template lane_sum<L>();
-    double M[P * (P + 1) / 2], rhs[P], th[P], anorm;
-    const double iW = gram_solve<F, double>(gm, C, M, rhs, th, anorm);
-    double e0[P], vv[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) e0[k] = k == 0 ? 1.0 : 0.0;
-    chol_solve<P, double>(M, e0, vv);
-    double vLt = 0.0;      // v^T Lambda theta (Lambda = scaled ridge on the beta block)
-#pragma unroll
-    for (int k = 1; k < P; ++k) vLt = fma(vv[k] * (C.ridge * C.c2[k - 1]), th[k], vLt);
-    if (active && j == 0) {
-      const double gw = static_cast<double>(g_alpha[i]) * iW;
-      double* o = bd.rec + i * R;
-#pragma unroll
-      for (int k = 0; k < P; ++k) {
-        o[k] = gw * vv[k];
-        o[P + k] = th[k];
-      }
-      o[2 * P] = gw * vLt;
-    }
   }
 }
 
@@ -420,33 +326,7 @@ __global__ void reduce_gb_final(BwdDev bd, int nblk, int D, double* g_b) {
   g_b[d] += s;
 }
 
-using AdjFn = void (*)(const ClipDev*, const int64_t*, const float*, BwdDev, int);
 using GatherFn = void (*)(const ClipDev*, BwdDev, float*, int);
-
-template <int F>
-AdjFn pick_adj(bool f16, bool wide) {
-  if (wide)
-    return f16 ? adjoint_kernel<F, kAdjLanesWide, true, true> : adjoint_kernel<F, kAdjLanesWide, false, true>;
-  return f16 ? adjoint_kernel<F, kAdjLanes, true, false> : adjoint_kernel<F, kAdjLanes, false, false>;
-}
-
-AdjFn pick(int F, bool f16, bool wide) {
-  switch (F) {
-    case 1: return pick_adj<1>(f16, wide);
-    case 2: return pick_adj<2>(f16, wide);
-    case 3: return pick_adj<3>(f16, wide);
-    case 4: return pick_adj<4>(f16, wide);
-    case 5: return pick_adj<5>(f16, wide);
-    case 6: return pick_adj<6>(f16, wide);
-    case 7: return pick_adj<7>(f16, wide);
-    case 8: return pick_adj<8>(f16, wide);
-    case 9: return pick_adj<9>(f16, wide);
-    case 10: return pick_adj<10>(f16, wide);
-    case 11: return pick_adj<11>(f16, wide);
-    case 12: return pick_adj<12>(f16, wide);
-    default: return nullptr;
-  }
-}
 
 GatherFn pick_gather(int F) {
   switch (F) {
@@ -532,12 +412,16 @@ size_t backward_gather_lds_bytes(const ClipDev& hc) {
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   const ClipDev& hc = *a.host_clip;
   const int F = hc.F, D = F + 2;
-  // 16 lanes per item (one column each) when the window has at most 16 columns
-  const bool wide = 2 * hc.r + 1 <= kAdjLanesWide;
-  AdjFn adj = pick(F, hc.feat_f16 != 0, wide);
+  const RegressTable* t = regress_table(F);
+  // 16 lanes per item (one column each) when the window is a single walk; wider
+  // ones leave fewer lanes idle with 4
+  AdjointArgs adj{};
+  adj.reg = a.reg;
+  const int L = adj.reg.single ? 16 : 4;
+  const AdjointFn fn = t ? t->adjoint[adj.reg.single ? 0 : 1][hc.feat_f16 != 0] : nullptr;
   GatherFn gat = pick_gather(F);
   RedFn rb = pick_red(D);
-  if (!adj || !gat || !rb) return hipErrorInvalidValue;
+  if (!fn || !gat || !rb) return hipErrorInvalidValue;
   const Layout l = layout(hc, a.n);
   char* m = static_cast<char*>(a.scratch);
   const int64_t gblocks = gather_blocks(hc);
@@ -545,16 +429,14 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
             reinterpret_cast<double*>(m + l.gbpart), reinterpret_cast<double*>(m + l.gbblk), a.n, gblocks};
   const int64_t map_n = static_cast<int64_t>(hc.T) * hc.HW;
   hipLaunchKernelGGL(fill_map_kernel, dim3(grid_for(map_n, 4096)), dim3(256), 0, s, bd.item_map, map_n);
-  hipLaunchKernelGGL(map_items_kernel, dim3(grid_for(a.n, 4096)), dim3(256), 0, s, a.clip, a.items, a.n,
+  hipLaunchKernelGGL(map_items_kernel, dim3(grid_for(a.n, 4096)), dim3(256), 0, s, a.clip, a.reg.items, a.n,
                      a.g_alpha, bd.item_map);
-  const int L = wide ? kAdjLanesWide : kAdjLanes;
-  const int G = kWave / L;
-  int64_t blocks = ((a.n + G - 1) / G + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int64_t cap = static_cast<int64_t>(a.dev.cus) * 8;
-  if (blocks > cap) blocks = cap;
-  blocks = (blocks + a.dev.xcds - 1) / a.dev.xcds * a.dev.xcds;   // a multiple of the XCDs (see GroupIter)
-  hipLaunchKernelGGL(adj, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, s, a.clip, a.items, a.g_alpha, bd,
-                     a.dev.xcds);
+  adj.g_alpha = a.g_alpha;
+  adj.bd = bd;
+  adj.reg.max_groups = (a.n + kWave / L - 1) / (kWave / L);
+  const int waves = regress_waves_per_simd(F, false);
+  const hipError_t e = launch_groups(reinterpret_cast<const void*>(fn), &adj, adj.reg, waves, true, waves, a.dev, s);
+  if (e != hipSuccess) return e;
   const size_t lds = std::max(backward_gather_lds_bytes(hc), sizeof(double) * kGatherWaves * D);
   hipLaunchKernelGGL(gat, dim3(static_cast<unsigned>(gblocks)), dim3(kGatherThreads), lds, s, a.clip, bd, a.g_y,
                      gather_capacity(F));

@@ -205,6 +205,8 @@ struct RegressArgs {
 // Regression launcher: picks the kernel instance for (F, dtype, precision)
 // and the lanes-per-item L; returns hipSuccess or the launch error.
 using KernelFn = void (*)(RegressArgs);
+struct AdjointArgs;
+using AdjointFn = void (*)(AdjointArgs);
 struct BandwidthArgs;
 using BandwidthFn = void (*)(BandwidthArgs);
 
@@ -221,6 +223,7 @@ struct RegressTable {
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item
   BandwidthFn bandwidth[4][2] = {};   // dense tiles, dense from memory, lists (single column), lists
+  AdjointFn adjoint[2][2] = {};       // 16 lanes per item (single column), 4 lanes
   KernelFn tile[2] = {};       // FP64 Gram, one lane per item, dense, windows in LDS
 };
 
@@ -239,7 +242,7 @@ bool regress_supports(int F, int lanes, int precision);
 struct BackwardArgs {
   const ClipDev* clip;      // single clip (device)
   const ClipDev* host_clip; // the same, host copy
-  const int64_t* items;
+  RegressArgs reg;          // the items' regressions
   int64_t n;
   const float* g_alpha;
   float* g_y;

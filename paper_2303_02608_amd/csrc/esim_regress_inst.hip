@@ -1,5 +1,6 @@
-// Instantiates the regression and bandwidth kernels of one feature count (ESIM_REGRESS_F,
+// Instantiates the regression, bandwidth and adjoint kernels of one feature count (ESIM_REGRESS_F,
 // set by the build) and fills its dispatch table.
+#include "esim_backward_impl.h"
 #include "esim_bandwidth_impl.h"
 #include "esim_regress_impl.h"
 
@@ -36,6 +37,10 @@ void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   t.bandwidth[2][1] = bandwidth_list_kernel<F, true, true>;
   t.bandwidth[3][0] = bandwidth_list_kernel<F, false, false>;
   t.bandwidth[3][1] = bandwidth_list_kernel<F, true, false>;
+  t.adjoint[0][0] = adjoint_kernel<F, 16, false, true>;
+  t.adjoint[0][1] = adjoint_kernel<F, 16, true, true>;
+  t.adjoint[1][0] = adjoint_kernel<F, 4, false, false>;
+  t.adjoint[1][1] = adjoint_kernel<F, 4, true, false>;
   t.kappa[0] = regress_kernel<F, 1, false, false, true>;
   t.kappa[1] = regress_kernel<F, 1, true, false, true>;
   // the compensated-FP32 variant is compiled for the feature counts of the
