@@ -5,9 +5,13 @@
 
 namespace esim {
 
+// Doubles of an item's record: c = g_alpha v / W and theta (F + 3 each),
+// q = g_alpha v^T Lambda theta / W, and the scaled centre features.
+constexpr int adjoint_record(int F) { return 2 * (F + 3) + 1 + F; }
+
 struct BwdDev {
   int32_t* item_map;   // [T*HW]
-  double* rec;         // [n][2P + 1] per-item records (c, theta, q)
+  double* rec;         // [n][adjoint_record] per-item records
   double* gbpart;      // [npart][D] per-gather-block bandwidth partials
   double* gbblk;       // [kRedBlocks][D]
   int64_t n;

@@ -17,11 +17,10 @@
 //   gather_kernel         per input sample (frame, pixel): for every item whose
 //                         window holds it, in a fixed order, recomputes the
 //                         sample's weight and regressors from the item's
-//                         centre features and record, adds w_i c^T z_i to g_y
-//                         and accumulates w_i (c^T z_i r_i - q) z_ij^2 for the
-//                         bandwidths.  A wave owns 8 x 8 samples and walks the
-//                         items staged in LDS one at a time, every lane reading
-//                         the same record (a broadcast); per-block partials
+//                         record, adds w_i c^T z_i to g_y and accumulates
+//                         w_i (c^T z_i r_i - q) z_ij^2 for the bandwidths.  A wave
+//                         owns 8 x 8 samples and visits the items one at a time,
+//                         the record in scalar registers; per-block partials
 //   reduce_gb_*           fixed-order two-level sum of the per-block partials
 #include "esim_backward.h"
 #include "esim_wlr.h"
@@ -33,9 +32,8 @@ constexpr int kRedBlocks = 256;
 constexpr int kGatherTile = 16;     // input pixels of a gather block: 16 x 16, four waves of 8 x 8
 constexpr int kGatherThreads = 256;
 constexpr int kGatherWaves = kGatherThreads / kWave;
-constexpr size_t kGatherLdsBudget = 40960;    // four blocks per CU
 constexpr int kGatherSlots = 4;              // region slots per thread and step of the gather's scan
-constexpr size_t kGatherCountBytes = sizeof(int32_t) * 2 * kGatherSlots * kGatherWaves;
+constexpr int kGatherCap = kGatherSlots * kGatherThreads;   // listed items: a step's at least
 
 __global__ void __launch_bounds__(256) fill_map_kernel(int32_t* m, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -62,46 +60,38 @@ map_items_kernel(const ClipDev* __restrict__ clips, const int64_t* __restrict__ 
   }
 }
 
-// LDS bytes of one staged item of the gather: its record, its centre features
-// (scaled) and its packed position in the block's item region.
-size_t gather_item_bytes(int F) {
-  const int P = F + 3;
-  return sizeof(double) * (2 * P + 1) + sizeof(double) * F + sizeof(int32_t);
-}
-
-// Items staged at a time (the LDS budget, less the per-wave counts).
-int gather_capacity(int F) {
-  return static_cast<int>((kGatherLdsBudget - kGatherCountBytes) / gather_item_bytes(F));
-}
-
 // One block per (input frame tq, 16 x 16 tile of input pixels); wave w owns the
 // 8 x 8 sub-tile (w & 1, w >> 1), lane l the sample (l & 7, l >> 3) in it.
 // The block's item region is the (frame, row, column) slots whose window can
 // reach the tile: rows yc, frames tc and columns x within r (tr) of it, taken
 // in a fixed order (tc ascending, then yc, then x), 1024 slots per step, four
 // per thread.  A step's present items (the frame-pixel map holds their index) are
-// compacted in that order into an LDS buffer of cap items (records, centre
-// features, positions): a wave ballot and prefix per set of 256 slots, and the
-// waves' counts exchanged through LDS.  When the next item would not fit, every wave walks
-// the buffer in order, skipping the items out of reach of all of its lanes
-// (64 positions tested per ballot), and each lane whose window holds the item
-// adds its sample's terms.  The order of every sum is fixed, so g_y and the
-// partials do not depend on scheduling.
+// listed in that order in LDS (index and position): a wave ballot and prefix per
+// set of 256 slots, and the waves' counts exchanged through LDS.  When the list
+// would overflow, every wave walks it in order, skipping the items out of reach
+// of all of its lanes (64 positions tested per ballot), and each lane whose window
+// holds the item adds its sample's terms.  The order of every sum is fixed, so g_y
+// and the partials do not depend on scheduling.
+//
+// The item of a visit is the same for the whole wave, so its record comes through
+// scalar loads into SGPRs, one operand of each FMA.  (Staged in LDS, a visit read
+// 28 doubles with every lane at one address: 512 bytes a read, 450 cycles of the
+// CU's LDS for the four SIMDs against about 55 VALU instructions each.)
 template <int F>
 __global__ void __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(F <= 8 ? 4 : 1)))
-gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ g_y, int cap) {
+gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ g_y) {
   constexpr int D = F + 2;
   constexpr int P = F + 3;
-  constexpr int R = 2 * P + 1;
+  constexpr int R = adjoint_record(F);
   constexpr double K = kHalfLog2e;
-  extern __shared__ double sm[];
+  constexpr int cap = kGatherCap;
+  using ScalarDouble = const __attribute__((address_space(4))) double;
+  __shared__ int2 list[kGatherCap];                             // item, (row << 8) | column
+  __shared__ int32_t wcnt[2 * kGatherSlots * kGatherWaves];     // present items per wave and step
+  __shared__ double part[kGatherWaves * D];
   const ClipDev& C = clips[0];
   const int r = C.r, tr = C.tr, W = C.W, H = C.H, T = C.T;
   const int ncol = kGatherTile + 2 * r;                        // at most 66 (r <= 25)
-  double* srec = sm;                                            // [cap][R]
-  double* sxcs = srec + static_cast<size_t>(cap) * R;           // [cap][F]
-  int32_t* spos = reinterpret_cast<int32_t*>(sxcs + static_cast<size_t>(cap) * F);  // [cap] (row << 8) | column
-  int32_t* wcnt = spos + cap;                                   // [2][slots][waves] present items per wave and step
   const int ntx = (W + kGatherTile - 1) / kGatherTile;
   const int nty = (H + kGatherTile - 1) / kGatherTile;
   int64_t b = blockIdx.x;
@@ -151,7 +141,8 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
   auto walk = [&](int n) {
     for (int i0 = 0; i0 < n; i0 += kWave) {
       const int ii = i0 + lane;
-      const int pp = ii < n ? spos[ii] : 0;
+      const int2 entry = ii < n ? list[ii] : make_int2(0, 0);
+      const int pp = entry.y;
       const int prow = pp >> 8, pcol = pp & 255;
       const int yc = yc0 + prow;
       // items out of reach of every lane of the wave are skipped (ballot)
@@ -160,12 +151,12 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
         const int bi = __ffsll(static_cast<unsigned long long>(m)) - 1;
         m &= m - 1;
         const int pu = __builtin_amdgcn_readlane(pp, bi);
+        ScalarDouble* rc = reinterpret_cast<ScalarDouble*>(reinterpret_cast<uintptr_t>(bd.rec)) +
+                           static_cast<int64_t>(__builtin_amdgcn_readlane(entry.x, bi)) * R;
+        ScalarDouble* xc = rc + 2 * P + 1;
         const int dy = yq - (yc0 + (pu >> 8));
         const int dx = xq - (xs + (pu & 255));
         if (!in || dy < -r || dy > r || dx < -r || dx > r) continue;
-        const int q = i0 + bi;
-        const double* rc = srec + static_cast<size_t>(q) * R;
-        const double* xc = sxcs + static_cast<size_t>(q) * F;
         // the sample's regressors and weight as the item's window pass forms them
         const double vy = static_cast<double>(dy) * vy_step;
         const double kyy = K * vy;
@@ -251,18 +242,9 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
 #pragma unroll
       for (int u = 0; u < kGatherSlots; ++u) {
         if (it[u] >= 0 && mine[u] >= base && mine[u] < base + cap) {
-          const int e = mine[u] - base;
           const int su = s + u * kGatherThreads;
-          const int k = su / ncol, c = su - k * ncol;
-          const int yc = yc0 + k % nry, tc = t0 + k / nry;
-          const double* src = bd.rec + static_cast<int64_t>(it[u]) * R;
-#pragma unroll
-          for (int j = 0; j < R; ++j) srec[static_cast<size_t>(e) * R + j] = src[j];
-          const int64_t p = static_cast<int64_t>(yc) * W + xs + c;
-#pragma unroll
-          for (int f = 0; f < F; ++f)
-            sxcs[static_cast<size_t>(e) * F + f] = static_cast<double>(feat_value(C, tc, f, p)) * sf[f];
-          spos[e] = ((yc - yc0) << 8) | c;
+          const int k = su / ncol;
+          list[mine[u] - base] = make_int2(it[u], ((k % nry) << 8) | (su - k * ncol));
         }
       }
       resume = seq > base + cap;
@@ -284,14 +266,13 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
   for (int d = 0; d < D; ++d)
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) gb[d] += __shfl_xor(gb[d], o);
-  __syncthreads();                             // the last walk's reads are done
   if (lane == 0)
 #pragma unroll
-    for (int d = 0; d < D; ++d) sm[wv * D + d] = gb[d];
+    for (int d = 0; d < D; ++d) part[wv * D + d] = gb[d];
   __syncthreads();
   if (threadIdx.x < D) {
     double s = 0.0;
-    for (int w2 = 0; w2 < kGatherWaves; ++w2) s += sm[w2 * D + threadIdx.x];
+    for (int w2 = 0; w2 < kGatherWaves; ++w2) s += part[w2 * D + threadIdx.x];
     bd.gbpart[static_cast<int64_t>(blockIdx.x) * D + threadIdx.x] = s * C.sf[threadIdx.x] * C.h;
   }
 }
@@ -318,15 +299,18 @@ __global__ void __launch_bounds__(256) reduce_gb_blocks(BwdDev bd) {
   if (threadIdx.x < D) bd.gbblk[blockIdx.x * D + threadIdx.x] = sh[0][threadIdx.x];
 }
 
-__global__ void reduce_gb_final(BwdDev bd, int nblk, int D, double* g_b) {
-  const int d = threadIdx.x;
-  if (d >= D) return;
+// One wave per bandwidth: lane l sums every 64th partial from the l-th on, then a
+// fixed butterfly.
+__global__ void __launch_bounds__(kWave* ESIM_MAX_D) reduce_gb_final(BwdDev bd, int nblk, int D, double* g_b) {
+  const int d = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += bd.gbblk[b * D + d];
-  g_b[d] += s;
+  for (int b = lane; b < nblk; b += kWave) s += bd.gbblk[b * D + d];
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) g_b[d] += s;
 }
 
-using GatherFn = void (*)(const ClipDev*, BwdDev, float*, int);
+using GatherFn = void (*)(const ClipDev*, BwdDev, float*);
 
 GatherFn pick_gather(int F) {
   switch (F) {
@@ -380,12 +364,12 @@ struct Layout {
 
 Layout layout(const ClipDev& hc, int64_t n) {
   Layout l{};
-  const int D = hc.F + 2, P = hc.F + 3;
+  const int D = hc.F + 2;
   size_t off = 0;
   l.map = off;
   off = align256(off + sizeof(int32_t) * static_cast<size_t>(hc.T) * hc.HW);
   l.rec = off;
-  off = align256(off + sizeof(double) * (2 * P + 1) * static_cast<size_t>(n));
+  off = align256(off + sizeof(double) * adjoint_record(hc.F) * static_cast<size_t>(n));
   l.gbpart = off;
   off = align256(off + sizeof(double) * D * static_cast<size_t>(gather_blocks(hc)));
   l.gbblk = off;
@@ -404,10 +388,6 @@ unsigned grid_for(int64_t n, int64_t cap) {
 }  // namespace
 
 size_t backward_scratch_bytes(const ClipDev& hc, int64_t n) { return layout(hc, n).total; }
-
-size_t backward_gather_lds_bytes(const ClipDev& hc) {
-  return gather_item_bytes(hc.F) * gather_capacity(hc.F) + kGatherCountBytes;
-}
 
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   const ClipDev& hc = *a.host_clip;
@@ -437,11 +417,9 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   const int waves = regress_waves_per_simd(F, false);
   const hipError_t e = launch_groups(reinterpret_cast<const void*>(fn), &adj, adj.reg, waves, true, waves, a.dev, s);
   if (e != hipSuccess) return e;
-  const size_t lds = std::max(backward_gather_lds_bytes(hc), sizeof(double) * kGatherWaves * D);
-  hipLaunchKernelGGL(gat, dim3(static_cast<unsigned>(gblocks)), dim3(kGatherThreads), lds, s, a.clip, bd, a.g_y,
-                     gather_capacity(F));
+  hipLaunchKernelGGL(gat, dim3(static_cast<unsigned>(gblocks)), dim3(kGatherThreads), 0, s, a.clip, bd, a.g_y);
   hipLaunchKernelGGL(rb, dim3(kRedBlocks), dim3(256), 0, s, bd);
-  hipLaunchKernelGGL(reduce_gb_final, dim3(1), dim3(64), 0, s, bd, kRedBlocks, D, a.g_b);
+  hipLaunchKernelGGL(reduce_gb_final, dim3(1), dim3(kWave * D), 0, s, bd, kRedBlocks, D, a.g_b);
   return hipGetLastError();
 }
 

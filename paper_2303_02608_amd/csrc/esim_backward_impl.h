@@ -1,8 +1,7 @@
 // Item kernel of the adjoint (esim_backward.hip), instantiated per feature count
 // beside the regression kernels: the list regression's window sums (groups from
 // the block's queue, totals parked in LDS, one lane per item factors and solves),
-// then theta, v = A^-1 e_0 and the item's record c = g_alpha v / W, theta,
-// q = g_alpha v^T Lambda theta / W.  Bound like the list regression by VALU issue
+// then theta, v = A^-1 e_0 and the item's record.  Bound like the list regression by VALU issue
 // and the window loads.
 #pragma once
 
@@ -17,7 +16,7 @@ __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
 __attribute__((amdgpu_waves_per_eu(regress_waves_per_simd(F, false))))
 adjoint_kernel(AdjointArgs b) {
   constexpr int P = F + 3;
-  constexpr int REC = 2 * P + 1;
+  constexpr int REC = adjoint_record(F);
   constexpr int G = kWave / L;
   using R = ListRound<F, L>;
   __shared__ double parked[R::ITEMS * R::STRIDE];
@@ -77,6 +76,9 @@ adjoint_kernel(AdjointArgs b) {
             o[P + u] = th[u];
           }
           o[2 * P] = gw * vLt;
+#pragma unroll
+          for (int f = 0; f < F; ++f)
+            o[2 * P + 1 + f] = static_cast<double>(feat_value(C, t, f, pix)) * C.sf[2 + f];
         }
       }
     }

@@ -252,10 +252,6 @@ struct BackwardArgs {
   DeviceShape dev;
 };
 size_t backward_scratch_bytes(const ClipDev& hc, int64_t n);
-// LDS of the gather kernel's item buffer (records, centre features and
-// positions of the items staged at a time, and the per-wave counts).
-size_t backward_gather_lds_bytes(const ClipDev& hc);
-constexpr size_t kMaxGatherLds = 65536;
 hipError_t launch_backward(const BackwardArgs& a, hipStream_t s);
 
 // Nearest same-polarity neighbour distances (event-set comparison).
