@@ -78,7 +78,7 @@ map_items_kernel(const ClipDev* __restrict__ clips, const int64_t* __restrict__ 
 // 28 doubles with every lane at one address: 512 bytes a read, 450 cycles of the
 // CU's LDS for the four SIMDs against about 55 VALU instructions each.)
 template <int F>
-__global__ void __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(F <= 8 ? 4 : 1)))
+__global__ void __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(F <= 7 ? 5 : 4)))
 gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ g_y) {
   constexpr int D = F + 2;
   constexpr int P = F + 3;
@@ -109,13 +109,10 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
   // region columns whose items reach the wave's columns: wc0 .. wc0 + 7 + 2r
   const int wc0 = wx0 - r - xs;
   const int64_t pq = in ? static_cast<int64_t>(yq) * W + xq : 0;
-  double fi[F];
+  double fi[F];                                // scaled features
 #pragma unroll
-  for (int f = 0; f < F; ++f) fi[f] = in ? static_cast<double>(feat_value(C, tq, f, pq)) : 0.0;
+  for (int f = 0; f < F; ++f) fi[f] = in ? static_cast<double>(feat_value(C, tq, f, pq)) * C.sf[2 + f] : 0.0;
   const double yi = in ? static_cast<double>(C.y[static_cast<int64_t>(tq) * C.HW + pq]) : 0.0;
-  double sf[F];
-#pragma unroll
-  for (int f = 0; f < F; ++f) sf[f] = C.sf[2 + f];
   const double vx_step = C.sf[0] / r, vy_step = C.sf[1] / r;
   double acc = 0.0;
   double gb[D];
@@ -151,13 +148,16 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
         const int bi = __ffsll(static_cast<unsigned long long>(m)) - 1;
         m &= m - 1;
         const int pu = __builtin_amdgcn_readlane(pp, bi);
-        ScalarDouble* rc = reinterpret_cast<ScalarDouble*>(reinterpret_cast<uintptr_t>(bd.rec)) +
-                           static_cast<int64_t>(__builtin_amdgcn_readlane(entry.x, bi)) * R;
-        ScalarDouble* xc = rc + 2 * P + 1;
+        ScalarDouble* src = reinterpret_cast<ScalarDouble*>(reinterpret_cast<uintptr_t>(bd.rec)) +
+                            static_cast<int64_t>(__builtin_amdgcn_readlane(entry.x, bi)) * R;
+        double rc[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) rc[u] = src[u];
         const int dy = yq - (yc0 + (pu >> 8));
         const int dx = xq - (xs + (pu & 255));
         if (!in || dy < -r || dy > r || dx < -r || dx > r) continue;
-        // the sample's regressors and weight as the item's window pass forms them
+        // the sample's regressors and weight (as the item's window pass forms
+        // them, up to the rounding of the scaled features)
         const double vy = static_cast<double>(dy) * vy_step;
         const double kyy = K * vy;
         const double vx = static_cast<double>(dx) * vx_step;
@@ -165,21 +165,22 @@ gather_kernel(const ClipDev* __restrict__ clips, BwdDev bd, float* __restrict__ 
         double s0 = 0.0, s1 = 0.0;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
-          v[f] = fma(fi[f], sf[f], -xc[f]);
+          v[f] = fi[f] - rc[2 * P + 1 + f];
           if (f & 1) s1 = fma(v[f], v[f], s1);
           else s0 = fma(v[f], v[f], s0);
         }
         const double arg = fma(s0 + s1, K, fma(kyy, vy, K * vx * vx));
         const double w = static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(arg)));
-        double cs = fma(rc[1], vx, fma(rc[2], vy, rc[0]));
-        double pred = fma(rc[P + 1], vx, fma(rc[P + 2], vy, rc[P]));
+        // (each operation takes one scalar operand)
+        double cs = fma(rc[1], vx, rc[2] * vy) + rc[0];
+        double pred = fma(rc[P + 1], vx, rc[P + 2] * vy) + rc[P];
 #pragma unroll
         for (int f = 0; f < F; ++f) {
           cs = fma(rc[3 + f], v[f], cs);
           pred = fma(rc[P + 3 + f], v[f], pred);
         }
         acc = fma(w, cs, acc);
-        const double kq = w * fma(cs, yi - pred, -rc[2 * P]);
+        const double kq = w * (cs * (yi - pred) - rc[2 * P]);
         gb[0] = fma(kq, vx * vx, gb[0]);
         gb[1] = fma(kq, vy * vy, gb[1]);
 #pragma unroll
