@@ -27,6 +27,7 @@ struct esim_plan_s {
   int tile_last = 0;       // see RegressArgs
   int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles (0: a clip's windows do not fit)
   int lanes_dense = 1;     // lanes per regression item, dense launches
+  bool auto_dense = true;  // no schedule was set: small frames take more lanes (dense_lanes)
   int lanes_list = 16;     // lanes per regression item, work-list launches
   int blocks_per_cu = 4;   // persistent grid: 256 CUs x this many blocks
   uint64_t max_feat_bytes = 0;   // largest feature array of a clip
@@ -85,6 +86,16 @@ bool query_device_shape(DeviceShape& out) {
 
 namespace {
 
+// Lanes per item of a dense launch.  A tile is a wave of 64 pixels: a frame of
+// fewer tiles than the device has SIMDs leaves SIMDs idle for as long as one wave
+// takes over its window, so it runs 16 lanes per item (r = 7, three frames, F = 7:
+// 4096 pixels 129 -> 19 us, 32768 pixels 143 -> 77 us, 65536 pixels, a tile for
+// each SIMD, 154 against 146 us, 131072 pixels 263 against 289 us).
+int dense_lanes(esim_plan pl) {
+  const bool few = pl->dense_groups[5] < 4ll * pl->shape.cus;
+  return pl->auto_dense && few && pl->host[0].precision == ESIM_GRAM_F64 ? 16 : pl->lanes_dense;
+}
+
 // Arguments of a regression launch with L lanes per item; seg: the clips of one
 // segment of a split work list only (-1: all).
 esim::RegressArgs regress_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
@@ -111,7 +122,9 @@ esim::RegressArgs regress_args(esim_plan pl, int32_t t, const int64_t* worklist,
   a.n_out = n_out;
   a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * dense : nullptr;
   a.nxcd = pl->shape.xcds;
-  a.single = max_r <= 7 && max_tr <= 1 ? 1 : 0;
+  // 9 to 15 columns are one uncut turn of 16 lanes; narrower windows fill the lanes
+  // better cut into parts (65536 items at r = 3: 84 us, uncut 98)
+  a.single = max_r >= 4 && max_r <= 7 && max_tr <= 1 ? 1 : 0;
   return a;
 }
 
@@ -120,7 +133,7 @@ int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const 
                         bool update_state, hipStream_t stream, int seg = -1) {
   // the condition estimate of the FP64 Gram comes from a one-lane instance
   const bool kappa_f64 = kappa && pl->host[0].precision == ESIM_GRAM_F64;
-  const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : pl->lanes_dense;
+  const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : dense_lanes(pl);
   if (!esim::regress_supports(pl->F, L, pl->host[0].precision))
     return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
   esim::RegressArgs a = regress_args(pl, t, worklist, count, n_out, L, kappa != nullptr, seg);
@@ -726,8 +739,8 @@ int esim_wlr_regress_bandwidth(esim_plan pl, int32_t t, const int64_t* worklist,
       a.h[k] = hs[k];
       a.scale[k] = hc.h / hs[k];
     }
-    a.reg = regress_args(pl, t, worklist, count, worklist ? std::min(n_out, pl->wl_capacity) : n_out,
-                         worklist ? 16 : 1, false);
+    const int L = worklist || dense_lanes(pl) == 16 ? 16 : 1;
+    a.reg = regress_args(pl, t, worklist, count, worklist ? std::min(n_out, pl->wl_capacity) : n_out, L, false);
     a.reg.n_out = n_out;
     a.reg.alpha = alpha;
     a.reg.beta = beta;
@@ -735,7 +748,7 @@ int esim_wlr_regress_bandwidth(esim_plan pl, int32_t t, const int64_t* worklist,
     a.K = K;
     a.hsel = hsel;
     a.sure = sure;
-    return hip_check(esim::launch_bandwidth(a, pl->F, pl->f16, pl->shape, static_cast<hipStream_t>(stream)),
+    return hip_check(esim::launch_bandwidth(a, pl->F, pl->f16, L, pl->shape, static_cast<hipStream_t>(stream)),
                      "regress_bandwidth");
   } catch (...) {
     return fail(ESIM_E_HIP, "exception");
@@ -866,6 +879,7 @@ int esim_plan_set_schedule(esim_plan pl, int32_t lanes_dense, int32_t lanes_list
       return fail(ESIM_E_UNSUPPORTED, "lanes per item not compiled for this F and precision");
   if (blocks_per_cu < 1 || blocks_per_cu > 64) return fail(ESIM_E_INVAL, "blocks_per_cu outside 1..64");
   pl->lanes_dense = lanes_dense;
+  pl->auto_dense = false;
   pl->lanes_list = lanes_list;
   pl->blocks_per_cu = blocks_per_cu;
   return ok();

@@ -394,11 +394,8 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   const ClipDev& hc = *a.host_clip;
   const int F = hc.F, D = F + 2;
   const RegressTable* t = regress_table(F);
-  // 16 lanes per item (one column each) when the window is a single walk; wider
-  // ones leave fewer lanes idle with 4
   AdjointArgs adj{};
   adj.reg = a.reg;
-  const int L = adj.reg.single ? 16 : 4;
   const AdjointFn fn = t ? t->adjoint[adj.reg.single ? 0 : 1][hc.feat_f16 != 0] : nullptr;
   GatherFn gat = pick_gather(F);
   RedFn rb = pick_red(D);
@@ -414,7 +411,7 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
                      a.g_alpha, bd.item_map);
   adj.g_alpha = a.g_alpha;
   adj.bd = bd;
-  adj.reg.max_groups = (a.n + kWave / L - 1) / (kWave / L);
+  adj.reg.max_groups = (a.n + kWave / 16 - 1) / (kWave / 16);
   const int waves = regress_waves_per_simd(F, false);
   const hipError_t e = launch_groups(reinterpret_cast<const void*>(fn), &adj, adj.reg, waves, true, waves, a.dev, s);
   if (e != hipSuccess) return e;

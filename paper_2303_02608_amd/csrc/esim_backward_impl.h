@@ -34,17 +34,7 @@ adjoint_kernel(AdjointArgs b) {
       int64_t pix, idx;
       const bool valid = group_item<L>(a, queue.group(k), slot, n_items, cl, pix, t, idx) && b.g_alpha[idx] != 0.0f;
       double* to = parked + (static_cast<int>(k - k0) * G + slot) * R::STRIDE + j;
-      window_grams<F, L, F16, SINGLE>(a, valid, cl, pix, t, j,
-                                      [&](const ClipDev&, bool active, int64_t, int, Gram<F, double>& got) {
-        double s[R::NE];
-        int e = 0;
-        got.each([&](double& v) { s[e++] = v; });
-        scatter_sum<L>(s, lane);
-        if (active) {
-#pragma unroll
-          for (int q = 0; q < R::REGS; ++q) to[q * L] = s[q];
-        }
-      });
+      park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to);
     }
     __syncthreads();
     const int i = threadIdx.x;
@@ -56,9 +46,7 @@ adjoint_kernel(AdjointArgs b) {
         if (g != 0.0f) {
           const ClipDev& C = a.clips[0];
           Gram<F, double> gm;
-          const double* q = parked + i * R::STRIDE;
-          int e = 0;
-          gm.each([&](double& v) { v = q[total_pos<L>(e++)]; });
+          parked_gram<F, L>(parked + i * R::STRIDE, gm);
           double M[P * (P + 1) / 2], rhs[P], th[P], e0[P], vv[P], anorm;
           const double iW = gram_solve<F, double>(gm, C, M, rhs, th, anorm);
           (void)anorm;

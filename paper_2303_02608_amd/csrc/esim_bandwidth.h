@@ -19,6 +19,8 @@ struct BandwidthArgs {
 
 hipError_t launch_log_variance(const float* E, const float* var, float* vy, int64_t n, int spp, float eps,
                                hipStream_t s);
-hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, const DeviceShape& dev, hipStream_t s);
+// lanes: 16 (work lists, small frames) or 1 (dense).
+hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, int lanes, const DeviceShape& dev,
+                            hipStream_t s);
 
 }  // namespace esim

@@ -45,16 +45,16 @@ hipError_t launch_log_variance(const float* E, const float* var, float* vy, int6
   return hipGetLastError();
 }
 
-hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, const DeviceShape& dev, hipStream_t s) {
+hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, int lanes, const DeviceShape& dev, hipStream_t s) {
   const RegressArgs& a = b.reg;
   const RegressTable* t = regress_table(F);
-  const BandwidthFn k = !t         ? nullptr
-                        : !a.items ? t->bandwidth[a.tile_units ? 0 : 1][f16]
-                                   : t->bandwidth[a.single ? 2 : 3][f16];
+  const BandwidthFn k = !t            ? nullptr
+                        : lanes == 16 ? t->bandwidth[a.single ? 2 : 3][f16]
+                                      : t->bandwidth[a.tile_units ? 0 : 1][f16];
   if (!k) return hipErrorInvalidValue;
   const int waves = regress_waves_per_simd(F, false);
   return launch_groups(reinterpret_cast<const void*>(k), const_cast<BandwidthArgs*>(&b), a, waves,
-                       a.items || a.tile_units, waves, dev, s);
+                       lanes == 16 || a.tile_units, waves, dev, s);
 }
 
 }  // namespace esim

@@ -72,7 +72,7 @@ bandwidth_tile_kernel(BandwidthArgs b) {
       LaneSums<F> ls;
       tile_window(geo, lds, c, ls);
       Gram<F, double> gm;
-      gram_of_lane<F, true>(c, ls, geo.vx_step, geo.r, gm);
+      gram_of_lane<F, true>(c, ls, geo.vx_step, gm);
       if (geo.px < geo.W && geo.py < geo.H) {
         const int64_t pix = static_cast<int64_t>(geo.py) * geo.W + geo.px;
         solve_candidate<F>(b, C, k, pix, pix, gm, best);
@@ -96,14 +96,14 @@ bandwidth_dense_kernel(BandwidthArgs b) {
     double best = INFINITY;
 #pragma unroll 1
     for (int k = 0; k < b.K; ++k)
-      window_grams<F, 1, F16, false>(a, valid, cl, pix, t, 0,
+      window_grams<F, 1, F16>(a, valid, cl, pix, t, 0,
                                      [&](const ClipDev& C, bool active, int64_t p, int, Gram<F, double>& gm) {
         if (active) solve_candidate<F>(b, C, k, idx, p, gm, best);
       }, uni(b.scale[k] * b.scale[k]));
   }
 }
 
-// Work lists: the list regression's rounds, once per candidate; the thread that
+// Work lists and small frames: the list regression's rounds, once per candidate; the thread that
 // solves an item keeps its best SURE.
 template <int F, bool F16, bool SINGLE>
 __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
@@ -114,10 +114,11 @@ bandwidth_list_kernel(BandwidthArgs b) {
   __shared__ double parked[R::ITEMS * R::STRIDE];
   __shared__ int taken;
   const RegressArgs& a = b.reg;
-  const int64_t n_items = max(static_cast<int64_t>(0), min(static_cast<int64_t>(a.count[0]), a.n_out));
+  const int64_t n_items =
+      a.items ? max(static_cast<int64_t>(0), min(static_cast<int64_t>(a.count[0]), a.n_out)) : 0;
   const int lane = threadIdx.x & (kWave - 1);
   const int slot = item_slot<L>(lane), j = item_lane<L>(lane);
-  const GroupQueue queue((n_items + G - 1) / G, 1, a.nxcd, &taken);
+  const GroupQueue queue(a.items ? (n_items + G - 1) / G : a.n_dense_groups, 1, a.nxcd, &taken);
   for (int64_t k0 = 0; k0 < queue.count; k0 += R::GROUPS) {
     const int n = static_cast<int>(min(static_cast<int64_t>(R::GROUPS), queue.count - k0));
     const int i = threadIdx.x;                  // the item of the round that this thread solves
@@ -132,25 +133,13 @@ bandwidth_list_kernel(BandwidthArgs b) {
         int64_t pix, idx;
         const bool valid = group_item<L>(a, queue.group(k0 + q), slot, n_items, cl, pix, t, idx);
         double* to = parked + (static_cast<int>(q) * G + slot) * R::STRIDE + j;
-        window_grams<F, L, F16, SINGLE>(a, valid, cl, pix, t, j,
-                                        [&](const ClipDev&, bool active, int64_t, int, Gram<F, double>& got) {
-          double s[R::NE];
-          int e = 0;
-          got.each([&](double& v) { s[e++] = v; });
-          scatter_sum<L>(s, lane);
-          if (active) {
-#pragma unroll
-            for (int u = 0; u < R::REGS; ++u) to[u * L] = s[u];
-          }
-        }, uni(b.scale[k] * b.scale[k]));
+        park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to, uni(b.scale[k] * b.scale[k]));
       }
       __syncthreads();
       if (threadIdx.x == 0) *queue.taken = static_cast<int>(blockDim.x / kWave);
       if (mine) {
         Gram<F, double> gm;
-        const double* p = parked + i * R::STRIDE;
-        int e = 0;
-        gm.each([&](double& v) { v = p[total_pos<L>(e++)]; });
+        parked_gram<F, L>(parked + i * R::STRIDE, gm);
         solve_candidate<F>(b, a.clips[0], k, my_idx, my_pix, gm, best);
       }
       __syncthreads();

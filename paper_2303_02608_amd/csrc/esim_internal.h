@@ -197,7 +197,7 @@ struct RegressArgs {
   int32_t update_state;     // write each item's model into its clip state (Sec. 2.2)
   const int64_t* xcd_bounds;  // dense multi-clip launches: [nxcd + 1] group bounds per XCD (device)
   int32_t nxcd;               // XCDs of the device (group-to-XCD mapping)
-  int32_t single;             // every item's window has at most 16 columns and three frames
+  int32_t single;             // every item's window is one turn of uncut columns of 16 lanes (walk_parts)
   int32_t tile_units;         // dense tiles: 16-byte units of a wave's LDS (0: groups of lanes, no tiles)
   int32_t tile_last;          // and of the record behind the block's last wave
 };
@@ -219,11 +219,11 @@ constexpr int regress_waves_per_simd(int F, bool c32) { return (!c32 && F <= 8) 
 // compensated FP32 [lanes 4, 16][f16] (null where not compiled).
 struct RegressTable {
   KernelFn general[5][2] = {};
-  KernelFn single[2] = {};     // 16 lanes per item, each with a single column of at most three frames
+  KernelFn single[2] = {};     // 16 lanes per item, windows of one turn of uncut columns (walk_parts)
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item
   BandwidthFn bandwidth[4][2] = {};   // dense tiles, dense from memory, lists (single column), lists
-  AdjointFn adjoint[2][2] = {};       // 16 lanes per item (single column), 4 lanes
+  AdjointFn adjoint[2][2] = {};       // 16 lanes per item, single column or any window
   KernelFn tile[2] = {};       // FP64 Gram, one lane per item, dense, windows in LDS
 };
 

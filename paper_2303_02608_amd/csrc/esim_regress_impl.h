@@ -146,15 +146,13 @@ __device__ __forceinline__ void write_item(const RegressArgs& a, const ClipDev& 
   }
 }
 
-// The items of one wave's group: calls fn(C, active, pix, t, got) with the
-// window sums `got` (weights to the power wscale) of the lane's part of its item (FP64 Gram; the columns j,
-// j + L, ... of the window; SINGLE: at most one column of at most three frames).
-// Rounds over the (clip, first
-// frame, frame count) present in the wave, so that those are uniform in the
-// walk: nearly always one round.
-template <int F, int L, bool F16, bool SINGLE, class Fn>
-__device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, int my_cl, int64_t my_pix, int my_t,
-                                             int j, Fn&& fn, double wscale = 1.0) {
+// The items of one wave's group: calls fn(C, geo, active, pix, t) for the lanes'
+// items with their walk's geometry (weights to the power wscale).  Rounds over the
+// (clip, first frame, frame count) present in the wave, so that those are uniform
+// in the walk: nearly always one round.
+template <int F, bool F16, class Fn>
+__device__ __forceinline__ void group_rounds(const RegressArgs& a, bool valid, int my_cl, int64_t my_pix, int my_t,
+                                             double wscale, Fn&& fn) {
   uint64_t todo = __ballot(valid);
   while (todo != 0) {
     const int src = __ffsll(static_cast<unsigned long long>(todo)) - 1;
@@ -176,22 +174,24 @@ __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, i
     const int f1 = a.t >= 0 ? min(T, a.t + tr + 1) : T;
     WalkGeom<F, F16> geo;
     make_walk(geo, C, pix, t, lo, hi - lo + 1, f0, f1, active, wscale);
-    ColumnSums<F> c;
-    Gram<F, double> got;
-    if constexpr (SINGLE) {
-      c.zero();
-      const int dx = j - geo.r;
-      if (geo.nt == 3) walk_frames<F, F16, 3, 2>(geo, dx, 0, c);
-      else if (geo.nt == 2) walk_frames<F, F16, 2, 2>(geo, dx, 0, c);
-      else walk_frames<F, F16, 1, 2>(geo, dx, 0, c);
-      gram_of_column(c, static_cast<double>(dx) * geo.vx_step, geo.vy_step, geo.r, got);
-    } else {
-      LaneSums<F> ls;
-      walk_window<F, L, F16>(geo, j, c, ls);
-      gram_of_lane(c, ls, geo.vy_step, geo.r, got);
-    }
-    fn(C, active, pix, t, got);
+    fn(C, geo, active, pix, t);
   }
+}
+
+// The same with the window sums `got` of the lane's part of its item (the columns
+// j, j + L, ...): fn(C, active, pix, t, got).
+template <int F, int L, bool F16, class Fn>
+__device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, int my_cl, int64_t my_pix, int my_t,
+                                             int j, Fn&& fn, double wscale = 1.0) {
+  group_rounds<F, F16>(a, valid, my_cl, my_pix, my_t, wscale,
+                       [&](const ClipDev& C, const WalkGeom<F, F16>& geo, bool active, int64_t pix, int t) {
+    ColumnSums<F> c;
+    LaneSums<F> ls;
+    walk_window<F, L, F16>(geo, j, c, ls);
+    Gram<F, double> got;
+    gram_of_lane(c, ls, geo.vy_step, got);
+    fn(C, active, pix, t, got);
+  });
 }
 
 // The groups of one wave of an instance of 1 or 2 lanes per item, FP64 Gram: every
@@ -208,7 +208,7 @@ __device__ __forceinline__ void regress_groups(const RegressArgs& a, GroupIter& 
     int cl, t;
     int64_t pix, idx;
     const bool valid = group_item<L>(a, g, slot, n_items, cl, pix, t, idx);
-    window_grams<F, L, F16, false>(a, valid, cl, pix, t, j,
+    window_grams<F, L, F16>(a, valid, cl, pix, t, j,
                             [&](const ClipDev& C, bool active, int64_t ipix, int it_t, Gram<F, double>& gm) {
       gm.template lane_sum<L>();
       double M[P * (P + 1) / 2], th[P], rhs[P], anorm, kap = 0.0;
@@ -242,6 +242,35 @@ struct ListRound {
   static constexpr int STRIDE = REGS * L + 1;                       // odd: neighbouring items on other banks
 };
 
+// Walks the items of a group and parks their totals: lane j's share of item
+// `slot` goes to to[q L], to being the lane's place in the item's parking space.
+template <int F, int L, bool F16, bool SINGLE>
+__device__ __forceinline__ void park_group(const RegressArgs& a, bool valid, int cl, int64_t pix, int t, int j,
+                                           double* to, double wscale = 1.0) {
+  using R = ListRound<F, L>;
+  const int lane = threadIdx.x & (kWave - 1);
+  group_rounds<F, F16>(a, valid, cl, pix, t, wscale,
+                       [&](const ClipDev&, const WalkGeom<F, F16>& geo, bool active, int64_t, int) {
+    walk_parts<F, L, F16, SINGLE>(geo, j, [&](Gram<F, double>& got, bool first) {
+      double s[R::NE];
+      int e = 0;
+      got.each([&](double& v) { s[e++] = v; });
+      scatter_sum<L>(s, lane);
+      if (active) {
+#pragma unroll
+        for (int q = 0; q < R::REGS; ++q) to[q * L] = first ? s[q] : to[q * L] + s[q];
+      }
+    });
+  });
+}
+
+// The totals of a parked item.
+template <int F, int L>
+__device__ __forceinline__ void parked_gram(const double* at, Gram<F, double>& gm) {
+  int e = 0;
+  gm.each([&](double& v) { v = at[total_pos<L>(e++)]; });
+}
+
 template <int F, int L, bool F16, bool SINGLE = false>
 __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
 __attribute__((amdgpu_waves_per_eu(regress_waves_per_simd(F, false))))
@@ -267,17 +296,7 @@ regress_list_kernel(RegressArgs a) {
       int64_t pix, idx;
       const bool valid = group_item<L>(a, queue.group(k), slot, n_items, cl, pix, t, idx);
       double* to = parked + (static_cast<int>(k - k0) * G + slot) * R::STRIDE + j;
-      window_grams<F, L, F16, SINGLE>(a, valid, cl, pix, t, j,
-                              [&](const ClipDev&, bool active, int64_t, int, Gram<F, double>& got) {
-        double s[R::NE];
-        int e = 0;
-        got.each([&](double& v) { s[e++] = v; });
-        scatter_sum<L>(s, lane);
-        if (active) {
-#pragma unroll
-          for (int q = 0; q < R::REGS; ++q) to[q * L] = s[q];
-        }
-      });
+      park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to);
     }
     __syncthreads();
     const int i = threadIdx.x;
@@ -287,9 +306,7 @@ regress_list_kernel(RegressArgs a) {
       if (group_item<L>(a, queue.group(k0 + i / G), i % G, n_items, cl, pix, t, idx)) {
         const ClipDev& C = a.clips[cl];
         Gram<F, double> gm;
-        const double* q = parked + i * R::STRIDE;
-        int e = 0;
-        gm.each([&](double& v) { v = q[total_pos<L>(e++)]; });
+        parked_gram<F, L>(parked + i * R::STRIDE, gm);
         double M[P * (P + 1) / 2], th[P], rhs[P], anorm;
         const double iW = gram_solve<F, double>(gm, C, M, rhs, th, anorm);
         (void)anorm;
@@ -390,7 +407,7 @@ regress_tile_kernel(RegressArgs a) {
     LaneSums<F> ls;
     tile_window(geo, lds, c, ls);
     Gram<F, double> gm;
-    gram_of_lane<F, true>(c, ls, geo.vx_step, geo.r, gm);
+    gram_of_lane<F, true>(c, ls, geo.vx_step, gm);
     double M[P * (P + 1) / 2], th[P], rhs[P], anorm;
     const double iW = gram_solve<F, double>(gm, C, M, rhs, th, anorm);
     (void)anorm;

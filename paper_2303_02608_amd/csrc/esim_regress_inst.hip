@@ -39,8 +39,8 @@ void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   t.bandwidth[3][1] = bandwidth_list_kernel<F, true, false>;
   t.adjoint[0][0] = adjoint_kernel<F, 16, false, true>;
   t.adjoint[0][1] = adjoint_kernel<F, 16, true, true>;
-  t.adjoint[1][0] = adjoint_kernel<F, 4, false, false>;
-  t.adjoint[1][1] = adjoint_kernel<F, 4, true, false>;
+  t.adjoint[1][0] = adjoint_kernel<F, 16, false, false>;
+  t.adjoint[1][1] = adjoint_kernel<F, 16, true, false>;
   t.kappa[0] = regress_kernel<F, 1, false, false, true>;
   t.kappa[1] = regress_kernel<F, 1, true, false, true>;
   // the compensated-FP32 variant is compiled for the feature counts of the

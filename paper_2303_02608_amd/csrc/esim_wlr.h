@@ -358,35 +358,38 @@ struct ColumnSums {
   }
 };
 
-// What the finished columns of a lane add up to, and their sums times v_x.
+// What the finished lines of a lane add up to: the sums, their first moment along
+// the walk (Y, and YY of W) and both times the line's coordinate (X).
 template <int F>
 struct LaneSums {
-  double W, g, f[F], PW, PPW, Pg, Pf[F];
-  double XW, Xg, Xf[F], XX, XPW;
+  double W, g, f[F], YW, YY, Yg, Yf[F];
+  double XW, XX, Xg, Xf[F], XY;
 
   __device__ __forceinline__ void zero() {
-    W = g = PW = PPW = Pg = XW = Xg = XX = XPW = 0;
+    W = g = YW = YY = Yg = XW = Xg = XX = XY = 0;
 #pragma unroll
-    for (int k = 0; k < F; ++k) f[k] = Pf[k] = Xf[k] = 0;
+    for (int k = 0; k < F; ++k) f[k] = Yf[k] = Xf[k] = 0;
   }
-  // Takes over the column at v_x and clears its part of c (the sums without a
-  // coordinate factor stay in c).
-  __device__ __forceinline__ void end_column(ColumnSums<F>& c, double vx) {
+  // Takes over the line at coordinate x and clears its part of c (the sums
+  // without a coordinate factor stay in c).  The walk ended at e: its cells lay at
+  // e - n .. e - 1 in steps of the walked coordinate.
+  __device__ __forceinline__ void end_line(ColumnSums<F>& c, double x, double e) {
+    const double yw = fma(e, c.W, -c.PW);
     W += c.W;
-    XW = fma(vx, c.W, XW);
-    XX = fma(vx * vx, c.W, XX);
-    XPW = fma(vx, c.PW, XPW);
+    XW = fma(x, c.W, XW);
+    XX = fma(x * x, c.W, XX);
+    YW += yw;
+    XY = fma(x, yw, XY);
+    YY += fma(e * e, c.W, fma(-(2.0 * e + 1.0), c.PW, 2.0 * c.PPW));
     g += c.g;
-    Xg = fma(vx, c.g, Xg);
-    PW += c.PW;
-    PPW += c.PPW;
-    Pg += c.Pg;
+    Xg = fma(x, c.g, Xg);
+    Yg += fma(e, c.g, -c.Pg);
     c.W = c.g = c.PW = c.PPW = c.Pg = 0;
 #pragma unroll
     for (int k = 0; k < F; ++k) {
       f[k] += c.f[k];
-      Xf[k] = fma(vx, c.f[k], Xf[k]);
-      Pf[k] += c.Pf[k];
+      Xf[k] = fma(x, c.f[k], Xf[k]);
+      Yf[k] += fma(e, c.f[k], -c.Pf[k]);
       c.f[k] = c.Pf[k] = 0;
     }
   }
@@ -444,9 +447,11 @@ __device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C,
 // Walks R consecutive frames, the first k0 frames after dt_lo, of the column dx
 // of the lane's item (dx > r: an idle column, weight 0), adding their samples to
 // c.  DEPTH (1 or 2) cells of samples are loaded ahead: a sample's registers are
-// reloaded as soon as it is used.
-template <int F, bool F16, int R, int DEPTH = 1>
-__device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, ColumnSums<F>& c) {
+// reloaded as soon as it is used.  PART: only the n rows from s0 on (s0 >= -r may
+// differ between the lanes; rows below r get weight 0).
+template <int F, bool F16, int R, int DEPTH = 1, bool PART = false>
+__device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, ColumnSums<F>& c,
+                                            int s0 = 0, int n = 0) {
   constexpr uint32_t ES = WalkGeom<F, F16>::ES;
   const double K = g.kexp;
   const int r = g.r;
@@ -460,6 +465,11 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
   const uint32_t HES = g.HW * ES, FES = static_cast<uint32_t>(F) * HES, HW4 = g.HW * 4u;
   const uint32_t sof = static_cast<uint32_t>(k0) * FES, soy = static_cast<uint32_t>(k0) * HW4;   // uniform
   uint32_t vf = g.vf0 + cc * ES, vy = g.vy0 + cc * 4u;         // offsets of the next row to load
+  if constexpr (PART) {                    // from row py + s0 on
+    const uint32_t skip = static_cast<uint32_t>(min(max(g.py + min(s0, r), 0), g.H - 1) - max(g.py - r, 0));
+    vf += skip * WES;
+    vy += skip * W4;
+  }
   float ys[DEPTH][R], fs[DEPTH][R][F];
   auto load = [&](int d, int i) {
     ys[d][i] = ld_f32(g.ry, vy, soy + i * HW4);
@@ -467,14 +477,16 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
     for (int f = 0; f < F; ++f) fs[d][i][f] = ld_feat<F16>(g.rf, vf, sof + i * FES + f * HES);
   };
   auto next_row = [&](int dy) {            // a step down where rows dy and dy + 1 are in the image
-    const bool down = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H - 1);
+                                           // (a part's also in the window: what it reads counts)
+    const bool down = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H - 1) && (!PART || dy < r);
     vf += down ? WES : 0u;
     vy += down ? W4 : 0u;
   };
   auto cell = [&](int d, int dy) {
     next_row(dy + DEPTH - 1);
     const double e = fma(kyy, static_cast<double>(dy * dy), kx);
-    const double base = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H) ? e : kDropped;
+    const bool row_ok = static_cast<uint32_t>(g.py + dy) < static_cast<uint32_t>(g.H) && (!PART || dy <= r);
+    const double base = row_ok ? e : kDropped;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       double v[F], s0 = 0, s1 = 0;
@@ -496,9 +508,19 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
   for (int d = 0; d < DEPTH; ++d) {
 #pragma unroll
     for (int i = 0; i < R; ++i) load(d, i);
-    if (d + 1 < DEPTH) next_row(d - r);
+    if (d + 1 < DEPTH) next_row(d + (PART ? s0 : -r));
   }
-  if constexpr (DEPTH == 1) {
+  if constexpr (PART && DEPTH == 1) {
+#pragma unroll 1
+    for (int k = 0; k < n; ++k) cell(0, s0 + k);
+  } else if constexpr (PART) {
+#pragma unroll 1
+    for (int k = 0; k + 1 < n; k += 2) {
+      cell(0, s0 + k);
+      cell(1, s0 + k + 1);
+    }
+    if (n & 1) cell(0, s0 + n - 1);
+  } else if constexpr (DEPTH == 1) {
 #pragma unroll 1
     for (int dy = -r; dy <= r; ++dy) cell(0, dy);
   } else {
@@ -512,9 +534,8 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
   }
 }
 
-// The columns j, j + L, ... of the lane's item, up to three frames at a time
-// (three rows of loads in flight); the totals go to c (entries without a
-// coordinate) and ls.
+// The columns j, j + L, ... of the lane's item, up to three frames at a time; the
+// totals go to c (entries without a coordinate) and ls.
 template <int F, int L, bool F16>
 __device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, ColumnSums<F>& c, LaneSums<F>& ls) {
   c.zero();
@@ -524,11 +545,11 @@ __device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, Co
     const double vx = static_cast<double>(d0 + j) * g.vx_step;
 #pragma unroll 1
     for (int k0 = 0; k0 < g.nt; k0 += 3) {
-      const int n = g.nt - k0;
-      if (n >= 3) walk_frames<F, F16, 3>(g, d0 + j, k0, c);
-      else if (n == 2) walk_frames<F, F16, 2>(g, d0 + j, k0, c);
+      const int left = g.nt - k0;
+      if (left >= 3) walk_frames<F, F16, 3>(g, d0 + j, k0, c);
+      else if (left == 2) walk_frames<F, F16, 2>(g, d0 + j, k0, c);
       else walk_frames<F, F16, 1>(g, d0 + j, k0, c);
-      ls.end_column(c, vx);
+      ls.end_line(c, vx, static_cast<double>(g.r + 1));
     }
   }
 }
@@ -730,7 +751,7 @@ __device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* l
       at += U;
       c.end_cell();
     }
-    ls.end_column(c, vy);
+    ls.end_line(c, vy, static_cast<double>(r + 1));
     wave_lds_order();
     next = next + 1 == TH ? 0 : next + 1;
     slot = slot + 1 == TH ? 0 : slot + 1;
@@ -897,55 +918,49 @@ struct Gram {
 // Totals of the lane's part of its item from its walk: along columns (v_y is the
 // walked coordinate, steps of s, and v_x the lines' one) or, ROWS, along rows.
 template <int F, bool ROWS = false>
-__device__ __forceinline__ void gram_of_lane(const ColumnSums<F>& c, const LaneSums<F>& l, double s, int r,
+__device__ __forceinline__ void gram_of_lane(const ColumnSums<F>& c, const LaneSums<F>& l, double s,
                                              Gram<F, double>& G) {
-  const double r1 = static_cast<double>(r + 1);
-  const double first = s * fma(r1, l.W, -l.PW);
-  const double second = s * s * fma(r1 * r1, l.W, fma(-static_cast<double>(2 * r + 3), l.PW, 2.0 * l.PPW));
-  const double gwalk = s * fma(r1, l.g, -l.Pg);
   G.SW = l.W;
   G.g0 = l.g;
   G.Syy = c.Syy;
-  G.A0x = ROWS ? first : l.XW;
-  G.A0y = ROWS ? l.XW : first;
-  G.Axx = ROWS ? second : l.XX;
-  G.Ayy = ROWS ? l.XX : second;
-  G.gx = ROWS ? gwalk : l.Xg;
-  G.gy = ROWS ? l.Xg : gwalk;
-  G.Axy = s * fma(r1, l.XW, -l.XPW);
+  G.A0x = ROWS ? s * l.YW : l.XW;
+  G.A0y = ROWS ? l.XW : s * l.YW;
+  G.Axx = ROWS ? s * s * l.YY : l.XX;
+  G.Ayy = ROWS ? l.XX : s * s * l.YY;
+  G.gx = ROWS ? s * l.Yg : l.Xg;
+  G.gy = ROWS ? l.Xg : s * l.Yg;
+  G.Axy = s * l.XY;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    const double fwalk = s * fma(r1, l.f[f], -l.Pf[f]);
     G.A0f[f] = l.f[f];
     G.gf[f] = c.gf[f];
-    G.Axf[f] = ROWS ? fwalk : l.Xf[f];
-    G.Ayf[f] = ROWS ? l.Xf[f] : fwalk;
+    G.Axf[f] = ROWS ? s * l.Yf[f] : l.Xf[f];
+    G.Ayf[f] = ROWS ? l.Xf[f] : s * l.Yf[f];
   }
 #pragma unroll
   for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
 }
 
-// The same for a lane with a single column, at v_x.
+// The same for one column or part of it, at v_x; its walk ended at e (steps of s).
 template <int F>
-__device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx, double s, int r,
+__device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx, double s, double e,
                                                Gram<F, double>& G) {
-  const double r1 = static_cast<double>(r + 1);
   G.SW = c.W;
   G.g0 = c.g;
   G.Syy = c.Syy;
   G.A0x = vx * c.W;
   G.Axx = vx * G.A0x;
   G.gx = vx * c.g;
-  G.A0y = s * fma(r1, c.W, -c.PW);
-  G.Ayy = s * s * fma(r1 * r1, c.W, fma(-static_cast<double>(2 * r + 3), c.PW, 2.0 * c.PPW));
+  G.A0y = s * fma(e, c.W, -c.PW);
+  G.Ayy = s * s * fma(e * e, c.W, fma(-(2.0 * e + 1.0), c.PW, 2.0 * c.PPW));
   G.Axy = vx * G.A0y;
-  G.gy = s * fma(r1, c.g, -c.Pg);
+  G.gy = s * fma(e, c.g, -c.Pg);
 #pragma unroll
   for (int f = 0; f < F; ++f) {
     G.A0f[f] = c.f[f];
     G.gf[f] = c.gf[f];
     G.Axf[f] = vx * c.f[f];
-    G.Ayf[f] = s * fma(r1, c.f[f], -c.Pf[f]);
+    G.Ayf[f] = s * fma(e, c.f[f], -c.Pf[f]);
   }
 #pragma unroll
   for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
@@ -1020,6 +1035,54 @@ __host__ __device__ constexpr int total_pos(int e) {
   for (int b = 1, m = L >> 1; b < L; b <<= 1, m >>= 1)
     if (e & b) low |= m;
   return e / L * L + low;
+}
+
+// Walks the lane's part of its item's window (lane j of L) and calls fn(G, first)
+// with the totals of each turn, to be summed over the turns: no sums are kept in
+// registers from one turn to the next, so that a turn has room for two rows of
+// loads ahead.  A turn is up to three frames of a column per lane; where fewer
+// than L columns are left (q), each is cut into L / q parts of equal height, one
+// lane each, so that the last turn is as short as the lanes allow: at r = 9,
+// 16 lanes walk 19 rows of 16 columns and then 4 rows of the last 3 columns (5
+// lanes a column).  SINGLE: one turn of uncut columns (L / 2 < 2 r + 1 <= L, at
+// most three frames).  With whole columns in every turn, sums kept in registers
+// between turns and so one row of loads ahead, lists of 65536 / 4096 items (one in
+// eight pixels of a wide image, F = 7, three frames) took 98 / 14 us at r = 3, 392 /
+// 39 at r = 8, 426 / 42 at r = 9 and 537 / 50 at r = 12; now 84 / 14, 282 / 29, 324 /
+// 30 and 500 / 46.  F = 10, r = 10, five frames: 1344 / 95, now 955 / 69.
+template <int F, int L, bool F16, bool SINGLE, class Fn>
+__device__ __forceinline__ void walk_parts(const WalkGeom<F, F16>& g, int j, Fn&& fn) {
+  ColumnSums<F> c;
+  Gram<F, double> got;
+  if constexpr (SINGLE) {
+    const int dx = j - g.r;
+    c.zero();
+    if (g.nt == 3) walk_frames<F, F16, 3, 2>(g, dx, 0, c);
+    else if (g.nt == 2) walk_frames<F, F16, 2, 2>(g, dx, 0, c);
+    else walk_frames<F, F16, 1, 2>(g, dx, 0, c);
+    gram_of_column(c, static_cast<double>(dx) * g.vx_step, g.vy_step, static_cast<double>(g.r + 1), got);
+    fn(got, true);
+  } else {
+    const int span = 2 * g.r + 1;
+#pragma unroll 1
+    for (int d0 = 0; d0 < span; d0 += L) {
+      const int q = min(L, span - d0), parts = L / q, n = (span + parts - 1) / parts;
+      // idle lanes (part >= parts) and rows past the window walk with weight 0
+      const int part = j / q;
+      const int dx = part < parts ? d0 + j - part * q - g.r : g.r + 1;
+      const int s0 = part * n - g.r;
+#pragma unroll 1
+      for (int k0 = 0; k0 < g.nt; k0 += 3) {
+        const int left = g.nt - k0;
+        c.zero();
+        if (left >= 3) walk_frames<F, F16, 3, 2, true>(g, dx, k0, c, s0, n);
+        else if (left == 2) walk_frames<F, F16, 2, 2, true>(g, dx, k0, c, s0, n);
+        else walk_frames<F, F16, 1, 2, true>(g, dx, k0, c, s0, n);
+        gram_of_column(c, static_cast<double>(dx) * g.vx_step, g.vy_step, static_cast<double>(s0 + n), got);
+        fn(got, d0 == 0 && k0 == 0);
+      }
+    }
+  }
 }
 
 // Neumaier-compensated accumulation: (hi, lo) += x.

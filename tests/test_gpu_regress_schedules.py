@@ -57,6 +57,7 @@ def test_dense_tiles(W, H, T, F, r, tr, t, f16):
     p = B.Params(r=r, tr=tr, C=0.2, h=1.2)
     y, fd = to_dev(E, feat)
     plan = B.Plan([y], [fd], [p])
+    plan.set_schedule(1, 16, 2)          # a frame this small takes 16 lanes per item by itself
     got = _run(plan, t, None, W * H)
     ref = oracle.regress_items(oracle_clip(E, feat), oracle.Params(r, tr, 0.2, 1.2), t * W * H + np.arange(W * H),
                                kappa=False)
@@ -72,6 +73,7 @@ def test_dense_tiles_of_several_clips():
     devs = [to_dev(*c) for c in clips]
     plan = B.Plan([y for y, _ in devs], [f for _, f in devs],
                   [B.Params(r=r, tr=1, C=0.2) for *_, r in shapes])
+    plan.set_schedule(1, 16, 2)
     a, b, R = _run(plan, 2, None, plan.npix)
     for k, (W, H, T, r) in enumerate(shapes):
         s = slice(plan.offsets[k], plan.offsets[k] + W * H)
@@ -84,7 +86,7 @@ def test_dense_tiles_of_several_clips():
 
 
 @pytest.mark.parametrize("lanes", [4, 8, 16])
-@pytest.mark.parametrize("r,tr", [(7, 1), (8, 1), (3, 2)])
+@pytest.mark.parametrize("r,tr", [(7, 1), (8, 1), (3, 2), (1, 1), (12, 0)])
 def test_work_lists(lanes, r, tr):
     """Lists shorter than a group, around a wave's and a block's share and longer
     than one round of every CU, each item at a frame of its own (windows cut by
@@ -103,6 +105,22 @@ def test_work_lists(lanes, r, tr):
         got = _run(plan, -1, items, n, cnt)
         k = t * W * H + pix
         _compare(*got, {"theta": ref["theta"][k], "R": ref["R"][k]}, f"list of {n}, lanes {lanes}, r={r} tr={tr}")
+
+
+@pytest.mark.parametrize("r,tr,f16", [(1, 1, False), (2, 1, True), (7, 0, False), (8, 2, False), (9, 1, True),
+                                      (11, 1, False), (16, 0, False), (23, 1, False)])
+def test_small_dense_frames(r, tr, f16):
+    """Frames that would not fill the chip with tiles, by the default schedule:
+    whole columns, and leftover columns cut into 16, 5, 3, 2 and 1 parts."""
+    W, H, T = 23, 14, 3
+    tag = f"dense {W}x{H} r={r} tr={tr} f16={f16}"
+    say(tag)
+    E, feat = _clip(W, H, T, 4, 40 + r, f16)
+    p = B.Params(r=r, tr=tr, C=0.2)
+    y, fd = to_dev(E, feat)
+    got = _run(B.Plan([y], [fd], [p]), 1, None, W * H)
+    ref = oracle.regress_items(oracle_clip(E, feat), oracle.Params(r, tr, 0.2), W * H + np.arange(W * H), kappa=False)
+    _compare(*got, ref, tag)
 
 
 def test_work_list_longer_than_its_outputs():
