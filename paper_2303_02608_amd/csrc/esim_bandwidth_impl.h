@@ -68,11 +68,8 @@ bandwidth_tile_kernel(BandwidthArgs b) {
     for (int k = 0; k < b.K; ++k) {
       TileGeom<F, F16> geo;
       make_tile(geo, C, static_cast<int>(queue.group(q)), a.t, uni(b.scale[k] * b.scale[k]));
-      ColumnSums<F> c;
-      LaneSums<F> ls;
-      tile_window(geo, lds, c, ls);
       Gram<F, double> gm;
-      gram_of_lane<F, true>(c, ls, geo.vx_step, gm);
+      tile_gram(geo, lds, gm);
       if (geo.px < geo.W && geo.py < geo.H) {
         const int64_t pix = static_cast<int64_t>(geo.py) * geo.W + geo.px;
         solve_candidate<F>(b, C, k, pix, pix, gm, best);

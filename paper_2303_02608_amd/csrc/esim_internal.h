@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "esim.h"
 
@@ -89,15 +90,27 @@ __device__ __forceinline__ float ld_f32(__amdgpu_buffer_rsrc_t r, uint32_t voff,
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
 
-__device__ __forceinline__ float ld_f16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  const uint16_t h = __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
-  return static_cast<float>(__builtin_bit_cast(_Float16, h));
+// A feature as it is stored, in a register of its own.  Loads ahead hold it in this
+// form: converted where it is loaded, it would be waited for there (half precision,
+// lists of 18000 items, r = 10, F = 10, five frames: 315 us, 581 before; with
+// registers of 16 bits the dense tiles spilled).
+template <bool F16>
+using Feat = std::conditional_t<F16, uint32_t, float>;
+
+template <bool F16>
+__device__ __forceinline__ Feat<F16> ld_raw(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  if constexpr (F16) return __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
+  else return ld_f32(r, voff, soff);
+}
+
+__device__ __forceinline__ float feat_f32(float v) { return v; }
+__device__ __forceinline__ float feat_f32(uint32_t v) {
+  return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(v)));
 }
 
 template <bool F16>
 __device__ __forceinline__ float ld_feat(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  if constexpr (F16) return ld_f16(r, voff, soff);
-  else return ld_f32(r, voff, soff);
+  return feat_f32(ld_raw<F16>(r, voff, soff));
 }
 
 // Value of the first active lane, for values that every lane holds alike but that
@@ -167,12 +180,15 @@ __device__ __forceinline__ int item_frame(int64_t it) { return static_cast<int>(
 // columns, each wave with its own LDS.
 constexpr int tile_quads(int F) { return (F + 4) / 4; }                            // 16-byte units of F + 1 channels
 constexpr int tile_units(int F, int frames) { return (frames * tile_quads(F)) | 1; }   // of a pixel's record
-constexpr int kMaxTileFrames = 5;                                                  // walked at a time
+// Frames walked at a time (windows of more: one by one): five, where the rows
+// loaded ahead leave the registers for them (F = 12, three frames, 307200 pixels,
+// r = 7: spilling with three at a time 3.17 ms, one by one 2.17).
+constexpr int max_tile_frames(int F) { return F > 11 ? 1 : F > 10 ? 3 : 5; }
 // 16-byte units of a wave's LDS for windows of radius r (the ring of rows), and
 // of the record behind a block's last wave that the look-ahead of a row's walk
 // may read.
 constexpr int tile_last_units(int F, int tr) {
-  return tile_units(F, 2 * tr + 1 < kMaxTileFrames ? 2 * tr + 1 : kMaxTileFrames);
+  return tile_units(F, 2 * tr + 1 < max_tile_frames(F) ? 2 * tr + 1 : max_tile_frames(F));
 }
 constexpr int tile_wave_units(int F, int r, int tr, int lw) {
   return tile_last_units(F, tr) * ((1 << lw) + 2 * r) * (kWave >> lw);

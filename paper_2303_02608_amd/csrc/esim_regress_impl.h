@@ -403,11 +403,8 @@ regress_tile_kernel(RegressArgs a) {
     if (a.t >= C.T) continue;
     TileGeom<F, F16> geo;
     make_tile(geo, C, static_cast<int>(g - C.grp_off[5]), a.t);
-    ColumnSums<F> c;
-    LaneSums<F> ls;
-    tile_window(geo, lds, c, ls);
     Gram<F, double> gm;
-    gram_of_lane<F, true>(c, ls, geo.vx_step, gm);
+    tile_gram(geo, lds, gm);
     double M[P * (P + 1) / 2], th[P], rhs[P], anorm;
     const double iW = gram_solve<F, double>(gm, C, M, rhs, th, anorm);
     (void)anorm;

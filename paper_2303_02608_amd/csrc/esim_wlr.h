@@ -470,11 +470,12 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
     vf += skip * WES;
     vy += skip * W4;
   }
-  float ys[DEPTH][R], fs[DEPTH][R][F];
+  float ys[DEPTH][R];
+  Feat<F16> fs[DEPTH][R][F];
   auto load = [&](int d, int i) {
     ys[d][i] = ld_f32(g.ry, vy, soy + i * HW4);
 #pragma unroll
-    for (int f = 0; f < F; ++f) fs[d][i][f] = ld_feat<F16>(g.rf, vf, sof + i * FES + f * HES);
+    for (int f = 0; f < F; ++f) fs[d][i][f] = ld_raw<F16>(g.rf, vf, sof + i * FES + f * HES);
   };
   auto next_row = [&](int dy) {            // a step down where rows dy and dy + 1 are in the image
                                            // (a part's also in the window: what it reads counts)
@@ -492,7 +493,7 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
       double v[F], s0 = 0, s1 = 0;
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        v[f] = fma(static_cast<double>(fs[d][i][f]), g.sf[f], -g.xcs[f]);
+        v[f] = fma(static_cast<double>(feat_f32(fs[d][i][f])), g.sf[f], -g.xcs[f]);
         if (f & 1) s1 = fma(v[f], v[f], s1);
         else s0 = fma(v[f], v[f], s0);
       }
@@ -642,21 +643,19 @@ template <int F, bool F16, int R>
 struct RowLoads {
   static constexpr uint32_t ES = TileGeom<F, F16>::ES;
   static constexpr int NQ = tile_quads(F), U = tile_units(F, R);
-  float v[R][4 * NQ];
+  Feat<F16> v[R][F];
+  float y[R];
 
-  __device__ __forceinline__ void load(const TileGeom<F, F16>& g, int h, int y, int k0) {
+  __device__ __forceinline__ void load(const TileGeom<F, F16>& g, int h, int y0, int k0) {
     const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t row = static_cast<uint32_t>(min(max(y, 0), g.H - 1)) * static_cast<uint32_t>(g.W);
+    const uint32_t row = static_cast<uint32_t>(min(max(y0, 0), g.H - 1)) * static_cast<uint32_t>(g.W);
     const uint32_t x = static_cast<uint32_t>(min(max(g.x0 - g.r + lane + h * kWave, 0), g.W - 1));
 #pragma unroll
     for (int i = 0; i < R; ++i) {
 #pragma unroll
-      for (int c = 0; c < 4 * NQ; ++c) {
-        if (c < F)
-          v[i][c] = ld_feat<F16>(g.rf, x * ES, (static_cast<uint32_t>((k0 + i) * F + c) * g.HW + row) * ES);
-        else
-          v[i][c] = c == F ? ld_f32(g.ry, x * 4u, (static_cast<uint32_t>(k0 + i) * g.HW + row) * 4u) : 0.0f;
-      }
+      for (int c = 0; c < F; ++c)
+        v[i][c] = ld_raw<F16>(g.rf, x * ES, (static_cast<uint32_t>((k0 + i) * F + c) * g.HW + row) * ES);
+      y[i] = ld_f32(g.ry, x * 4u, (static_cast<uint32_t>(k0 + i) * g.HW + row) * 4u);
     }
   }
   __device__ __forceinline__ void store(const TileGeom<F, F16>& g, float4* lds, int h, int slot) const {
@@ -664,11 +663,16 @@ struct RowLoads {
     const int rowpx = (1 << g.lw) + 2 * g.r;
     if (p < rowpx) {
 #pragma unroll
-      for (int i = 0; i < R; ++i)
+      for (int i = 0; i < R; ++i) {
+        float ch[4 * NQ] = {};
+#pragma unroll
+        for (int c = 0; c < F; ++c) ch[c] = feat_f32(v[i][c]);
+        ch[F] = y[i];
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
           lds[(slot * rowpx + p) * U + i * NQ + q] =
-              make_float4(v[i][4 * q], v[i][4 * q + 1], v[i][4 * q + 2], v[i][4 * q + 3]);
+              make_float4(ch[4 * q], ch[4 * q + 1], ch[4 * q + 2], ch[4 * q + 3]);
+      }
     }
   }
 };
@@ -758,22 +762,6 @@ __device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* l
   }
 }
 
-// The whole window of the lane's pixel.
-template <int F, bool F16>
-__device__ __forceinline__ void tile_window(const TileGeom<F, F16>& g, float4* lds, ColumnSums<F>& c,
-                                            LaneSums<F>& ls) {
-  c.zero();
-  ls.zero();
-#pragma unroll 1
-  for (int k0 = 0; k0 < g.nt; k0 += kMaxTileFrames) {
-    const int n = g.nt - k0;
-    if (n == 3) tile_frames<F, F16, 3>(g, lds, k0, c, ls);
-    else if (n >= 5) tile_frames<F, F16, 5>(g, lds, k0, c, ls);
-    else if (n == 4) tile_frames<F, F16, 4>(g, lds, k0, c, ls);
-    else if (n == 2) tile_frames<F, F16, 2>(g, lds, k0, c, ls);
-    else tile_frames<F, F16, 1>(g, lds, k0, c, ls);
-  }
-}
 
 // Normal equations of one item, accumulated per lane.  Within a column pass
 // v_x is constant in a lane, so the entries with a v_x factor are not summed
@@ -966,6 +954,40 @@ __device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx
   for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
 }
 
+// The Gram of the window of the lane's pixel.  The sums of each count of frames
+// live and die in their own branch: kept across the branches, the register
+// allocator had fitted one of the five walks and spilled 28 to 56 registers at
+// every row of the others (640 x 480, F = 7, r = 7: one frame 339 -> 251 us, two 571
+// -> 409, three 644 -> 574; F = 8, two frames 2181 -> 573).  The rest, windows of more
+// frames than are walked at a time, keeps its sums over a loop of a single walk
+// for the same reason (seven frames, r = 5: 919 -> 916 us, F = 10 1811 -> 1726).
+template <int F, bool F16>
+__device__ __forceinline__ void tile_gram(const TileGeom<F, F16>& g, float4* lds, Gram<F, double>& G) {
+  auto whole = [&](auto frames) {
+    ColumnSums<F> c;
+    LaneSums<F> ls;
+    c.zero();
+    ls.zero();
+    tile_frames<F, F16, decltype(frames)::value>(g, lds, 0, c, ls);
+    gram_of_lane<F, true>(c, ls, g.vx_step, G);
+  };
+  constexpr int MAX = max_tile_frames(F);
+  if (MAX >= 3 && g.nt == 3) whole(std::integral_constant<int, MAX >= 3 ? 3 : 1>{});
+  else if (MAX >= 5 && g.nt == 5) whole(std::integral_constant<int, MAX >= 5 ? 5 : 1>{});
+  else if (MAX >= 4 && g.nt == 4) whole(std::integral_constant<int, MAX >= 4 ? 4 : 1>{});
+  else if (MAX >= 2 && g.nt == 2) whole(std::integral_constant<int, MAX >= 2 ? 2 : 1>{});
+  else if (MAX >= 2 && g.nt == 1) whole(std::integral_constant<int, 1>{});
+  else {
+    ColumnSums<F> c;
+    LaneSums<F> ls;
+    c.zero();
+    ls.zero();
+#pragma unroll 1
+    for (int k0 = 0; k0 < g.nt; ++k0) tile_frames<F, F16, 1>(g, lds, k0, c, ls);
+    gram_of_lane<F, true>(c, ls, g.vx_step, G);
+  }
+}
+
 // ---- lane sums that leave each total in one lane ---------------------------
 //
 // A step halves both the lanes that share a value and the values a lane holds:
@@ -1052,14 +1074,17 @@ __host__ __device__ constexpr int total_pos(int e) {
 // 30 and 500 / 46.  F = 10, r = 10, five frames: 1344 / 95, now 955 / 69.
 template <int F, int L, bool F16, bool SINGLE, class Fn>
 __device__ __forceinline__ void walk_parts(const WalkGeom<F, F16>& g, int j, Fn&& fn) {
+  // two rows ahead where they fit the registers (two waves per SIMD to F = 8, one
+  // above): at F = 8, r = 10, five frames, 18000 items spilled to 303 us, 232 with one
+  constexpr int DEPTH = F == 12 || (F == 8 && !SINGLE) ? 1 : 2;
   ColumnSums<F> c;
   Gram<F, double> got;
   if constexpr (SINGLE) {
     const int dx = j - g.r;
     c.zero();
-    if (g.nt == 3) walk_frames<F, F16, 3, 2>(g, dx, 0, c);
-    else if (g.nt == 2) walk_frames<F, F16, 2, 2>(g, dx, 0, c);
-    else walk_frames<F, F16, 1, 2>(g, dx, 0, c);
+    if (g.nt == 3) walk_frames<F, F16, 3, DEPTH>(g, dx, 0, c);
+    else if (g.nt == 2) walk_frames<F, F16, 2, DEPTH>(g, dx, 0, c);
+    else walk_frames<F, F16, 1, DEPTH>(g, dx, 0, c);
     gram_of_column(c, static_cast<double>(dx) * g.vx_step, g.vy_step, static_cast<double>(g.r + 1), got);
     fn(got, true);
   } else {
@@ -1075,9 +1100,9 @@ __device__ __forceinline__ void walk_parts(const WalkGeom<F, F16>& g, int j, Fn&
       for (int k0 = 0; k0 < g.nt; k0 += 3) {
         const int left = g.nt - k0;
         c.zero();
-        if (left >= 3) walk_frames<F, F16, 3, 2, true>(g, dx, k0, c, s0, n);
-        else if (left == 2) walk_frames<F, F16, 2, 2, true>(g, dx, k0, c, s0, n);
-        else walk_frames<F, F16, 1, 2, true>(g, dx, k0, c, s0, n);
+        if (left >= 3) walk_frames<F, F16, 3, DEPTH, true>(g, dx, k0, c, s0, n);
+        else if (left == 2) walk_frames<F, F16, 2, DEPTH, true>(g, dx, k0, c, s0, n);
+        else walk_frames<F, F16, 1, DEPTH, true>(g, dx, k0, c, s0, n);
         gram_of_column(c, static_cast<double>(dx) * g.vx_step, g.vy_step, static_cast<double>(s0 + n), got);
         fn(got, d0 == 0 && k0 == 0);
       }

@@ -48,6 +48,8 @@ def _run(plan, t, items, n, cnt=None):
     (48, 5, 5, 8, 5, 2, 1, False),      # four frames, three quads of channels
     (80, 6, 5, 10, 6, 2, 2, True),      # one wave per SIMD: rows loaded ahead
     (40, 21, 7, 3, 2, 3, 3, False),     # seven frames: groups of five and two
+    (33, 9, 5, 11, 3, 2, 2, False),     # eleven channels: three frames at a time, here one by one
+    (34, 8, 3, 12, 2, 1, 1, True),      # twelve: always one
     (30, 34, 2, 7, 33, 0, 1, False),    # rows wider than two turns of a wave: no tiles
 ])
 def test_dense_tiles(W, H, T, F, r, tr, t, f16):
