@@ -13,13 +13,13 @@
 //                      block 0 records the event base.
 //   chunk_kernel       totals of chunks of kChunkBlocks block counts (only for
 //                      grids above kDirectPrefixBlocks blocks).
-//   scatter_kernel     each block's offset: the sum of the counts of the
-//                      blocks before it, read directly (or as chunk totals plus
-//                      the counts inside its chunk), with no inter-block
+//   scatter_kernel     one wave per flag block; its offset: the sum of the counts
+//                      of the blocks before it, read directly (or as chunk totals
+//                      plus the counts inside its chunk), with no inter-block
 //                      signalling; rank = offset + popcounts of
 //                      the ballots below the lane; writes the work list
-//                      (threshold) and/or the events; the last block writes
-//                      the count and advances the event count.
+//                      (threshold) and/or the events; the last block's wave
+//                      writes the count and advances the event count.
 //   list_events_kernel events of the work-list items and the state update
 //                      (Sec. 2.2: the model at the last event is kept until the
 //                      pixel's next event); advance_kernel then advances the
@@ -65,21 +65,54 @@ __device__ __forceinline__ int crossings(double d, double C) {
   return n >= 1.0 ? static_cast<int>(fmin(n, kMaxCrossings)) : 0;
 }
 
-// Exclusive prefix of one int per thread of a kBlock-thread block.
-__device__ int block_exclusive_scan(int v) {
-  __shared__ int wsum[kWavesPerBlock];
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+// Exclusive prefix of one int per lane of a wave.
+__device__ __forceinline__ int wave_exclusive_scan(int v) {
+  const int lane = threadIdx.x & (kWave - 1);
   int x = v;
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
     const int y = __shfl_up(x, o);
     if (lane >= o) x += y;
   }
-  if (lane == kWave - 1) wsum[w] = x;
-  __syncthreads();
-  int before = 0;
-  for (int k = 0; k < w; ++k) before += wsum[k];
-  return before + x - v;
+  return x - v;
+}
+
+// The threshold's change of pixel p at frame t over F <= N channels, with the loads
+// of all of them in flight together (channels past the last one load it again):
+// taken channel by channel, with the descriptor read again for each, they were F
+// trips to memory in a row (flag_kernel, F = 7: 64 x 64 pixels 4.9 -> 3.3 us; 640 x
+// 480, where the 26 MB of state and features bound it, 6.8 -> 6.6).
+template <bool F16, int N>
+__device__ __forceinline__ double model_change(const ClipDev& C, int F, int t, uint32_t p) {
+  constexpr uint32_t ES = F16 ? 2u : 4u;
+  const uint32_t HW = static_cast<uint32_t>(uni(static_cast<int>(C.HW)));
+  const uint64_t all = static_cast<uint64_t>(F) * HW;
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(uni(C.st_beta), all * 4u), rx = make_rsrc(uni(C.st_xref), all * 4u);
+  const __amdgpu_buffer_rsrc_t rf =
+      make_rsrc(static_cast<const char*>(uni(C.feat)) + static_cast<uint64_t>(t) * all * ES, all * ES);
+  float bf[N], xf[N];
+  Feat<F16> ff[N];
+#pragma unroll
+  for (int f = 0; f < N; ++f) {
+    const uint32_t c = static_cast<uint32_t>(min(f, F - 1)) * HW;
+    bf[f] = ld_f32(rb, p * 4u, c * 4u);
+    xf[f] = ld_f32(rx, p * 4u, c * 4u);
+    ff[f] = ld_raw<F16>(rf, p * ES, c * ES);
+  }
+  double d = 0.0;
+#pragma unroll
+  for (int f = 0; f < N; ++f)
+    if (f < F)
+      d = fma(static_cast<double>(bf[f]), static_cast<double>(feat_f32(ff[f])) - static_cast<double>(xf[f]), d);
+  return d;
+}
+
+template <bool F16>
+__device__ __forceinline__ double model_change(const ClipDev& C, int t, uint32_t p) {
+  const int F = uni(C.F);
+  if (F <= 4) return model_change<F16, 4>(C, F, t, p);
+  if (F <= 8) return model_change<F16, 8>(C, F, t, p);
+  return model_change<F16, ESIM_MAX_F>(C, F, t, p);
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -97,12 +130,8 @@ flag_kernel(const ClipDev* __restrict__ clips, int nclips, int t, int mode, floa
     float val = __builtin_nanf("");
     if (mode == kFlagThreshold) {
       if (t >= 1) {
-        double d = 0.0;
-        for (int f = 0; f < C.F; ++f) {
-          const double bf = C.st_beta[f * C.HW + p];
-          const double xf = C.st_xref[f * C.HW + p];
-          d = fma(bf, static_cast<double>(feat_value(C, t, f, p)) - xf, d);
-        }
+        const uint32_t q = static_cast<uint32_t>(p);
+        const double d = C.feat_f16 ? model_change<true>(C, t, q) : model_change<false>(C, t, q);
         flag = d * d >= C.C * C.C;
         pos = d > 0.0;
         val = static_cast<float>(d);
@@ -157,12 +186,21 @@ flag_kernel(const ClipDev* __restrict__ clips, int nclips, int t, int mode, floa
   }
 }
 
+constexpr int kSumLoads = 4;
+
 // Sum of a[lo, hi) by one block of kBlock threads.
 template <class V>
 __device__ int64_t block_sum(const V* __restrict__ a, int64_t lo, int64_t hi) {
   __shared__ int64_t red[kWavesPerBlock];
   int64_t s = 0;
-  for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) s += a[k];
+  for (int64_t k = lo + threadIdx.x; k < hi; k += kSumLoads * kBlock) {
+#pragma unroll
+    for (int u = 0; u < kSumLoads; ++u) {      // in flight together
+      const int64_t e = k + u * kBlock;
+      const int64_t v = a[min(e, hi - 1)];
+      s += e < hi ? v : 0;
+    }
+  }
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
   __syncthreads();
@@ -190,17 +228,46 @@ __global__ void __launch_bounds__(kBlock) chunk_kernel(Workspace ws, int64_t nbl
   if (threadIdx.x == 0) ws.chunk[c] = t;
 }
 
+// A wave takes a flag block, so that the sum of the counts before it is read once
+// for kWavesPerBlock of them, and its pixels' loads are in flight meanwhile.
+// Bound by latency (a frame without events, 1280 x 720: 4.6 us) and, where every
+// pixel has events, by their writes.
 __global__ void __launch_bounds__(kBlock)
-scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int t, int mode, Workspace ws, int chunked,
-               const float* __restrict__ alpha, int64_t* __restrict__ worklist, int32_t* __restrict__ count,
-               EventsDev ev, int64_t seg_b) {
+scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int t, int mode, Workspace ws,
+               int chunked, const float* __restrict__ alpha, int64_t* __restrict__ worklist,
+               int32_t* __restrict__ count, EventsDev ev, int64_t seg_b) {
   constexpr int64_t kLow = 0xFFFFFFFFll;
-  const int64_t b = blockIdx.x;
-  const int64_t packed = counts_before(ws, b, chunked != 0);
-  const int64_t off0 = packed & kLow;         // flagged pixels before this block
+  constexpr int NW = kWavesPerBlock;          // waves of the block and 64-pixel words of a flag block
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = uni(static_cast<int>(threadIdx.x) / kWave);
+  const int64_t b0 = static_cast<int64_t>(blockIdx.x) * NW;
+  const int64_t b = b0 + w;                   // this wave's flag block
+  const bool mine = b < nblk;
+  const int cl = mine ? block_clip(clips, nclips, b) : 0;
+  const ClipDev& C = clips[cl];
+  const int64_t p0 = (b - C.blk_off) * kBlock + lane;       // its first word's pixel
+  const bool multi = C.multi && mode != kFlagThreshold;     // uniform: one clip per flag block
+  float L[NW], Lref[NW], Llast[NW];
+  uint64_t m[NW];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int64_t p = p0 + i * kWave;
+    L[i] = Lref[i] = Llast[i] = 0.0f;
+    m[i] = 0;
+    if (mine && multi && p < C.HW && t >= 1 && t < C.T) {
+      L[i] = mode == kFlagExhaustive ? alpha[C.pix_off + p] : C.y[static_cast<int64_t>(t) * C.HW + p];
+      Lref[i] = C.st_alpha[p];
+      Llast[i] = C.st_last[p];
+    }
+    if (mine && !multi) m[i] = ws.flags[b * NW + i];
+  }
+  int64_t packed = counts_before(ws, b0, chunked != 0);
+  if (!mine) return;
+  for (int k = 0; k < w; ++k) packed += ws.bcount[b0 + k];
+  const int64_t off0 = packed & kLow;         // flagged pixels before this flag block
   const int64_t offb0 = packed >> 32;         // of them in second-segment clips (split only)
   const int64_t base = ws.misc[0];
-  if (b == gridDim.x - 1 && threadIdx.x == 0) {
+  if (b == nblk - 1 && lane == 0) {
     const int64_t tp = packed + ws.bcount[b];
     const int64_t total = tp & kLow;
     if (count) {
@@ -214,69 +281,111 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int t, int mode, W
     }
     if (ev.count) *ev.count = base + total;
   }
-  const int cl = block_clip(clips, nclips, b);
-  const ClipDev& C = clips[cl];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int w = threadIdx.x / kWave;
-  if (C.multi && mode != kFlagThreshold) {   // uniform: one clip per block
+  if (multi) {
     // every-crossing rule: n events per pixel at the interpolated times the
-    // levels L_ref + k p C are passed; then L_ref += n p C and L_last = L
-    const int64_t p = (b - C.blk_off) * kBlock + threadIdx.x;
-    const bool in = p < C.HW && t >= 1 && t < C.T;
-    float L = 0.0f, Lref = 0.0f, Llast = 0.0f;
-    int n = 0;
-    if (in) {
-      L = mode == kFlagExhaustive ? alpha[C.pix_off + p] : C.y[static_cast<int64_t>(t) * C.HW + p];
-      Lref = C.st_alpha[p];
-      Llast = C.st_last[p];
-      n = crossings(static_cast<double>(L) - static_cast<double>(Lref), C.C);
-    }
-    const int64_t off = off0 + block_exclusive_scan(n);
-    if (n > 0) {
-      const double d = static_cast<double>(L) - static_cast<double>(Lref);
-      const int pol = d > 0.0 ? 1 : -1;
-      const double step = pol * C.C;               // exact: C times +-1
-      const double den = static_cast<double>(L) - static_cast<double>(Llast);
-      for (int k = 1; k <= n; ++k) {
-        const int64_t e = base + off + (k - 1);
-        if (e >= ev.capacity) break;
-        const double level = static_cast<double>(Lref) + static_cast<double>(k) * step;
-        ev.x[e] = static_cast<int32_t>(p % C.W);
-        ev.y[e] = static_cast<int32_t>(p / C.W);
-        ev.t[e] = t;
-        ev.p[e] = static_cast<int8_t>(pol);
-        if (ev.clip) ev.clip[e] = cl;
-        if (ev.ts) ev.ts[e] = static_cast<float>(((t - 1) + (level - static_cast<double>(Llast)) / den) * C.dt);
-      }
+    // levels L_ref + k p C are passed; then L_ref += n p C and L_last = L.  The
+    // events of the wave's pixels go round its lanes and not each pixel's to its
+    // own: counts differ between neighbours, and a wave waited for its largest.
+    // At 1.4 events a pixel (1280 x 720, 44 MB of reads and writes a frame, 9 us at
+    // the copy rate) 15.6 us, each pixel's events in its own lane 22.4 (the four
+    // waves of a block sharing theirs 18.7; half as many instructions an event, no
+    // less than 15.6: the writes bound it).
+    __shared__ int first[NW][kBlock];         // events of the wave before each pixel's
+    __shared__ float3 level_of[NW][kBlock];   // L, L_ref, L_last
+    const double thr = uni(C.C), dt = uni(C.dt);
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int64_t p = p0 + i * kWave;
+      const bool in = p < C.HW && t >= 1 && t < C.T;
+      const double d = static_cast<double>(L[i]) - static_cast<double>(Lref[i]);
+      const int n = in ? crossings(d, thr) : 0;
+      if (in) C.st_last[p] = L[i];
       // the reference level is kept in FP32 like the rest of the state
-      C.st_alpha[p] = static_cast<float>(static_cast<double>(Lref) + static_cast<double>(n) * step);
+      if (n > 0)
+        C.st_alpha[p] =
+            static_cast<float>(static_cast<double>(Lref[i]) + static_cast<double>(n) * (d > 0.0 ? thr : -thr));
+      const int k = i * kWave + lane;
+      const int before = __ballot(n > 0) != 0 ? wave_exclusive_scan(n) : 0;
+      first[w][k] = total + before;
+      level_of[w][k] = make_float3(L[i], Lref[i], Llast[i]);
+      total += __builtin_amdgcn_readlane(before + n, kWave - 1);
     }
-    if (in) C.st_last[p] = L;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t W = static_cast<uint32_t>(uni(static_cast<int>(C.W)));
+    const uint32_t pw = static_cast<uint32_t>(uni(static_cast<int>((b - C.blk_off) * kBlock)));
+    const uint32_t yw = pw / W, xw = pw - yw * W;               // of the wave's first pixel
+    const int64_t e0 = base + off0;
+    int32_t* const ex = ev.x + e0;
+    int32_t* const ey = ev.y + e0;
+    int32_t* const et = ev.t + e0;
+    int8_t* const ep = ev.p + e0;
+    const int64_t room = max(ev.capacity - e0, static_cast<int64_t>(0));
+    const uint32_t end = static_cast<uint32_t>(min(static_cast<int64_t>(total), room));
+    constexpr int kAhead = 2;                 // searches at a time
+    for (uint32_t i0 = lane; i0 < end; i0 += kAhead * kWave) {
+      int k[kAhead] = {};                     // the last pixel with first <= i
+#pragma unroll
+      for (int o = kBlock / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (first[w][k[u] + o] <= static_cast<int>(i0 + u * kWave)) k[u] += o;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const uint32_t i = i0 + u * kWave;
+        if (i >= end) break;
+        const float3 l = level_of[w][k[u]];
+        const bool up = l.x > l.y;
+        const double den = static_cast<double>(l.x) - static_cast<double>(l.z);
+        const double nth = static_cast<double>(static_cast<int>(i) - first[w][k[u]] + 1);
+        const double level = static_cast<double>(l.y) + nth * (up ? thr : -thr);
+        uint32_t x = xw + k[u], y = yw;
+        if (W >= kBlock) {                    // at most one row further
+          if (x >= W) {
+            x -= W;
+            ++y;
+          }
+        } else {
+          y += x / W;
+          x %= W;
+        }
+        ex[i] = static_cast<int32_t>(x);
+        ey[i] = static_cast<int32_t>(y);
+        et[i] = t;
+        ep[i] = up ? 1 : -1;
+        if (ev.clip) ev.clip[e0 + i] = cl;
+        if (ev.ts) ev.ts[e0 + i] = static_cast<float>(((t - 1) + (level - static_cast<double>(l.z)) / den) * dt);
+      }
+    }
     return;
   }
-  const uint64_t m = ws.flags[b * kWavesPerBlock + w];
-  if (!((m >> lane) & 1ull)) return;
-  const int64_t p = (b - C.blk_off) * kBlock + threadIdx.x;
-  int64_t rank = 0;                           // among the block's flagged pixels
-  for (int k = 0; k < w; ++k) rank += __popcll(ws.flags[b * kWavesPerBlock + k]);
-  rank += __popcll(m & ((1ull << lane) - 1ull));
-  const int64_t off = off0 + rank;
-  if (mode == kFlagThreshold && worklist) {
-    // a block lies in one clip, so its items all go to the same segment
-    const int64_t pos = seg_b < 0 ? off : C.list_class ? seg_b + offb0 + rank : off0 - offb0 + rank;
-    worklist[pos] = (static_cast<int64_t>(cl) << 32) | p;
-  }
-  if (ev.x) {
-    const int64_t e = base + off;
-    if (e < ev.capacity) {
-      const bool pos = (ws.pol[b * kWavesPerBlock + w] >> lane) & 1ull;
-      ev.x[e] = static_cast<int32_t>(p % C.W);
-      ev.y[e] = static_cast<int32_t>(p / C.W);
-      ev.t[e] = t;
-      ev.p[e] = pos ? 1 : -1;
-      if (ev.clip) ev.clip[e] = cl;
-      if (ev.ts) ev.ts[e] = static_cast<float>(t * C.dt);
+  int64_t rank0 = 0;                          // flagged pixels in the words before
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    if ((m[i] >> lane) & 1ull) {
+      const int64_t p = p0 + i * kWave;
+      const int64_t rank = rank0 + __popcll(m[i] & ((1ull << lane) - 1ull));
+      const int64_t off = off0 + rank;
+      if (mode == kFlagThreshold && worklist) {
+        // a flag block lies in one clip, so its items all go to the same segment
+        const int64_t pos = seg_b < 0 ? off : C.list_class ? seg_b + offb0 + rank : off0 - offb0 + rank;
+        worklist[pos] = (static_cast<int64_t>(cl) << 32) | p;
+      }
+      if (ev.x) {
+        const int64_t e = base + off;
+        if (e < ev.capacity) {
+          const bool pos = (ws.pol[b * NW + i] >> lane) & 1ull;
+          ev.x[e] = static_cast<int32_t>(static_cast<uint32_t>(p) % static_cast<uint32_t>(C.W));
+          ev.y[e] = static_cast<int32_t>(static_cast<uint32_t>(p) / static_cast<uint32_t>(C.W));
+          ev.t[e] = t;
+          ev.p[e] = pos ? 1 : -1;
+          if (ev.clip) ev.clip[e] = cl;
+          if (ev.ts) ev.ts[e] = static_cast<float>(t * C.dt);
+        }
+      }
     }
+    rank0 += __popcll(m[i]);
   }
 }
 
@@ -418,8 +527,8 @@ hipError_t launch_scatter(const ClipDev* clips, int nclips, int64_t nblk, int t,
     hipLaunchKernelGGL(chunk_kernel, dim3(static_cast<unsigned>((nblk + kChunkBlocks - 1) / kChunkBlocks)),
                        dim3(kBlock), 0, s, ws, nblk);
   EventsDev none{};
-  hipLaunchKernelGGL(scatter_kernel, dim3(static_cast<unsigned>(nblk)), dim3(kBlock), 0, s, clips, nclips,
-                     t, mode, ws, chunked, alpha, wl, wl ? count : nullptr, ev ? *ev : none, seg_b);
+  hipLaunchKernelGGL(scatter_kernel, dim3(static_cast<unsigned>((nblk + kWavesPerBlock - 1) / kWavesPerBlock)),
+                     dim3(kBlock), 0, s, clips, nclips, nblk, t, mode, ws, chunked, alpha, wl, wl ? count : nullptr, ev ? *ev : none, seg_b);
   return hipGetLastError();
 }
 
