@@ -974,11 +974,12 @@ def main():
     ld, ll, bpc = sched
     roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_ALU_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_ALU_TFLOPS, 4),
-            "traffic": traffic, "kernel": f"regress_kernel<F={F},L={ll},f32> (work-list launches)",
+            "traffic": traffic, "kernel": f"regress_list_kernel<F={F},L={ll},f32> (work-list launches)",
             "launches": int(list_ms.size), "avg_launch_ms": round(float(list_ms.mean()), 4),
             "flop_per_launch": float(fl_list / list_ms.size),
             "regress_share_of_step": round(float(list_ms.sum() + dense_ms.sum()) / ms_thr, 3),
-            "dense_frame0": {"kernel": f"regress_kernel<F={F},L={ld},f32>",
+            "dense_frame0": {"kernel": f"regress_tile_kernel<F={F},f32>" if ld == 1
+                             else f"regress_list_kernel<F={F},L={ld},f32>",
                              "ms": round(float(dense_ms.sum()), 4),
                              "tflops": round(fl_dense / (dense_ms.sum() * 1e-3) / 1e12, 3)}}
     log(f"regress list launches: {list_ms.size}, avg {list_ms.mean():.4f} ms, {achieved:.2f} TFLOP/s; "

@@ -199,8 +199,11 @@ int64_t esim_plan_pixel_offset(esim_plan plan, int32_t c);
 /* Schedule of the regression kernel (set by the autotuner, or by hand): the
  * lanes that share one regression item in dense launches and in work-list
  * launches (1, 2, 4, 8 or 16; more lanes = more, shorter wave tasks for sparse
- * lists) and the persistent blocks per CU (1..64).  Defaults 1, 16, 4 (4, 16, 4 with
- * ESIM_GRAM_F32C).
+ * lists) and the persistent blocks per CU (1..64; of the instances of 1 and 2
+ * lanes that read windows from memory and of ESIM_GRAM_F32C, the others take one
+ * block per CU).  Defaults 1, 16, 4 (4, 16, 4 with ESIM_GRAM_F32C); without a
+ * schedule set, frames too small to fill the device with one lane per pixel take
+ * 16 lanes per item.
  * Errors: E_UNSUPPORTED (lanes not compiled), E_INVAL. */
 int esim_plan_set_schedule(esim_plan plan, int32_t lanes_dense, int32_t lanes_list,
                            int32_t blocks_per_cu);
@@ -357,8 +360,8 @@ int esim_log_variance(const float* E, const float* var, int32_t spp, float* vy, 
  * beta[d * n_out + i] over D (nullable); hsel[i] the chosen h (nullable);
  * sure[i] its SURE (nullable).  vy: [T][H][W], the variance of y
  * (esim_log_variance).  Single-clip plans, FP64 Gram; K window passes per
- * item (one lane per pixel for every pixel of the frame, 16 lanes per item for
- * work lists).
+ * item (one lane per pixel for every pixel of a frame that fills the device, 16
+ * lanes per item for smaller frames and work lists).
  * Errors: E_INVAL (K outside 1..8, h <= 0, null pointers, n_out),
  * E_UNSUPPORTED (several clips). */
 int esim_wlr_regress_bandwidth(esim_plan plan, int32_t t, const int64_t* worklist, const int32_t* count,

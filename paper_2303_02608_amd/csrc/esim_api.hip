@@ -39,7 +39,7 @@ struct esim_plan_s {
   int64_t* step_wl = nullptr;     // [wl_capacity]
   int32_t* step_count = nullptr;  // [4] (two segments of a split work list)
   // esim_step's split work list: clips whose windows fit 16 columns (the
-  // one-pass list instance) in the first segment, wider ones from split_seg
+  // list instance of uncut columns) in the first segment, wider ones from split_seg
   // on (-1: one segment)
   int64_t split_seg = -1;
   float* step_alpha = nullptr;    // [npix]
@@ -661,7 +661,7 @@ int esim_step(esim_plan pl, int32_t t, int32_t mode, float* dl, esim_events_buf*
     if (mode == ESIM_THRESHOLDED) {
       // Mixed window widths: the compaction writes the narrow clips' items and
       // the wide ones' into two segments, and each gets its own launch, so the
-      // narrow ones run the one-pass list instance (one column per lane)
+      // narrow ones run the list instance of uncut columns (one column per lane)
       // instead of the general one, each launch spread over every XCD.
       const bool split = pl->split_seg >= 0 && pl->thr == ESIM_THRESHOLD_CLOSED && pl->lanes_list == 16 &&
                          pl->host[0].precision == ESIM_GRAM_F64;

@@ -252,7 +252,6 @@ const RegressTable* regress_table(int F);   // null outside 1..ESIM_MAX_F
 // blocks_per_cu a CU, that stride over them.
 hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int waves_per_simd, bool queue,
                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
-int regress_supported_lanes(int F);
 bool regress_supports(int F, int lanes, int precision);
 
 struct BackwardArgs {

@@ -55,8 +55,6 @@ KernelFn pick_c32(int F, int lanes, bool f16) {
 
 }  // namespace
 
-int regress_supported_lanes(int F) { return (F >= 1 && F <= ESIM_MAX_F) ? 0x1 | 0x2 | 0x4 | 0x8 | 0x10 : 0; }
-
 bool regress_supports(int F, int lanes, int precision) {
   if (precision == ESIM_GRAM_F32C) return pick_c32(F, lanes, false) != nullptr;
   return pick(F, lanes, false) != nullptr;

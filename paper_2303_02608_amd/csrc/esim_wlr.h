@@ -1,16 +1,20 @@
-// Window geometry and the streamed window loop of one weighted local
-// regression (Sec. 2.1, eqs. 4-5), shared by the forward and adjoint kernels.
+// Window geometry, window walks, lane sums and solve of one weighted local
+// regression (Sec. 2.1, eqs. 4-5), shared by the forward, bandwidth and adjoint
+// kernels.
 //
 // Regressors are kept in bandwidth-scaled units v_j = u_j / (h b_j): the
 // weight exponent is then sum_j v_j^2 (eq. 5 with a Gaussian fall-off) and
 // the fit in v equals the fit in u with beta_j = theta_j / (h b_j) and the
 // ridge scaled to lambda / (h b_j)^2.
 //
-// The L lanes of an item split the window columns (lane j takes dx = -r + j,
-// -r + j + L, ...); for one column pass v_x is constant in the lane.  The rows
-// (dt, dy) of a column are software-pipelined in registers (window_loop): the
-// loads of a row are issued two rows ahead of its use.  Rows outside the image
-// (or past the last row) read the valid centre pixel and get weight 0.
+// The FP64 Gram's walks: walk_frames (columns of a lane, read from memory, for
+// lists and small frames) and tile_frames (a pixel per lane, windows from LDS, for
+// whole frames).  window_loop is the older loop of the compensated FP32 Gram, whose
+// rounding depends on its order, and of the explicit threshold: the L lanes of an
+// item split the window columns (lane j takes dx = -r + j, -r + j + L, ...), and
+// the rows (dt, dy) of a column are software-pipelined in registers, loaded two
+// rows ahead of their use.  Rows outside the image (or past the last row) read the
+// valid centre pixel and get weight 0.
 #pragma once
 
 #include <type_traits>
@@ -209,86 +213,6 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
     if constexpr (kPeel) {
       if (q < nrows) use(wA);     // odd row count: the last row alone
     }
-    pass_end(vx);
-  }
-}
-
-// The window of one item whose window lies entirely inside the image and the
-// clip (the FULL case of window_loop), with a deeper load pipeline: a ring of
-// R rows in registers.  Each step weighs and accumulates the oldest row and
-// issues the loads of the row R ahead into its slot, so every load has R - 1
-// rows of work to arrive (the window rows of scattered work-list items often
-// miss the L2).  Same calls and order of samples as window_loop; sample()
-// receives dt = dy = 0 (unused by its callers).
-template <int F, int L, bool F16, int R, class PassBegin, class Sample, class PassEnd>
-__device__ __forceinline__ void window_loop_ring(const ItemGeom<F, F16, double>& g, int j,
-                                                 PassBegin&& pass_begin, Sample&& sample,
-                                                 PassEnd&& pass_end) {
-  constexpr uint32_t ES = ItemGeom<F, F16, double>::ES;
-  constexpr double K = kHalfLog2e;
-  const int r = g.r;
-  const int span = 2 * r + 1;
-  const int nt = 2 * g.tr + 1;
-  const int nrows = nt * span;
-  const int npass = (span + L - 1) / L;
-  const uint32_t WES = static_cast<uint32_t>(g.W) * ES, W4 = static_cast<uint32_t>(g.W) * 4u;
-  const uint32_t FES = static_cast<uint32_t>(F) * g.HW * ES, HW4 = g.HW * 4u;
-  for (int k = 0; k < npass; ++k) {
-    const int dx = -r + j + k * L;
-    const int col = g.px + min(dx, r);        // an idle column reads the last one (weight 0)
-    const bool col_ok = g.active && dx <= r;
-    const double vx = static_cast<double>(dx) * g.vx_step;
-    const double kx = K * vx * vx;
-    pass_begin(vx);
-    const uint32_t vf_base = (static_cast<uint32_t>(g.fc - g.tr) * F * g.HW +
-                              static_cast<uint32_t>((g.py - r) * g.W + col)) * ES;
-    const uint32_t vy_base = (static_cast<uint32_t>(g.fc - g.tr) * g.HW +
-                              static_cast<uint32_t>((g.py - r) * g.W + col)) * 4u;
-    int ldt = 0, ldy = 0;                     // next row to load (uniform)
-    auto load_next = [&](float& yv, float (&fv)[F]) {
-      // rows past the window repeat the last row; they are never consumed
-      const bool in = ldt < nt;
-      const uint32_t lt = static_cast<uint32_t>(in ? ldt : nt - 1);
-      const uint32_t ly = static_cast<uint32_t>(in ? ldy : span - 1);
-      yv = ld_f32(g.ry, vy_base, lt * HW4 + ly * W4);
-#pragma unroll
-      for (int f = 0; f < F; ++f) fv[f] = ld_feat<F16>(g.rf, vf_base, lt * FES + ly * WES + f * g.HW * ES);
-      if (++ldy == span) {
-        ldy = 0;
-        ++ldt;
-      }
-    };
-    int cdy = -r;                             // next row to consume (uniform)
-    auto consume = [&](float yv, const float (&fv)[F]) {
-      const double vy = static_cast<double>(cdy) * g.vy_step;
-      if (++cdy > r) cdy = -r;
-      double v[F], s0 = 0, s1 = 0;
-#pragma unroll
-      for (int f = 0; f < F; ++f) {
-        v[f] = fma(static_cast<double>(fv[f]), g.sf[2 + f], -g.xcs[f]);
-        if (f & 1) s1 = fma(v[f], v[f], s1);
-        else s0 = fma(v[f], v[f], s0);
-      }
-      const double arg = fma(s0 + s1, K, fma(K * vy, vy, kx));
-      const float e = __builtin_amdgcn_exp2f(static_cast<float>(arg));
-      sample(static_cast<double>(col_ok ? e : 0.0f), static_cast<double>(yv), v, vy, dx, 0, 0, col_ok);
-    };
-    float ys[R], fs[R][F];
-#pragma unroll
-    for (int i = 0; i < R; ++i) load_next(ys[i], fs[i]);
-    int q = 0;
-#pragma unroll 1
-    for (; q + R <= nrows; q += R) {
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        consume(ys[i], fs[i]);
-        load_next(ys[i], fs[i]);
-      }
-    }
-    // the last nrows - q rows sit in slots 0 .. nrows - q - 1
-#pragma unroll
-    for (int i = 0; i + 1 < R; ++i)
-      if (q + i < nrows) consume(ys[i], fs[i]);
     pass_end(vx);
   }
 }
@@ -763,88 +687,14 @@ __device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* l
 }
 
 
-// Normal equations of one item, accumulated per lane.  Within a column pass
-// v_x is constant in a lane, so the entries with a v_x factor are not summed
-// per sample: they are v_x times sums of the first-row entries (formed once per
-// item by the one-pass form, once per pass by the pass-snapshot form).
+// Normal equations of one item (or a lane's share of them).
 template <int F, class Real = double>
 struct Gram {
   static constexpr int NA = F * (F + 1) / 2;
   Real SW, A0y, g0, A0f[F];
   Real A0x, Axx, Axy, gx, Axf[F];
   Real Ayy, gy, Syy, Ayf[F], gf[F], Aff[NA];
-  Real qW, qY, qG, qF[F];                 // first-row totals at the pass start
 
-  // One-pass form (every lane owns a single window column): the column sums
-  // are the totals, and the entries with a v_x factor are formed once after
-  // the window loop, so they are not live during it.
-  __device__ __forceinline__ void zero_onepass() {
-    SW = A0y = g0 = Ayy = gy = Syy = 0;
-#pragma unroll
-    for (int f = 0; f < F; ++f) A0f[f] = Ayf[f] = gf[f] = 0;
-#pragma unroll
-    for (int k = 0; k < NA; ++k) Aff[k] = 0;
-  }
-  __device__ __forceinline__ void add_onepass(Real w, Real yd, const Real (&v)[F], Real vy) {
-    const Real wy = w * yd;
-    const Real wvy = w * vy;
-    SW += w;
-    A0y += wvy;
-    g0 += wy;
-    Ayy = fma(wvy, vy, Ayy);
-    gy = fma(wy, vy, gy);
-    Syy = fma(wy, yd, Syy);
-    int qq = 0;
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-      const Real wz = w * v[f];
-      A0f[f] += wz;
-      Ayf[f] = fma(wvy, v[f], Ayf[f]);
-      gf[f] = fma(wz, yd, gf[f]);
-#pragma unroll
-      for (int e = f; e < F; ++e) {
-        Aff[qq] = fma(wz, v[e], Aff[qq]);
-        ++qq;
-      }
-    }
-  }
-  __device__ __forceinline__ void fold_onepass(Real vx) {
-    A0x = vx * SW;
-    Axx = vx * vx * SW;
-    Axy = vx * A0y;
-    gx = vx * g0;
-#pragma unroll
-    for (int f = 0; f < F; ++f) Axf[f] = vx * A0f[f];
-  }
-  // Pass-snapshot form: the window loop accumulates as the one-pass form; at
-  // each pass start the first-row totals (W, v_y, y and feature sums) are
-  // copied, and at its end the entries with a v_x factor take v_x times the
-  // pass's increment of them.  The snapshot and the v_x entries are only
-  // touched once per pass, so the loop's live accumulators are the one-pass
-  // ones.  (The increment is a difference of two FP64 totals of at most
-  // 2r + 1 passes: its rounding is of the order of the totals' own.)
-  __device__ __forceinline__ void zero_snap() {
-    zero_onepass();
-    A0x = Axx = Axy = gx = 0;
-#pragma unroll
-    for (int f = 0; f < F; ++f) Axf[f] = 0;
-  }
-  __device__ __forceinline__ void pass_begin_snap() {
-    qW = SW;
-    qY = A0y;
-    qG = g0;
-#pragma unroll
-    for (int f = 0; f < F; ++f) qF[f] = A0f[f];
-  }
-  __device__ __forceinline__ void pass_end_snap(Real vx) {
-    const Real dW = SW - qW;
-    A0x = fma(vx, dW, A0x);
-    Axx = fma(vx * vx, dW, Axx);
-    Axy = fma(vx, A0y - qY, Axy);
-    gx = fma(vx, g0 - qG, gx);
-#pragma unroll
-    for (int f = 0; f < F; ++f) Axf[f] = fma(vx, A0f[f] - qF[f], Axf[f]);
-  }
   // Calls fn on every total, in a fixed order.
   template <class Fn>
   __device__ __forceinline__ void each(Fn&& fn) {
