@@ -77,6 +77,12 @@ __device__ __forceinline__ int wave_exclusive_scan(int v) {
   return x - v;
 }
 
+// A uniform pointer to device memory: loads through it need not tell it from LDS.
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(1))) T* in_memory(const T* p) {
+  return reinterpret_cast<const __attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(uni(p)));
+}
+
 // The threshold's change of pixel p at frame t over F <= N channels, with the loads
 // of all of them in flight together (channels past the last one load it again):
 // taken channel by channel, with the descriptor read again for each, they were F
@@ -84,20 +90,19 @@ __device__ __forceinline__ int wave_exclusive_scan(int v) {
 // 480, where the 26 MB of state and features bound it, 6.8 -> 6.6).
 template <bool F16, int N>
 __device__ __forceinline__ double model_change(const ClipDev& C, int F, int t, uint32_t p) {
-  constexpr uint32_t ES = F16 ? 2u : 4u;
   const uint32_t HW = static_cast<uint32_t>(uni(static_cast<int>(C.HW)));
-  const uint64_t all = static_cast<uint64_t>(F) * HW;
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(uni(C.st_beta), all * 4u), rx = make_rsrc(uni(C.st_xref), all * 4u);
-  const __amdgpu_buffer_rsrc_t rf =
-      make_rsrc(static_cast<const char*>(uni(C.feat)) + static_cast<uint64_t>(t) * all * ES, all * ES);
+  // (64-bit channel bases: a window's frames stay below 4 GiB, all of the state may not)
+  using Stored = std::conditional_t<F16, uint16_t, float>;
+  const auto beta = in_memory(C.st_beta), xref = in_memory(C.st_xref);
+  const auto feat = in_memory(static_cast<const Stored*>(C.feat)) + static_cast<uint64_t>(t) * F * HW;
   float bf[N], xf[N];
   Feat<F16> ff[N];
 #pragma unroll
   for (int f = 0; f < N; ++f) {
-    const uint32_t c = static_cast<uint32_t>(min(f, F - 1)) * HW;
-    bf[f] = ld_f32(rb, p * 4u, c * 4u);
-    xf[f] = ld_f32(rx, p * 4u, c * 4u);
-    ff[f] = ld_raw<F16>(rf, p * ES, c * ES);
+    const uint64_t c = static_cast<uint64_t>(min(f, F - 1)) * HW;
+    bf[f] = (beta + c)[p];
+    xf[f] = (xref + c)[p];
+    ff[f] = (feat + c)[p];
   }
   double d = 0.0;
 #pragma unroll
