@@ -18,16 +18,21 @@ struct esim_plan_s {
   bool f16 = false;
   std::vector<esim::ClipDev> host;
   esim::ClipDev* dev = nullptr;
+  // for work lists of clips of several ListKinds: the descriptors with the clips of
+  // the other kinds empty, so that a launch skips their items
+  esim::ClipDev* kind_dev[esim::kListKinds] = {};
   esim::Workspace ws{};
   void* ws_mem = nullptr;
   int64_t npix = 0;
   int64_t nblk = 0;
   int64_t wl_capacity = 0;
-  int64_t dense_groups[6] = {0, 0, 0, 0, 0, 0};   // [5]: tiles
-  int tile_last = 0;       // see RegressArgs
-  int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles (0: a clip's windows do not fit)
+  std::vector<esim::ClipRoute> routes;
+  int64_t dense_groups[esim::kDenseSets] = {};
+  int64_t* first_group = nullptr;   // [kDenseSets][nclips] first dense group of each clip (device)
+  int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles
+  uint32_t kinds = 0;      // bit k: a clip of ListKind k
   int lanes_dense = 1;     // lanes per regression item, dense launches
-  bool auto_dense = true;  // no schedule was set: small frames take more lanes (dense_lanes)
+  bool auto_dense = true;  // no schedule was set (FP64 Gram): clip_route's choice
   int lanes_list = 16;     // lanes per regression item, work-list launches
   int blocks_per_cu = 4;   // persistent grid: 256 CUs x this many blocks
   uint64_t max_feat_bytes = 0;   // largest feature array of a clip
@@ -35,12 +40,11 @@ struct esim_plan_s {
   esim::DeviceShape shape;       // compute units and XCDs of the plan's device
   // work buffers of esim_step (allocated with the plan)
   void* step_mem = nullptr;
-  int64_t* xcd_bounds = nullptr;  // [5 lane counts, tiles][kMaxXcds + 1] dense group bounds per XCD (device)
+  int64_t* xcd_bounds = nullptr;  // [kDenseSets][kMaxXcds + 1] dense group bounds per XCD (device)
   int64_t* step_wl = nullptr;     // [wl_capacity]
   int32_t* step_count = nullptr;  // [4] (two segments of a split work list)
-  // esim_step's split work list: clips whose windows fit 16 columns (the
-  // list instance of uncut columns) in the first segment, wider ones from split_seg
-  // on (-1: one segment)
+  // esim_step's split work list: kListSingle clips in the first segment, the
+  // others from split_seg on (-1: one segment)
   int64_t split_seg = -1;
   float* step_alpha = nullptr;    // [npix]
   float* step_beta = nullptr;     // [F + 2][npix] (explicit thresholds only)
@@ -86,65 +90,94 @@ bool query_device_shape(DeviceShape& out) {
 
 namespace {
 
-// Lanes per item of a dense launch.  A tile is a wave of 64 pixels: a frame of
-// fewer tiles than the device has SIMDs leaves SIMDs idle for as long as one wave
-// takes over its window, so it runs 16 lanes per item (r = 7, three frames, F = 7:
-// 4096 pixels 129 -> 19 us, 32768 pixels 143 -> 77 us, 65536 pixels, a tile for
-// each SIMD, 154 against 146 us, 131072 pixels 263 against 289 us).
-int dense_lanes(esim_plan pl) {
-  const bool few = pl->dense_groups[5] < 4ll * pl->shape.cus;
-  return pl->auto_dense && few && pl->host[0].precision == ESIM_GRAM_F64 ? 16 : pl->lanes_dense;
+// Dense launches that cover the plan's clips: calls fn(set) for each, in turn, until
+// one fails.  lanes: per item (0: the plan's schedule).
+template <class Fn>
+int each_dense_set(esim_plan pl, int lanes, Fn&& fn) {
+  const bool f64 = pl->host[0].precision == ESIM_GRAM_F64;
+  const bool own = lanes == 0 && pl->auto_dense && f64;
+  const int L = lanes ? lanes : pl->lanes_dense;
+  int first = esim::kDenseLanes + esim::lanes_index(L), last = first;
+  if (own) {
+    first = esim::kDenseFewSingle;
+    last = esim::kDenseAutoMemory;
+  } else if (f64 && lanes == 0 && (L == 1 || L == 16)) {
+    first = L == 1 ? esim::kDenseTile : esim::kDense16Single;
+    last = first + 1;
+  }
+  for (int set = first; set <= last; ++set)
+    if (pl->dense_groups[set]) {
+      const int rc = fn(set);
+      if (rc != ESIM_OK) return rc;
+    }
+  return ok();
 }
 
-// Arguments of a regression launch with L lanes per item; seg: the clips of one
-// segment of a split work list only (-1: all).
-esim::RegressArgs regress_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
-                               int L, bool kappa, int seg = -1) {
-  int max_r = 0, max_tr = 0;           // over the clips (of the segment)
-  for (const auto& c : pl->host)
-    if (seg < 0 || c.list_class == seg) {
-      max_r = std::max(max_r, static_cast<int>(c.r));
-      max_tr = std::max(max_tr, static_cast<int>(c.tr));
-    }
+esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
   esim::RegressArgs a{};
   a.clips = pl->dev;
   a.nclips = pl->nclips;
   a.t = t;
-  a.items = worklist;
-  a.count = count;
-  const bool tiles = !worklist && !kappa && L == 1 && pl->tile_units && pl->host[0].precision == ESIM_GRAM_F64;
-  const int dense = tiles ? 5 : esim::lanes_index(L);
-  a.tile_units = tiles ? pl->tile_units : 0;
-  a.tile_last = pl->tile_last;
-  a.n_dense_groups = pl->dense_groups[dense];
-  const int G = esim::kWave / L;
-  a.max_groups = worklist ? (std::max<int64_t>(n_out, 1) + G - 1) / G : a.n_dense_groups;
+  a.first_group = pl->first_group + static_cast<int64_t>(set) * pl->nclips;
+  a.tile_units = esim::dense_tiles(set) ? pl->tile_units : 0;
+  a.n_dense_groups = a.max_groups = pl->dense_groups[set];
   a.n_out = n_out;
-  a.xcd_bounds = (!worklist && pl->nclips > 1) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * dense : nullptr;
+  a.xcd_bounds = pl->nclips > 1 ? pl->xcd_bounds + (esim::kMaxXcds + 1) * set : nullptr;
   a.nxcd = pl->shape.xcds;
-  // 9 to 15 columns are one uncut turn of 16 lanes; narrower windows fill the lanes
-  // better cut into parts (65536 items at r = 3: 84 us, uncut 98)
-  a.single = max_r >= 4 && max_r <= 7 && max_tr <= 1 ? 1 : 0;
+  a.single = esim::dense_single(set);
   return a;
 }
 
+// kind: the clips' ListKind (-1: whatever they are); `only`: of those clips only.
+esim::RegressArgs list_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
+                            int L, int kind, bool only) {
+  esim::RegressArgs a{};
+  a.clips = only ? pl->kind_dev[kind] : pl->dev;
+  a.nclips = pl->nclips;
+  a.t = t;
+  a.items = worklist;
+  a.count = count;
+  const int G = esim::kWave / L;
+  a.max_groups = (std::max<int64_t>(n_out, 1) + G - 1) / G;
+  a.n_out = n_out;
+  a.nxcd = pl->shape.xcds;
+  a.single = kind == esim::kListSingle;
+  return a;
+}
+
+// kinds: the ListKinds that the work list may hold (bits).
 int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count,
                         int64_t n_out, float* alpha, float* beta, float* resid, float* kappa,
-                        bool update_state, hipStream_t stream, int seg = -1) {
+                        bool update_state, hipStream_t stream, uint32_t kinds = ~0u) {
+  const int precision = pl->host[0].precision;
   // the condition estimate of the FP64 Gram comes from a one-lane instance
-  const bool kappa_f64 = kappa && pl->host[0].precision == ESIM_GRAM_F64;
-  const int L = kappa_f64 ? 1 : worklist ? pl->lanes_list : dense_lanes(pl);
-  if (!esim::regress_supports(pl->F, L, pl->host[0].precision))
-    return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
-  esim::RegressArgs a = regress_args(pl, t, worklist, count, n_out, L, kappa != nullptr, seg);
-  a.alpha = alpha;
-  a.beta = beta;
-  a.resid = resid;
-  a.kappa = kappa;
-  a.update_state = update_state ? 1 : 0;
-  return hip_check(esim::launch_regress(a, pl->F, pl->f16, pl->host[0].precision, L, pl->blocks_per_cu,
-                                        pl->shape, stream),
-                   "regress");
+  const bool kappa_f64 = kappa && precision == ESIM_GRAM_F64;
+  auto launch = [&](esim::RegressArgs a, int L) {
+    if (!esim::regress_supports(pl->F, L, precision))
+      return fail(ESIM_E_UNSUPPORTED, "no kernel instance for this F, lane count and precision");
+    a.alpha = alpha;
+    a.beta = beta;
+    a.resid = resid;
+    a.kappa = kappa;
+    a.update_state = update_state ? 1 : 0;
+    return hip_check(esim::launch_regress(a, pl->F, pl->f16, precision, L, pl->blocks_per_cu, pl->shape, stream),
+                     "regress");
+  };
+  if (!worklist)
+    return each_dense_set(pl, kappa_f64 ? 1 : 0, [&](int set) {
+      return launch(dense_args(pl, t, n_out, set), esim::dense_set_lanes(set));
+    });
+  const int L = kappa_f64 ? 1 : pl->lanes_list;
+  kinds &= pl->kinds;
+  if (L != 16 || precision != ESIM_GRAM_F64 || kinds == 0)
+    return launch(list_args(pl, t, worklist, count, n_out, L, -1, false), L);
+  // clips of several kinds: a launch for each, over the same list
+  for (int k = 0; k < esim::kListKinds; ++k)
+    if ((kinds >> k) & 1u) {
+      const int rc = launch(list_args(pl, t, worklist, count, n_out, L, k, kinds != (1u << k)), L);
+      if (rc != ESIM_OK) return rc;
+    }
+  return ok();
 }
 
 // The every-crossing rule keeps the previous frame's value in the state.
@@ -232,10 +265,8 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->nclips = nclips;
     pl->F = clips[0].F;
     pl->f16 = clips[0].feat_dtype == ESIM_F16;
-    int64_t pix = 0, blk = 0, grp[6] = {0, 0, 0, 0, 0, 0};
+    int64_t pix = 0, blk = 0;
     int64_t wl = 0;
-    int tile_units = 0, tile_last = 0;
-    bool tiles_fit = true;
     for (int c = 0; c < nclips; ++c) {
       const esim_clip& k = clips[c];
       const esim_params& p = params[c];
@@ -321,30 +352,6 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
       cd.pix_off = pix;
       cd.blk_off = blk;
       cd.nblk = (cd.HW + esim::kBlock - 1) / esim::kBlock;
-      const int Ls[5] = {1, 2, 4, 8, 16};
-      for (int q = 0; q < 5; ++q) {
-        cd.grp_off[q] = grp[q];
-        grp[q] += (cd.HW + (esim::kWave / Ls[q]) - 1) / (esim::kWave / Ls[q]);
-      }
-      {
-        // tiles of 64, 32 or 16 columns: the one that covers the image with the
-        // fewest pixels (the widest of equal ones)
-        int64_t best = -1;
-        for (int lw = 6; lw >= 4; --lw) {
-          const int64_t tw = 1 << lw, th = esim::kWave >> lw;
-          const int64_t n = ((k.W + tw - 1) / tw) * ((k.H + th - 1) / th);
-          if (best < 0 || n < best) {
-            best = n;
-            cd.tile_lw = lw;
-          }
-        }
-        cd.grp_off[5] = grp[5];
-        grp[5] += best;
-        // a row of the ring is loaded in at most two turns of the wave's lanes
-        tiles_fit = tiles_fit && (1 << cd.tile_lw) + 2 * p.r <= 2 * esim::kWave;
-        tile_last = std::max(tile_last, esim::tile_last_units(k.F, p.tr));
-        tile_units = std::max(tile_units, esim::tile_wave_units(k.F, p.r, p.tr, cd.tile_lw));
-      }
       cd.C = p.C;
       cd.h = p.h;
       cd.ridge = p.ridge;
@@ -384,26 +391,23 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->npix = pix;
     pl->nblk = blk;
     pl->wl_capacity = wl;
-    {
-      // the split work list of esim_step (multi-clip plans with windows on
-      // both sides of 16 columns)
-      int64_t seg = 0;
-      bool narrow = false, wide = false;
-      for (auto& cd : pl->host) {
-        cd.list_class = 2 * cd.r + 1 > 16 ? 1 : 0;
-        if (cd.list_class) {
-          wide = true;
-        } else {
-          narrow = true;
-          seg += cd.HW;
-        }
+    int64_t seg = 0;
+    std::vector<int64_t> first(static_cast<size_t>(esim::kDenseSets) * nclips);
+    for (int c = 0; c < nclips; ++c) {
+      auto& cd = pl->host[c];
+      const esim::ClipRoute rt = esim::clip_route(cd.W, cd.H, cd.F, cd.r, cd.tr, pl->shape.cus);
+      for (int set = 0; set < esim::kDenseSets; ++set) {
+        first[static_cast<size_t>(set) * nclips + c] = pl->dense_groups[set];
+        pl->dense_groups[set] += esim::dense_groups(set, rt, cd.W, cd.H);
       }
-      pl->split_seg = narrow && wide ? seg : -1;
+      if (rt.tiles) pl->tile_units = std::max(pl->tile_units, esim::tile_wave_units(cd.F, cd.r, cd.tr, rt.tile_lw));
+      cd.tile_lw = rt.tile_lw;
+      cd.list_class = rt.kind == esim::kListSingle ? 0 : 1;
+      if (cd.list_class == 0) seg += cd.HW;
+      pl->kinds |= 1u << rt.kind;
+      pl->routes.push_back(rt);
     }
-    for (int q = 0; q < 6; ++q) pl->dense_groups[q] = grp[q];
-    const size_t tile_block = (static_cast<size_t>(tile_units) * 4u * esim::regress_waves_per_simd(pl->F, false) + tile_last) * 16u;
-    pl->tile_last = tile_last;
-    pl->tile_units = tiles_fit && tile_block <= esim::kMaxTileLds ? tile_units : 0;
+    pl->split_seg = seg > 0 && seg < pix ? seg : -1;
 
     // device memory: descriptors + workspace
     const size_t clip_bytes = sizeof(esim::ClipDev) * nclips;
@@ -411,12 +415,18 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     size_t off = 0;
     const size_t o_clips = off;
     off = align(off + clip_bytes);
+    const bool mixed = (pl->kinds & (pl->kinds - 1)) != 0;
+    const size_t o_kinds = off;
+    const size_t kind_bytes = align(clip_bytes);
+    if (mixed) off += kind_bytes * esim::kListKinds;
     const size_t o_bcount = off;
     off = align(off + sizeof(int64_t) * blk);
     const size_t o_chunk = off;
     off = align(off + sizeof(int64_t) * ((blk + esim::kChunkBlocks - 1) / esim::kChunkBlocks));
     const size_t o_xcd = off;
-    off = align(off + sizeof(int64_t) * 6 * (esim::kMaxXcds + 1));
+    off = align(off + sizeof(int64_t) * esim::kDenseSets * (esim::kMaxXcds + 1));
+    const size_t o_first = off;
+    off = align(off + sizeof(int64_t) * first.size());
     const size_t o_flags = off;
     off = align(off + sizeof(uint64_t) * blk * esim::kWavesPerBlock);
     const size_t o_pol = off;
@@ -433,6 +443,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->ws.bcount = reinterpret_cast<int64_t*>(m + o_bcount);
     pl->ws.chunk = reinterpret_cast<int64_t*>(m + o_chunk);
     pl->xcd_bounds = reinterpret_cast<int64_t*>(m + o_xcd);
+    pl->first_group = reinterpret_cast<int64_t*>(m + o_first);
     pl->ws.flags = reinterpret_cast<uint64_t*>(m + o_flags);
     pl->ws.pol = reinterpret_cast<uint64_t*>(m + o_pol);
     pl->ws.misc = reinterpret_cast<int64_t*>(m + o_misc);
@@ -440,28 +451,30 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     // by work (window size x groups per clip) rather than by count, since a
     // clip's items cost in proportion to its window.
     const int nx = pl->shape.xcds;
-    std::vector<int64_t> xb(6 * (esim::kMaxXcds + 1), 0);
-    for (int q = 0; q < 6; ++q) {
+    std::vector<int64_t> xb(esim::kDenseSets * (esim::kMaxXcds + 1), 0);
+    for (int q = 0; q < esim::kDenseSets; ++q) {
+      const int64_t groups = pl->dense_groups[q];
+      const int64_t* at = first.data() + static_cast<size_t>(q) * nclips;
       int64_t* row = xb.data() + q * (esim::kMaxXcds + 1);
       double total = 0.0;
       std::vector<double> wc(nclips);
       std::vector<int64_t> gc(nclips);
       for (int c = 0; c < nclips; ++c) {
         const auto& cd = pl->host[c];
-        gc[c] = (c + 1 < nclips ? pl->host[c + 1].grp_off[q] : grp[q]) - cd.grp_off[q];
+        gc[c] = (c + 1 < nclips ? at[c + 1] : groups) - at[c];
         wc[c] = static_cast<double>(2 * cd.r + 1) * (2 * cd.r + 1) * (2 * cd.tr + 1);
         total += wc[c] * static_cast<double>(gc[c]);
       }
       row[0] = 0;
-      row[nx] = grp[q];
+      row[nx] = groups;
       for (int x = 1; x < nx; ++x) {
         const double target = total * x / nx;
         double cum = 0.0;
-        int64_t idx = grp[q];
+        int64_t idx = groups;
         for (int c = 0; c < nclips; ++c) {
           const double cw = wc[c] * static_cast<double>(gc[c]);
           if (cum + cw >= target) {
-            idx = pl->host[c].grp_off[q] +
+            idx = at[c] +
                   std::min<int64_t>(gc[c], static_cast<int64_t>(std::ceil((target - cum) / wc[c])));
             break;
           }
@@ -471,9 +484,18 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
       }
     }
     e = hipMemcpy(pl->dev, pl->host.data(), clip_bytes, hipMemcpyHostToDevice);
+    for (int k = 0; mixed && k < esim::kListKinds && e == hipSuccess; ++k) {
+      std::vector<esim::ClipDev> of_kind = pl->host;
+      for (int c = 0; c < nclips; ++c)
+        if (pl->routes[c].kind != k) of_kind[c].HW = 0;
+      pl->kind_dev[k] = reinterpret_cast<esim::ClipDev*>(m + o_kinds + kind_bytes * k);
+      e = hipMemcpy(pl->kind_dev[k], of_kind.data(), clip_bytes, hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = hipMemset(m + o_bcount, 0, off - o_bcount);
     if (e == hipSuccess)
       e = hipMemcpy(pl->xcd_bounds, xb.data(), sizeof(int64_t) * xb.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = hipMemcpy(pl->first_group, first.data(), sizeof(int64_t) * first.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
       (void)hipFree(pl->ws_mem);   // the upload's error is the one reported
@@ -659,21 +681,20 @@ int esim_step(esim_plan pl, int32_t t, int32_t mode, float* dl, esim_events_buf*
       return fail(ESIM_E_INVAL, "events buffer incomplete");
     esim::EventsDev ed{ev->x, ev->y, ev->t, ev->p, ev->clip, ev->capacity, ev->count, ev->ts};
     if (mode == ESIM_THRESHOLDED) {
-      // Mixed window widths: the compaction writes the narrow clips' items and
-      // the wide ones' into two segments, and each gets its own launch, so the
-      // narrow ones run the list instance of uncut columns (one column per lane)
-      // instead of the general one, each launch spread over every XCD.
+      // Clips of several list kinds: the compaction writes the kListSingle clips'
+      // items and the others' into two segments, so that a launch holds items of its
+      // own kind only, spread over every XCD.
       const bool split = pl->split_seg >= 0 && pl->thr == ESIM_THRESHOLD_CLOSED && pl->lanes_list == 16 &&
                          pl->host[0].precision == ESIM_GRAM_F64;
       int rc = threshold_compact(pl, t, dl, pl->step_wl, pl->step_count, &ed, s, split ? pl->split_seg : -1);
       if (rc != ESIM_OK) return rc;
       if (split) {
         rc = launch_plan_regress(pl, t, pl->step_wl, pl->step_count, pl->split_seg, nullptr, nullptr, nullptr,
-                                 nullptr, true, s, 0);
+                                 nullptr, true, s, 1u << esim::kListSingle);
         if (rc != ESIM_OK) return rc;
         return launch_plan_regress(pl, t, pl->step_wl + pl->split_seg, pl->step_count + 2,
                                    pl->wl_capacity - pl->split_seg, nullptr, nullptr, nullptr, nullptr, true, s,
-                                   1);
+                                   ~(1u << esim::kListSingle));
       }
       if (pl->thr == ESIM_THRESHOLD_CLOSED)
         return launch_plan_regress(pl, t, pl->step_wl, pl->step_count, pl->wl_capacity, nullptr, nullptr,
@@ -739,8 +760,17 @@ int esim_wlr_regress_bandwidth(esim_plan pl, int32_t t, const int64_t* worklist,
       a.h[k] = hs[k];
       a.scale[k] = hc.h / hs[k];
     }
-    const int L = worklist || dense_lanes(pl) == 16 ? 16 : 1;
-    a.reg = regress_args(pl, t, worklist, count, worklist ? std::min(n_out, pl->wl_capacity) : n_out, L, false);
+    int L = 16;
+    if (worklist) {
+      a.reg = list_args(pl, t, worklist, count, std::min(n_out, pl->wl_capacity), L, pl->routes[0].kind, false);
+    } else {
+      // the instance of the plan's dense regressions (16 lanes, or one)
+      int set = -1;
+      (void)each_dense_set(pl, 0, [&](int s) { return set = s, ok(); });
+      if (set < esim::kDenseTile) set = pl->routes[0].tiles ? esim::kDenseTile : esim::kDenseMemory;
+      a.reg = dense_args(pl, t, n_out, set);
+      L = esim::dense_set_lanes(set);
+    }
     a.reg.n_out = n_out;
     a.reg.alpha = alpha;
     a.reg.beta = beta;
@@ -774,7 +804,7 @@ int esim_wlr_backward(esim_plan pl, const int64_t* items, int64_t n, const float
       return fail(ESIM_E_UNSUPPORTED, "backward supports window radii up to 25");
     const size_t need = esim::backward_scratch_bytes(pl->host[0], n);
     if (!scratch || scratch_bytes < need) return fail(ESIM_E_CAPACITY, "scratch too small");
-    esim::BackwardArgs a{pl->dev, &pl->host[0], regress_args(pl, -1, items, nullptr, n, 16, false), n, g_alpha, g_y, g_b,
+    esim::BackwardArgs a{pl->dev, &pl->host[0], list_args(pl, -1, items, nullptr, n, 16, pl->routes[0].kind, false), n, g_alpha, g_y, g_b,
                          scratch, scratch_bytes, pl->shape};
     return hip_check(esim::launch_backward(a, static_cast<hipStream_t>(stream)), "backward");
   } catch (...) {

@@ -412,8 +412,7 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   adj.g_alpha = a.g_alpha;
   adj.bd = bd;
   adj.reg.max_groups = (a.n + kWave / 16 - 1) / (kWave / 16);
-  const int waves = regress_waves_per_simd(F, false);
-  const hipError_t e = launch_groups(reinterpret_cast<const void*>(fn), &adj, adj.reg, waves, true, waves, a.dev, s);
+  const hipError_t e = launch_groups(reinterpret_cast<const void*>(fn), &adj, adj.reg, F, true, 1, a.dev, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(gat, dim3(static_cast<unsigned>(gblocks)), dim3(kGatherThreads), 0, s, a.clip, bd, a.g_y);
   hipLaunchKernelGGL(rb, dim3(kRedBlocks), dim3(256), 0, s, bd);

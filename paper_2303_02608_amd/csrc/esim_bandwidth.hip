@@ -52,9 +52,8 @@ hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, int lanes, 
                         : lanes == 16 ? t->bandwidth[a.single ? 2 : 3][f16]
                                       : t->bandwidth[a.tile_units ? 0 : 1][f16];
   if (!k) return hipErrorInvalidValue;
-  const int waves = regress_waves_per_simd(F, false);
-  return launch_groups(reinterpret_cast<const void*>(k), const_cast<BandwidthArgs*>(&b), a, waves,
-                       lanes == 16 || a.tile_units, waves, dev, s);
+  return launch_groups(reinterpret_cast<const void*>(k), const_cast<BandwidthArgs*>(&b), a, F,
+                       lanes == 16 || a.tile_units, regress_waves_per_simd(F, false), dev, s);
 }
 
 }  // namespace esim

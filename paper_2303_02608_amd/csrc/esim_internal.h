@@ -8,10 +8,10 @@
 #include <type_traits>
 
 #include "esim.h"
+#include "esim_schedule.h"
 
 namespace esim {
 
-constexpr int kWave = 64;
 constexpr int kBlock = 256;                 // threads of flag/scatter blocks
 constexpr int kWavesPerBlock = kBlock / kWave;
 
@@ -31,7 +31,6 @@ struct ClipDev {
   int64_t pix_off;         // first pixel in the concatenated pixel range
   int64_t blk_off;         // first kBlock-pixel block of the flag/scatter grid
   int64_t nblk;            // kBlock-pixel blocks of this clip
-  int64_t grp_off[6];      // first dense wave-group, per lanes-per-item 1,2,4,8,16; [5]: first tile
   double C, h, ridge, kappa_fp64;
   double c2[ESIM_MAX_D];   // 1 / (h b_j)^2
   double sf[ESIM_MAX_D];   // 1 / (h b_j)
@@ -40,9 +39,9 @@ struct ClipDev {
   float* st_rmom;          // [2][HW] R and mean residual of the stored plane (nullable)
   int32_t thr;             // esim_threshold
   double dt;               // time between frames (event times t * dt)
-  int32_t tile_lw;         // log2 of the width of the clip's dense tiles (tiles of 256 pixels)
-  int32_t list_class;      // 1: esim_step's split work list puts this clip's items in its second
-                           // segment (windows wider than 16 columns), 0 otherwise
+  int32_t tile_lw;         // log2 of the width of the clip's dense tiles (of 64 pixels)
+  int32_t list_class;      // segment of esim_step's split work list that takes this clip's items:
+                           // 0: kListSingle clips, 1: the others
 };
 
 // Shape of the device a plan runs on, queried once when the plan is created:
@@ -167,33 +166,10 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
-__host__ __device__ constexpr int lanes_index(int L) {
-  return L == 1 ? 0 : L == 2 ? 1 : L == 4 ? 2 : L == 8 ? 3 : 4;
-}
-
 // Work item fields.
 __device__ __forceinline__ int item_clip(int64_t it) { return static_cast<int>((it >> 32) & 0xFFF); }
 __device__ __forceinline__ int64_t item_pixel(int64_t it) { return it & 0xFFFFFFFFll; }
 __device__ __forceinline__ int item_frame(int64_t it) { return static_cast<int>(it >> 44); }
-
-// Tiles of a dense launch with one lane per pixel (esim_wlr.h): 64 pixels of 2^lw
-// columns, each wave with its own LDS.
-constexpr int tile_quads(int F) { return (F + 4) / 4; }                            // 16-byte units of F + 1 channels
-constexpr int tile_units(int F, int frames) { return (frames * tile_quads(F)) | 1; }   // of a pixel's record
-// Frames walked at a time (windows of more: one by one): five, where the rows
-// loaded ahead leave the registers for them (F = 12, three frames, 307200 pixels,
-// r = 7: spilling with three at a time 3.17 ms, one by one 2.17).
-constexpr int max_tile_frames(int F) { return F > 11 ? 1 : F > 10 ? 3 : 5; }
-// 16-byte units of a wave's LDS for windows of radius r (the ring of rows), and
-// of the record behind a block's last wave that the look-ahead of a row's walk
-// may read.
-constexpr int tile_last_units(int F, int tr) {
-  return tile_units(F, 2 * tr + 1 < max_tile_frames(F) ? 2 * tr + 1 : max_tile_frames(F));
-}
-constexpr int tile_wave_units(int F, int r, int tr, int lw) {
-  return tile_last_units(F, tr) * ((1 << lw) + 2 * r) * (kWave >> lw);
-}
-constexpr size_t kMaxTileLds = 160 * 1024 - 64;      // of a block (one per CU): the CU's LDS less the queue
 
 // ---- launchers (host) -----------------------------------------------------
 
@@ -203,7 +179,8 @@ struct RegressArgs {
   int32_t t;                // >= 0 uniform frame, < 0 frame from the item
   const int64_t* items;     // nullptr = dense
   const int32_t* count;
-  int64_t n_dense_groups;   // dense: wave-groups over all clips (for the chosen L)
+  const int64_t* first_group;   // dense: [nclips] of its DenseSet (clips outside have no groups; device)
+  int64_t n_dense_groups;   // dense: wave-groups over the set's clips
   int64_t max_groups;       // upper bound of groups (grid sizing)
   int64_t n_out;
   float* alpha;             // nullable when update_state is set
@@ -213,9 +190,8 @@ struct RegressArgs {
   int32_t update_state;     // write each item's model into its clip state (Sec. 2.2)
   const int64_t* xcd_bounds;  // dense multi-clip launches: [nxcd + 1] group bounds per XCD (device)
   int32_t nxcd;               // XCDs of the device (group-to-XCD mapping)
-  int32_t single;             // every item's window is one turn of uncut columns of 16 lanes (walk_parts)
+  int32_t single;             // 16 lanes per item: the instance of kListSingle clips
   int32_t tile_units;         // dense tiles: 16-byte units of a wave's LDS (0: groups of lanes, no tiles)
-  int32_t tile_last;          // and of the record behind the block's last wave
 };
 
 // Regression launcher: picks the kernel instance for (F, dtype, precision)
@@ -226,11 +202,6 @@ using AdjointFn = void (*)(AdjointArgs);
 struct BandwidthArgs;
 using BandwidthFn = void (*)(BandwidthArgs);
 
-// FP64 instances up to 8 features keep their sums within half the register file
-// and run two waves per SIMD (a wave's scalar and memory instructions then issue
-// beside the other wave's FMAs); larger F, and the compensated-FP32 variant, run
-// one.
-constexpr int regress_waves_per_simd(int F, bool c32) { return (!c32 && F <= 8) ? 2 : 1; }
 // Regression kernels of one feature count: FP64 Gram [lanes 1, 2, 4, 8, 16][f16],
 // compensated FP32 [lanes 4, 16][f16] (null where not compiled).
 struct RegressTable {
@@ -247,10 +218,10 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
                           int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
 const RegressTable* regress_table(int F);   // null outside 1..ESIM_MAX_F
 // Launches a kernel over the groups of a (args: its one argument, which holds
-// a): `queue` with one block per CU of 4 waves_per_simd waves that hand out their
+// a): `queue` with one block per CU of 4 regress_waves_per_simd waves that hand out their
 // share of the groups (GroupQueue), else blocks of four waves, at most
 // blocks_per_cu a CU, that stride over them.
-hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int waves_per_simd, bool queue,
+hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int F, bool queue,
                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
 bool regress_supports(int F, int lanes, int precision);
 

@@ -76,19 +76,19 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
   // the others stride over them with the resident blocks (more would only start
   // when those end).
   const int resident = regress_waves_per_simd(F, c32);
-  return launch_groups(reinterpret_cast<const void*>(fn), const_cast<RegressArgs*>(&a), a, resident,
+  return launch_groups(reinterpret_cast<const void*>(fn), const_cast<RegressArgs*>(&a), a, F,
                        a.tile_units || (!c32 && !a.kappa && lanes >= 4), std::min(blocks_per_cu, resident), dev, s);
 }
 
-hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int waves_per_simd, bool queue,
+hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int F, bool queue,
                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s) {
-  const int waves = queue ? 4 * waves_per_simd : kWavesPerBlock;
+  const int waves = queue ? 4 * regress_waves_per_simd(F, false) : kWavesPerBlock;
   int64_t blocks = queue ? a.max_groups : (a.max_groups + waves - 1) / waves;
   const int64_t cap = static_cast<int64_t>(dev.cus) * (queue ? 1 : blocks_per_cu);
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   blocks = (blocks + dev.xcds - 1) / dev.xcds * dev.xcds;   // a multiple of the XCDs (see GroupIter, GroupQueue)
-  const size_t lds = a.tile_units ? (static_cast<size_t>(a.tile_units) * waves + a.tile_last) * 16u : 0;
+  const size_t lds = a.tile_units ? tile_block_bytes(F, a.tile_units) : 0;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;

@@ -1,0 +1,127 @@
+// Which kernel instance runs a clip's FP64 regressions, and how a launch over
+// several clips is put together.  Plain host code, no HIP.
+//
+// An instance fixes the order of a regression's sums.  What a clip gets follows
+// from its own shape and parameters (and the schedule, where one was set), never
+// from the other clips of its plan: converted in a batch it gives the bits that it
+// gives alone.  A launch takes the clips of one instance; a plan of several kinds
+// of clips takes one launch for each.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+namespace esim {
+
+constexpr int kWave = 64;
+
+// FP64 instances up to 8 features keep their sums within half the register file
+// and run two waves per SIMD (a wave's scalar and memory instructions then issue
+// beside the other wave's FMAs); larger F, and the compensated-FP32 variant, run
+// one.
+constexpr int regress_waves_per_simd(int F, bool c32) { return (!c32 && F <= 8) ? 2 : 1; }
+
+constexpr int lanes_index(int L) { return L == 1 ? 0 : L == 2 ? 1 : L == 4 ? 2 : L == 8 ? 3 : 4; }
+
+// Tiles of a dense launch with one lane per pixel (esim_wlr.h): 64 pixels of 2^lw
+// columns, each wave with its own LDS.
+constexpr int tile_quads(int F) { return (F + 4) / 4; }                            // 16-byte units of F + 1 channels
+constexpr int tile_units(int F, int frames) { return (frames * tile_quads(F)) | 1; }   // of a pixel's record
+// Frames walked at a time (windows of more: one by one): five, where the rows
+// loaded ahead leave the registers for them (F = 12, three frames, 307200 pixels,
+// r = 7: spilling with three at a time 3.17 ms, one by one 2.17).
+constexpr int max_tile_frames(int F) { return F > 11 ? 1 : F > 10 ? 3 : 5; }
+// 16-byte units of a wave's LDS for windows of radius r (the ring of rows), and
+// of the record behind a block's last wave that the look-ahead of a row's walk
+// may read (of the longest windows: plans mix them).
+constexpr int tile_last_units(int F) { return tile_units(F, max_tile_frames(F)); }
+constexpr int tile_wave_units(int F, int r, int tr, int lw) {
+  return tile_units(F, 2 * tr + 1 < max_tile_frames(F) ? 2 * tr + 1 : max_tile_frames(F)) * ((1 << lw) + 2 * r) *
+         (kWave >> lw);
+}
+constexpr size_t kMaxTileLds = 160 * 1024 - 64;      // of a block (one per CU): the CU's LDS less the queue
+constexpr size_t tile_block_bytes(int F, int wave_units) {
+  return (static_cast<size_t>(wave_units) * 4u * regress_waves_per_simd(F, false) + tile_last_units(F)) * 16u;
+}
+constexpr int64_t tile_count(int W, int H, int lw) {
+  return static_cast<int64_t>((W + (1ll << lw) - 1) >> lw) * ((H + (kWave >> lw) - 1) / (kWave >> lw));
+}
+
+// How the 16-lane instances walk a clip's windows (walk_parts).
+enum ListKind { kListParts = 0, kListSingle = 1, kListKinds = 2 };
+
+struct ClipRoute {
+  int tile_lw;        // log2 of the tiles' width
+  bool tiles;         // dense tiles run from LDS
+  bool few;           // a dense frame takes 16 lanes per item
+  int kind;           // ListKind
+};
+
+inline ClipRoute clip_route(int W, int H, int F, int r, int tr, int cus) {
+  ClipRoute c{};
+  // tiles of 64, 32 or 16 columns: the one that covers the image with the fewest
+  // pixels (the widest of equal ones)
+  c.tile_lw = 6;
+  for (int lw = 5; lw >= 4; --lw)
+    if (tile_count(W, H, lw) < tile_count(W, H, c.tile_lw)) c.tile_lw = lw;
+  // a row of the ring is loaded in at most two turns of the wave's lanes
+  c.tiles = (1 << c.tile_lw) + 2 * r <= 2 * kWave &&
+            tile_block_bytes(F, tile_wave_units(F, r, tr, c.tile_lw)) <= kMaxTileLds;
+  // A tile is a wave of 64 pixels: a frame of fewer tiles than the device has SIMDs
+  // leaves SIMDs idle for as long as one wave takes over its window, so it runs 16
+  // lanes per item (r = 7, three frames, F = 7: 4096 pixels 129 -> 19 us, 32768
+  // pixels 143 -> 77 us, 65536 pixels, a tile for each SIMD, 154 against 146 us,
+  // 131072 pixels 263 against 289 us).
+  c.few = tile_count(W, H, c.tile_lw) < 4ll * cus;
+  // 9 to 15 columns are one uncut turn of 16 lanes; narrower windows fill the lanes
+  // better cut into parts (65536 items at r = 3: 84 us, uncut 98)
+  c.kind = r >= 4 && r <= 7 && tr <= 1 ? kListSingle : kListParts;
+  return c;
+}
+
+// Dense launches: the clips that one takes, and their instance.  Of the automatic
+// schedule: kDenseFewSingle and the ones after it.
+enum DenseSet {
+  kDenseLanes = 0,        // + lanes_index(L): every clip, L lanes per item
+  kDenseTile = 5,         // one lane per item set by hand: clips whose tiles fit
+  kDenseMemory,           //   the others, windows from memory
+  kDense16Single,         // 16 lanes set by hand: clips of a ListKind
+  kDense16Parts,
+  kDenseFewSingle,        // few: 16 lanes, by ListKind
+  kDenseFewParts,
+  kDenseAutoTile,         // not few: tiles, or from memory
+  kDenseAutoMemory,
+  kDenseSets
+};
+
+inline bool dense_member(int set, const ClipRoute& c) {
+  const bool single = c.kind == kListSingle;
+  switch (set) {
+    case kDenseTile: return c.tiles;
+    case kDenseMemory: return !c.tiles;
+    case kDense16Single: return single;
+    case kDense16Parts: return !single;
+    case kDenseFewSingle: return c.few && single;
+    case kDenseFewParts: return c.few && !single;
+    case kDenseAutoTile: return !c.few && c.tiles;
+    case kDenseAutoMemory: return !c.few && !c.tiles;
+    default: return true;
+  }
+}
+
+constexpr bool dense_tiles(int set) { return set == kDenseTile || set == kDenseAutoTile; }
+constexpr int dense_set_lanes(int set) {
+  return set < kDenseTile ? 1 << set
+         : dense_tiles(set) || set == kDenseMemory || set == kDenseAutoMemory ? 1 : 16;
+}
+constexpr bool dense_single(int set) { return set == kDense16Single || set == kDenseFewSingle; }
+
+// Groups of a clip's pixels in a dense launch: tiles, or 64 / L pixels.
+inline int64_t dense_groups(int set, const ClipRoute& c, int W, int H) {
+  if (!dense_member(set, c)) return 0;
+  if (dense_tiles(set)) return tile_count(W, H, c.tile_lw);
+  const int64_t G = kWave / dense_set_lanes(set);
+  return (static_cast<int64_t>(W) * H + G - 1) / G;
+}
+
+}  // namespace esim
