@@ -59,14 +59,19 @@ struct ClipRoute {
 
 inline ClipRoute clip_route(int W, int H, int F, int r, int tr, int cus) {
   ClipRoute c{};
-  // tiles of 64, 32 or 16 columns: the one that covers the image with the fewest
-  // pixels (the widest of equal ones)
+  // tiles of 64, 32 or 16 columns: of those whose rows are loaded in at most two
+  // turns of a wave's lanes and whose ring fits LDS, the one that covers the image
+  // with the fewest pixels (the widest of equal ones)
+  auto fits = [&](int lw) {
+    return (1 << lw) + 2 * r <= 2 * kWave && tile_block_bytes(F, tile_wave_units(F, r, tr, lw)) <= kMaxTileLds;
+  };
   c.tile_lw = 6;
-  for (int lw = 5; lw >= 4; --lw)
-    if (tile_count(W, H, lw) < tile_count(W, H, c.tile_lw)) c.tile_lw = lw;
-  // a row of the ring is loaded in at most two turns of the wave's lanes
-  c.tiles = (1 << c.tile_lw) + 2 * r <= 2 * kWave &&
-            tile_block_bytes(F, tile_wave_units(F, r, tr, c.tile_lw)) <= kMaxTileLds;
+  c.tiles = false;
+  for (int lw = 6; lw >= 4; --lw)
+    if (fits(lw) && (!c.tiles || tile_count(W, H, lw) < tile_count(W, H, c.tile_lw))) {
+      c.tile_lw = lw;
+      c.tiles = true;
+    }
   // A tile is a wave of 64 pixels: a frame of fewer tiles than the device has SIMDs
   // leaves SIMDs idle for as long as one wave takes over its window, so it runs 16
   // lanes per item (r = 7, three frames, F = 7: 4096 pixels 129 -> 19 us, 32768
