@@ -99,11 +99,11 @@ int each_dense_set(esim_plan pl, int lanes, Fn&& fn) {
   const int L = lanes ? lanes : pl->lanes_dense;
   int first = esim::kDenseLanes + esim::lanes_index(L), last = first;
   if (own) {
-    first = esim::kDenseFewSingle;
+    first = esim::kDenseFew;
     last = esim::kDenseAutoMemory;
   } else if (f64 && lanes == 0 && (L == 1 || L == 16)) {
-    first = L == 1 ? esim::kDenseTile : esim::kDense16Single;
-    last = first + 1;
+    first = L == 1 ? esim::kDenseTile : esim::kDense16;
+    last = L == 1 ? esim::kDenseMemory : esim::kDenseFew - 1;
   }
   for (int set = first; set <= last; ++set)
     if (pl->dense_groups[set]) {
@@ -124,11 +124,11 @@ esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
   a.n_out = n_out;
   a.xcd_bounds = pl->nclips > 1 ? pl->xcd_bounds + (esim::kMaxXcds + 1) * set : nullptr;
   a.nxcd = pl->shape.xcds;
-  a.single = esim::dense_single(set);
+  a.kind = esim::dense_kind(set);
   return a;
 }
 
-// kind: the clips' ListKind (-1: whatever they are); `only`: of those clips only.
+// kind: ListKind of the instance (16 lanes); `only`: items of clips of that kind only.
 esim::RegressArgs list_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
                             int L, int kind, bool only) {
   esim::RegressArgs a{};
@@ -141,7 +141,7 @@ esim::RegressArgs list_args(esim_plan pl, int32_t t, const int64_t* worklist, co
   a.max_groups = (std::max<int64_t>(n_out, 1) + G - 1) / G;
   a.n_out = n_out;
   a.nxcd = pl->shape.xcds;
-  a.single = kind == esim::kListSingle;
+  a.kind = kind;
   return a;
 }
 
@@ -170,7 +170,7 @@ int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const 
   const int L = kappa_f64 ? 1 : pl->lanes_list;
   kinds &= pl->kinds;
   if (L != 16 || precision != ESIM_GRAM_F64 || kinds == 0)
-    return launch(list_args(pl, t, worklist, count, n_out, L, -1, false), L);
+    return launch(list_args(pl, t, worklist, count, n_out, L, 0, false), L);
   // clips of several kinds: a launch for each, over the same list
   for (int k = 0; k < esim::kListKinds; ++k)
     if ((kinds >> k) & 1u) {
@@ -395,7 +395,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     std::vector<int64_t> first(static_cast<size_t>(esim::kDenseSets) * nclips);
     for (int c = 0; c < nclips; ++c) {
       auto& cd = pl->host[c];
-      const esim::ClipRoute rt = esim::clip_route(cd.W, cd.H, cd.F, cd.r, cd.tr, pl->shape.cus);
+      const esim::ClipRoute rt = esim::clip_route(cd.W, cd.H, cd.F, cd.r, cd.tr, cd.ridge, pl->shape.cus);
       for (int set = 0; set < esim::kDenseSets; ++set) {
         first[static_cast<size_t>(set) * nclips + c] = pl->dense_groups[set];
         pl->dense_groups[set] += esim::dense_groups(set, rt, cd.W, cd.H);

@@ -396,7 +396,7 @@ hipError_t launch_backward(const BackwardArgs& a, hipStream_t s) {
   const RegressTable* t = regress_table(F);
   AdjointArgs adj{};
   adj.reg = a.reg;
-  const AdjointFn fn = t ? t->adjoint[adj.reg.single ? 0 : 1][hc.feat_f16 != 0] : nullptr;
+  const AdjointFn fn = t ? t->adjoint[adj.reg.kind][hc.feat_f16 != 0] : nullptr;
   GatherFn gat = pick_gather(F);
   RedFn rb = pick_red(D);
   if (!fn || !gat || !rb) return hipErrorInvalidValue;

@@ -11,7 +11,7 @@
 namespace esim {
 namespace {
 
-template <int F, int L, bool F16, bool SINGLE>
+template <int F, int L, bool F16, int KIND>
 __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
 __attribute__((amdgpu_waves_per_eu(regress_waves_per_simd(F, false))))
 adjoint_kernel(AdjointArgs b) {
@@ -34,7 +34,7 @@ adjoint_kernel(AdjointArgs b) {
       int64_t pix, idx;
       const bool valid = group_item<L>(a, queue.group(k), slot, n_items, cl, pix, t, idx) && b.g_alpha[idx] != 0.0f;
       double* to = parked + (static_cast<int>(k - k0) * G + slot) * R::STRIDE + j;
-      park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to);
+      park_group<F, L, F16, KIND>(a, valid, cl, pix, t, j, to);
     }
     __syncthreads();
     const int i = threadIdx.x;

@@ -49,7 +49,7 @@ hipError_t launch_bandwidth(const BandwidthArgs& b, int F, bool f16, int lanes, 
   const RegressArgs& a = b.reg;
   const RegressTable* t = regress_table(F);
   const BandwidthFn k = !t            ? nullptr
-                        : lanes == 16 ? t->bandwidth[a.single ? 2 : 3][f16]
+                        : lanes == 16 ? t->bandwidth_list[a.kind][f16]
                                       : t->bandwidth[a.tile_units ? 0 : 1][f16];
   if (!k) return hipErrorInvalidValue;
   return launch_groups(reinterpret_cast<const void*>(k), const_cast<BandwidthArgs*>(&b), a, F,

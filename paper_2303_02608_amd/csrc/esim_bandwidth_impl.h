@@ -102,7 +102,7 @@ bandwidth_dense_kernel(BandwidthArgs b) {
 
 // Work lists and small frames: the list regression's rounds, once per candidate; the thread that
 // solves an item keeps its best SURE.
-template <int F, bool F16, bool SINGLE>
+template <int F, bool F16, int KIND>
 __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
 __attribute__((amdgpu_waves_per_eu(regress_waves_per_simd(F, false))))
 bandwidth_list_kernel(BandwidthArgs b) {
@@ -130,7 +130,7 @@ bandwidth_list_kernel(BandwidthArgs b) {
         int64_t pix, idx;
         const bool valid = group_item<L>(a, queue.group(k0 + q), slot, n_items, cl, pix, t, idx);
         double* to = parked + (static_cast<int>(q) * G + slot) * R::STRIDE + j;
-        park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to, uni(b.scale[k] * b.scale[k]));
+        park_group<F, L, F16, KIND>(a, valid, cl, pix, t, j, to, uni(b.scale[k] * b.scale[k]));
       }
       __syncthreads();
       if (threadIdx.x == 0) *queue.taken = static_cast<int>(blockDim.x / kWave);

@@ -190,7 +190,7 @@ struct RegressArgs {
   int32_t update_state;     // write each item's model into its clip state (Sec. 2.2)
   const int64_t* xcd_bounds;  // dense multi-clip launches: [nxcd + 1] group bounds per XCD (device)
   int32_t nxcd;               // XCDs of the device (group-to-XCD mapping)
-  int32_t single;             // 16 lanes per item: the instance of kListSingle clips
+  int32_t kind;               // 16 lanes per item: ListKind of the instance
   int32_t tile_units;         // dense tiles: 16-byte units of a wave's LDS (0: groups of lanes, no tiles)
 };
 
@@ -202,15 +202,16 @@ using AdjointFn = void (*)(AdjointArgs);
 struct BandwidthArgs;
 using BandwidthFn = void (*)(BandwidthArgs);
 
-// Regression kernels of one feature count: FP64 Gram [lanes 1, 2, 4, 8, 16][f16],
+// Regression kernels of one feature count: FP64 Gram [lanes 1, 2, 4, 8][f16] and 16 [ListKind][f16],
 // compensated FP32 [lanes 4, 16][f16] (null where not compiled).
 struct RegressTable {
-  KernelFn general[5][2] = {};
-  KernelFn single[2] = {};     // 16 lanes per item, windows of one turn of uncut columns (walk_parts)
+  KernelFn general[4][2] = {};
+  KernelFn list[kListKinds][2] = {};
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item
-  BandwidthFn bandwidth[4][2] = {};   // dense tiles, dense from memory, lists (single column), lists
-  AdjointFn adjoint[2][2] = {};       // 16 lanes per item, single column or any window
+  BandwidthFn bandwidth[2][2] = {};   // dense tiles, dense from memory
+  BandwidthFn bandwidth_list[kListKinds][2] = {};   // 16 lanes per item
+  AdjointFn adjoint[kListKinds][2] = {};            // 16 lanes per item
   KernelFn tile[2] = {};       // FP64 Gram, one lane per item, dense, windows in LDS
 };
 

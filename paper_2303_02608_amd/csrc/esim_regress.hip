@@ -41,9 +41,10 @@ const RegressTable* regress_table(int F) { return make_table(F); }
 
 namespace {
 
-KernelFn pick(int F, int lanes, bool f16) {
+KernelFn pick(int F, int lanes, int kind, bool f16) {
   const RegressTable* t = regress_table(F);
-  const int li = lanes == 1 ? 0 : lanes == 2 ? 1 : lanes == 4 ? 2 : lanes == 8 ? 3 : lanes == 16 ? 4 : -1;
+  const int li = lanes == 1 ? 0 : lanes == 2 ? 1 : lanes == 4 ? 2 : lanes == 8 ? 3 : -1;
+  if (t && lanes == 16) return t->list[kind][f16];
   return (t && li >= 0) ? t->general[li][f16] : nullptr;
 }
 
@@ -57,7 +58,7 @@ KernelFn pick_c32(int F, int lanes, bool f16) {
 
 bool regress_supports(int F, int lanes, int precision) {
   if (precision == ESIM_GRAM_F32C) return pick_c32(F, lanes, false) != nullptr;
-  return pick(F, lanes, false) != nullptr;
+  return pick(F, lanes, kListParts, false) != nullptr;
 }
 
 hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, int lanes,
@@ -69,8 +70,7 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
   KernelFn fn = c32          ? pick_c32(F, lanes, f16)
                 : a.kappa    ? (tab ? tab->kappa[f16] : nullptr)
                 : a.tile_units ? (tab ? tab->tile[f16] : nullptr)
-                : lanes == 16 && a.single ? (tab ? tab->single[f16] : nullptr)
-                             : pick(F, lanes, f16);
+                             : pick(F, lanes, a.kind, f16);
   if (!fn) return hipErrorInvalidValue;
   // Tiles and the instances of 4 lanes and more hand out their groups themselves;
   // the others stride over them with the resident blocks (more would only start

@@ -185,7 +185,7 @@ __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, i
                                              int j, Fn&& fn, double wscale = 1.0) {
   group_rounds<F, F16>(a, valid, my_cl, my_pix, my_t, wscale,
                        [&](const ClipDev& C, const WalkGeom<F, F16>& geo, bool active, int64_t pix, int t) {
-    ColumnSums<F> c;
+    CellSums<F> c;
     LaneSums<F> ls;
     walk_window<F, L, F16>(geo, j, c, ls);
     Gram<F, double> got;
@@ -244,14 +244,14 @@ struct ListRound {
 
 // Walks the items of a group and parks their totals: lane j's share of item
 // `slot` goes to to[q L], to being the lane's place in the item's parking space.
-template <int F, int L, bool F16, bool SINGLE>
+template <int F, int L, bool F16, int KIND>
 __device__ __forceinline__ void park_group(const RegressArgs& a, bool valid, int cl, int64_t pix, int t, int j,
                                            double* to, double wscale = 1.0) {
   using R = ListRound<F, L>;
   const int lane = threadIdx.x & (kWave - 1);
   group_rounds<F, F16>(a, valid, cl, pix, t, wscale,
                        [&](const ClipDev&, const WalkGeom<F, F16>& geo, bool active, int64_t, int) {
-    walk_parts<F, L, F16, SINGLE>(geo, j, [&](Gram<F, double>& got, bool first) {
+    walk_parts<F, L, F16, KIND>(geo, j, [&](Gram<F, double>& got, bool first) {
       double s[R::NE];
       int e = 0;
       got.each([&](double& v) { s[e++] = v; });
@@ -271,7 +271,7 @@ __device__ __forceinline__ void parked_gram(const double* at, Gram<F, double>& g
   gm.each([&](double& v) { v = at[total_pos<L>(e++)]; });
 }
 
-template <int F, int L, bool F16, bool SINGLE = false>
+template <int F, int L, bool F16, int KIND>
 __global__ void __launch_bounds__(256 * regress_waves_per_simd(F, false))
 __attribute__((amdgpu_waves_per_eu(regress_waves_per_simd(F, false))))
 regress_list_kernel(RegressArgs a) {
@@ -296,7 +296,7 @@ regress_list_kernel(RegressArgs a) {
       int64_t pix, idx;
       const bool valid = group_item<L>(a, queue.group(k), slot, n_items, cl, pix, t, idx);
       double* to = parked + (static_cast<int>(k - k0) * G + slot) * R::STRIDE + j;
-      park_group<F, L, F16, SINGLE>(a, valid, cl, pix, t, j, to);
+      park_group<F, L, F16, KIND>(a, valid, cl, pix, t, j, to);
     }
     __syncthreads();
     const int i = threadIdx.x;

@@ -13,34 +13,36 @@
 
 namespace esim {
 
+// The instances of 16 lanes per item of one ListKind.
+template <int F, int KIND>
+void list_kernels(RegressTable& t) {
+  t.list[KIND][0] = regress_list_kernel<F, 16, false, KIND>;
+  t.list[KIND][1] = regress_list_kernel<F, 16, true, KIND>;
+  t.bandwidth_list[KIND][0] = bandwidth_list_kernel<F, false, KIND>;
+  t.bandwidth_list[KIND][1] = bandwidth_list_kernel<F, true, KIND>;
+  t.adjoint[KIND][0] = adjoint_kernel<F, 16, false, KIND>;
+  t.adjoint[KIND][1] = adjoint_kernel<F, 16, true, KIND>;
+}
+
 void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   constexpr int F = ESIM_REGRESS_F;
   t.general[0][0] = regress_kernel<F, 1, false, false>;
   t.general[0][1] = regress_kernel<F, 1, true, false>;
   t.general[1][0] = regress_kernel<F, 2, false, false>;
   t.general[1][1] = regress_kernel<F, 2, true, false>;
-  t.general[2][0] = regress_list_kernel<F, 4, false>;
-  t.general[2][1] = regress_list_kernel<F, 4, true>;
-  t.general[3][0] = regress_list_kernel<F, 8, false>;
-  t.general[3][1] = regress_list_kernel<F, 8, true>;
-  t.general[4][0] = regress_list_kernel<F, 16, false>;
-  t.general[4][1] = regress_list_kernel<F, 16, true>;
-  t.single[0] = regress_list_kernel<F, 16, false, true>;
-  t.single[1] = regress_list_kernel<F, 16, true, true>;
+  t.general[2][0] = regress_list_kernel<F, 4, false, kListExact>;
+  t.general[2][1] = regress_list_kernel<F, 4, true, kListExact>;
+  t.general[3][0] = regress_list_kernel<F, 8, false, kListExact>;
+  t.general[3][1] = regress_list_kernel<F, 8, true, kListExact>;
+  list_kernels<F, kListParts>(t);
+  list_kernels<F, kListSingle>(t);
+  list_kernels<F, kListExact>(t);
   t.tile[0] = regress_tile_kernel<F, false>;
   t.tile[1] = regress_tile_kernel<F, true>;
   t.bandwidth[0][0] = bandwidth_tile_kernel<F, false>;
   t.bandwidth[0][1] = bandwidth_tile_kernel<F, true>;
   t.bandwidth[1][0] = bandwidth_dense_kernel<F, false>;
   t.bandwidth[1][1] = bandwidth_dense_kernel<F, true>;
-  t.bandwidth[2][0] = bandwidth_list_kernel<F, false, true>;
-  t.bandwidth[2][1] = bandwidth_list_kernel<F, true, true>;
-  t.bandwidth[3][0] = bandwidth_list_kernel<F, false, false>;
-  t.bandwidth[3][1] = bandwidth_list_kernel<F, true, false>;
-  t.adjoint[0][0] = adjoint_kernel<F, 16, false, true>;
-  t.adjoint[0][1] = adjoint_kernel<F, 16, true, true>;
-  t.adjoint[1][0] = adjoint_kernel<F, 16, false, false>;
-  t.adjoint[1][1] = adjoint_kernel<F, 16, true, false>;
   t.kappa[0] = regress_kernel<F, 1, false, false, true>;
   t.kappa[1] = regress_kernel<F, 1, true, false, true>;
   // the compensated-FP32 variant is compiled for the feature counts of the

@@ -47,8 +47,12 @@ constexpr int64_t tile_count(int W, int H, int lw) {
   return static_cast<int64_t>((W + (1ll << lw) - 1) >> lw) * ((H + (kWave >> lw) - 1) / (kWave >> lw));
 }
 
-// How the 16-lane instances walk a clip's windows (walk_parts).
-enum ListKind { kListParts = 0, kListSingle = 1, kListKinds = 2 };
+// How the 16-lane instances walk a clip's windows and sum their moments (walk_parts,
+// RunSums, CellSums).
+enum ListKind { kListParts = 0, kListSingle, kListExact, kListKinds };
+// Ridges below this take the instance with exact moments: down to here the others'
+// error is at most 4e-9 of the ridge.
+constexpr double kExactRidge = 1e-7;
 
 struct ClipRoute {
   int tile_lw;        // log2 of the tiles' width
@@ -57,7 +61,7 @@ struct ClipRoute {
   int kind;           // ListKind
 };
 
-inline ClipRoute clip_route(int W, int H, int F, int r, int tr, int cus) {
+inline ClipRoute clip_route(int W, int H, int F, int r, int tr, double ridge, int cus) {
   ClipRoute c{};
   // tiles of 64, 32 or 16 columns: of those whose rows are loaded in at most two
   // turns of a wave's lanes and whose ring fits LDS, the one that covers the image
@@ -80,46 +84,41 @@ inline ClipRoute clip_route(int W, int H, int F, int r, int tr, int cus) {
   c.few = tile_count(W, H, c.tile_lw) < 4ll * cus;
   // 9 to 15 columns are one uncut turn of 16 lanes; narrower windows fill the lanes
   // better cut into parts (65536 items at r = 3: 84 us, uncut 98)
-  c.kind = r >= 4 && r <= 7 && tr <= 1 ? kListSingle : kListParts;
+  c.kind = ridge < kExactRidge ? kListExact : r >= 4 && r <= 7 && tr <= 1 ? kListSingle : kListParts;
   return c;
 }
 
 // Dense launches: the clips that one takes, and their instance.  Of the automatic
-// schedule: kDenseFewSingle and the ones after it.
+// schedule: kDenseFew and the ones after it.
 enum DenseSet {
   kDenseLanes = 0,        // + lanes_index(L): every clip, L lanes per item
   kDenseTile = 5,         // one lane per item set by hand: clips whose tiles fit
   kDenseMemory,           //   the others, windows from memory
-  kDense16Single,         // 16 lanes set by hand: clips of a ListKind
-  kDense16Parts,
-  kDenseFewSingle,        // few: 16 lanes, by ListKind
-  kDenseFewParts,
-  kDenseAutoTile,         // not few: tiles, or from memory
+  kDense16,               // + ListKind: 16 lanes set by hand
+  kDenseFew = kDense16 + kListKinds,         // + ListKind: few, 16 lanes
+  kDenseAutoTile = kDenseFew + kListKinds,   // not few: tiles, or from memory
   kDenseAutoMemory,
   kDenseSets
 };
 
 inline bool dense_member(int set, const ClipRoute& c) {
-  const bool single = c.kind == kListSingle;
-  switch (set) {
-    case kDenseTile: return c.tiles;
-    case kDenseMemory: return !c.tiles;
-    case kDense16Single: return single;
-    case kDense16Parts: return !single;
-    case kDenseFewSingle: return c.few && single;
-    case kDenseFewParts: return c.few && !single;
-    case kDenseAutoTile: return !c.few && c.tiles;
-    case kDenseAutoMemory: return !c.few && !c.tiles;
-    default: return true;
-  }
+  if (set < kDenseTile) return true;
+  if (set >= kDense16 && set < kDenseFew) return c.kind == set - kDense16;
+  if (set >= kDenseFew && set < kDenseAutoTile) return c.few && c.kind == set - kDenseFew;
+  const bool tiles = set == kDenseTile || set == kDenseAutoTile;
+  return c.tiles == tiles && !(set >= kDenseAutoTile && c.few);
 }
 
 constexpr bool dense_tiles(int set) { return set == kDenseTile || set == kDenseAutoTile; }
 constexpr int dense_set_lanes(int set) {
-  return set < kDenseTile ? 1 << set
-         : dense_tiles(set) || set == kDenseMemory || set == kDenseAutoMemory ? 1 : 16;
+  return set < kDenseTile ? 1 << set : set >= kDense16 && set < kDenseAutoTile ? 16 : 1;
 }
-constexpr bool dense_single(int set) { return set == kDense16Single || set == kDenseFewSingle; }
+// ListKind of a set of 16 lanes per item.
+constexpr int dense_kind(int set) {
+  return set >= kDenseFew && set < kDenseAutoTile ? set - kDenseFew
+         : set >= kDense16 && set < kDenseFew     ? set - kDense16
+                                                  : 0;
+}
 
 // Groups of a clip's pixels in a dense launch: tiles, or 64 / L pixels.
 inline int64_t dense_groups(int set, const ClipRoute& c, int W, int H) {

@@ -223,15 +223,24 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
 // from dy = -r to r, the frames of a row innermost, so that both coordinates
 // are constant over the 2 tr + 1 samples of a cell (dx, dy).  No entry with a
 // coordinate factor is summed per sample:
-//   v_y  the running column sums C_k of (w, w y, w f) after cell k are added up
-//        once per cell, P = sum_k C_k; a cell at dy is then counted r + 1 - dy
-//        times, so sum dy s = (r + 1) C - P, and with PP = sum_k P_k
-//        sum dy^2 s = (r + 1)^2 C - (2 r + 3) P + 2 PP;
-//   v_x  constant in the column: a factor of the column's sums.
-// A cell at tr = 1 spends 10 adds there, where one row of samples at a time
-// spent 11 fused multiply-adds and a multiply per sample.  The sums grow to
-// 2 r + 1 times the totals, so the differences keep an error of the order of
-// 2^-53 in the W-normalised, bandwidth-scaled system.
+//   v_x  constant in the column: a factor of the column's sums;
+//   v_y  CellSums: a cell's (w, w y, w f) are summed by themselves and go, once per
+//        cell, to the column's sums and, times the row, to its moments;
+//        RunSums: the running column sums C_k after cell k are added up once per
+//        cell, P = sum_k C_k; a cell at dy, e rows before the walk's end, is then
+//        counted e - dy times, so sum dy s = e C - P, and with PP = sum_k P_k
+//        sum dy^2 s = e^2 C - (2 e + 1) P + 2 PP.
+// A cell at tr = 1 and F = 7 spends 19 instructions there less the 9 adds that its
+// first sample saves (CellSums), or 10 adds, where one row of samples at a time
+// spent 11 fused multiply-adds and a multiply per sample.
+//
+// CellSums round a moment to 2^-53 or so of itself.  RunSums let the centre row's
+// weight, up to the whole of W, cancel to zero: a moment (of the W-normalised,
+// bandwidth-scaled system) keeps an error of about 4e-16 / (h b)^2.  That is the
+// ridge's own scale: it acts as a ridge changed by 4e-16.  The dense walks take
+// CellSums, which cost them nothing; in the lists' 256 registers the cell's own sums
+// cost 10 % (F = 7, r = 7, 100 000 items 250 -> 277 us, 2000 items 18 -> 23), so they
+// take RunSums unless the ridge is small (kExactRidge).
 //
 // Samples outside the image read the nearest pixel inside it, which lies in
 // the window too (so a NaN there counts where it counts anyway), and get
@@ -240,31 +249,30 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
 
 constexpr double kDropped = -65536.0;    // exponent (base 2) of a sample of weight 0
 
-// Sums of one column (the last line: of all columns of a lane).
+// Sums of products without a coordinate, over all of a lane's samples.
 template <int F>
-struct ColumnSums {
+struct ProductSums {
   static constexpr int NA = F * (F + 1) / 2;
-  double W, g, f[F];               // running column sums of w, w y, w f
-  double PW, Pg, Pf[F], PPW;       // their sums over the cells, and the sums of PW
   double Syy, gf[F], Aff[NA];
 
   __device__ __forceinline__ void zero() {
-    W = g = PW = Pg = PPW = Syy = 0;
+    Syy = 0;
 #pragma unroll
-    for (int k = 0; k < F; ++k) f[k] = Pf[k] = gf[k] = 0;
+    for (int k = 0; k < F; ++k) gf[k] = 0;
 #pragma unroll
     for (int k = 0; k < NA; ++k) Aff[k] = 0;
   }
-  __device__ __forceinline__ void add(double w, double yd, const double (&v)[F]) {
+  // Adds a sample; sink(k, wz) takes w y (k = -1) and w f_k.
+  template <class Sink>
+  __device__ __forceinline__ void add(double w, double yd, const double (&v)[F], Sink&& sink) {
     const double wy = w * yd;
-    W += w;
-    g += wy;
+    sink(-1, wy);
     Syy = fma(wy, yd, Syy);
     int q = 0;
 #pragma unroll
     for (int k = 0; k < F; ++k) {
       const double wz = w * v[k];
-      f[k] += wz;
+      sink(k, wz);
       gf[k] = fma(wz, yd, gf[k]);
 #pragma unroll
       for (int e = k; e < F; ++e) {
@@ -273,7 +281,62 @@ struct ColumnSums {
       }
     }
   }
-  __device__ __forceinline__ void end_cell() {
+};
+
+template <int F>
+struct CellSums {
+  double cW, cg, cf[F];            // of the cell: w, w y, w f
+  double W, g, f[F], YW;           // of the line, and the first moment of w along it
+  double YY, Yg, Yf[F];            // of all lines: the second moment of w, the first of w y, w f
+  ProductSums<F> p;
+
+  __device__ __forceinline__ void zero() {
+    W = g = YW = YY = Yg = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) f[k] = Yf[k] = 0;
+    p.zero();
+  }
+  // A sample; `first` of its cell (a constant after unrolling).
+  __device__ __forceinline__ void add(double w, double yd, const double (&v)[F], bool first) {
+    cW = first ? w : cW + w;
+    p.add(w, yd, v, [&](int k, double wz) {
+      double& c = k < 0 ? cg : cf[k < 0 ? 0 : k];
+      c = first ? wz : c + wz;
+    });
+  }
+  // The cell at d along the line is complete.
+  __device__ __forceinline__ void end_cell(int di) {
+    const double d = static_cast<double>(di), dW = d * cW;
+    W += cW;
+    YW += dW;
+    YY = fma(d, dW, YY);
+    g += cg;
+    Yg = fma(d, cg, Yg);
+#pragma unroll
+    for (int k = 0; k < F; ++k) {
+      f[k] += cf[k];
+      Yf[k] = fma(d, cf[k], Yf[k]);
+    }
+  }
+};
+
+template <int F>
+struct RunSums {
+  double W, g, f[F];               // running sums of w, w y, w f
+  double PW, Pg, Pf[F], PPW;       // their sums over the cells, and the sums of PW
+  ProductSums<F> p;
+
+  __device__ __forceinline__ void zero() {
+    W = g = PW = Pg = PPW = 0;
+#pragma unroll
+    for (int k = 0; k < F; ++k) f[k] = Pf[k] = 0;
+    p.zero();
+  }
+  __device__ __forceinline__ void add(double w, double yd, const double (&v)[F], bool) {
+    W += w;
+    p.add(w, yd, v, [&](int k, double wz) { (k < 0 ? g : f[k < 0 ? 0 : k]) += wz; });
+  }
+  __device__ __forceinline__ void end_cell(int) {
     PW += W;
     PPW += PW;
     Pg += g;
@@ -282,39 +345,34 @@ struct ColumnSums {
   }
 };
 
-// What the finished lines of a lane add up to: the sums, their first moment along
-// the walk (Y, and YY of W) and both times the line's coordinate (X).
+// What the finished lines of a lane add up to: the sums, and the lines' coordinate
+// (X) times them; YW as in CellSums, XY its moment with the lines' coordinate.
 template <int F>
 struct LaneSums {
-  double W, g, f[F], YW, YY, Yg, Yf[F];
+  double W, g, f[F], YW;
   double XW, XX, Xg, Xf[F], XY;
 
   __device__ __forceinline__ void zero() {
-    W = g = YW = YY = Yg = XW = Xg = XX = XY = 0;
+    W = g = YW = XW = Xg = XX = XY = 0;
 #pragma unroll
-    for (int k = 0; k < F; ++k) f[k] = Yf[k] = Xf[k] = 0;
+    for (int k = 0; k < F; ++k) f[k] = Xf[k] = 0;
   }
   // Takes over the line at coordinate x and clears its part of c (the sums
-  // without a coordinate factor stay in c).  The walk ended at e: its cells lay at
-  // e - n .. e - 1 in steps of the walked coordinate.
-  __device__ __forceinline__ void end_line(ColumnSums<F>& c, double x, double e) {
-    const double yw = fma(e, c.W, -c.PW);
+  // without a line's coordinate stay in c).
+  __device__ __forceinline__ void end_line(CellSums<F>& c, double x) {
     W += c.W;
     XW = fma(x, c.W, XW);
     XX = fma(x * x, c.W, XX);
-    YW += yw;
-    XY = fma(x, yw, XY);
-    YY += fma(e * e, c.W, fma(-(2.0 * e + 1.0), c.PW, 2.0 * c.PPW));
+    YW += c.YW;
+    XY = fma(x, c.YW, XY);
     g += c.g;
     Xg = fma(x, c.g, Xg);
-    Yg += fma(e, c.g, -c.Pg);
-    c.W = c.g = c.PW = c.PPW = c.Pg = 0;
+    c.W = c.g = c.YW = 0;
 #pragma unroll
     for (int k = 0; k < F; ++k) {
       f[k] += c.f[k];
       Xf[k] = fma(x, c.f[k], Xf[k]);
-      Yf[k] += fma(e, c.f[k], -c.Pf[k]);
-      c.f[k] = c.Pf[k] = 0;
+      c.f[k] = 0;
     }
   }
 };
@@ -373,8 +431,8 @@ __device__ __forceinline__ void make_walk(WalkGeom<F, F16>& g, const ClipDev& C,
 // c.  DEPTH (1 or 2) cells of samples are loaded ahead: a sample's registers are
 // reloaded as soon as it is used.  PART: only the n rows from s0 on (s0 >= -r may
 // differ between the lanes; rows below r get weight 0).
-template <int F, bool F16, int R, int DEPTH = 1, bool PART = false>
-__device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, ColumnSums<F>& c,
+template <int F, bool F16, int R, int DEPTH = 1, bool PART = false, class Sums>
+__device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, int k0, Sums& c,
                                             int s0 = 0, int n = 0) {
   constexpr uint32_t ES = WalkGeom<F, F16>::ES;
   const double K = g.kexp;
@@ -425,9 +483,9 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
       const double w = static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(arg)));
       const double yd = static_cast<double>(ys[d][i]);
       load(d, i);
-      c.add(w, yd, v);
+      c.add(w, yd, v, i == 0);
     }
-    c.end_cell();
+    c.end_cell(dy);
   };
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) {
@@ -462,7 +520,7 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
 // The columns j, j + L, ... of the lane's item, up to three frames at a time; the
 // totals go to c (entries without a coordinate) and ls.
 template <int F, int L, bool F16>
-__device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, ColumnSums<F>& c, LaneSums<F>& ls) {
+__device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, CellSums<F>& c, LaneSums<F>& ls) {
   c.zero();
   ls.zero();
 #pragma unroll 1
@@ -474,7 +532,7 @@ __device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, Co
       if (left >= 3) walk_frames<F, F16, 3>(g, d0 + j, k0, c);
       else if (left == 2) walk_frames<F, F16, 2>(g, d0 + j, k0, c);
       else walk_frames<F, F16, 1>(g, d0 + j, k0, c);
-      ls.end_line(c, vx, static_cast<double>(g.r + 1));
+      ls.end_line(c, vx);
     }
   }
 }
@@ -486,7 +544,7 @@ __device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, Co
 // reading in its own LDS, one record of all channels per pixel: (frames of a
 // cell) x (features and y), single precision, in 16-byte units.  A lane walks its
 // window row by row, so a step of the walk is one record further; the walked
-// coordinate of ColumnSums is v_x here and the lines' one is v_y.  The rows are a
+// coordinate of CellSums is v_x here and the lines' one is v_y.  The rows are a
 // ring as high as the tile; a new row replaces the one that left.
 //
 // Read straight from memory, a sample is 8 loads at F = 7, and 64 lanes' window
@@ -612,7 +670,7 @@ __device__ __forceinline__ void stage_row(const TileGeom<F, F16>& g, float4* lds
 
 // Walks R frames (from the window's k0-th on) of the windows of the wave's pixels.
 template <int F, bool F16, int R>
-__device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* lds, int k0, ColumnSums<F>& c,
+__device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* lds, int k0, CellSums<F>& c,
                                             LaneSums<F>& ls) {
   const double K = g.kexp;
   constexpr int NQ = tile_quads(F), U = tile_units(F, R);
@@ -674,12 +732,12 @@ __device__ __forceinline__ void tile_frames(const TileGeom<F, F16>& g, float4* l
         const double yd = static_cast<double>(ch[F]);
 #pragma unroll
         for (int k = 0; k < NQ; ++k) q[k] = at[(i + 1 < R ? (i + 1) * NQ : U) + k];
-        c.add(w, yd, v);
+        c.add(w, yd, v, i == 0);
       }
       at += U;
-      c.end_cell();
+      c.end_cell(dx);
     }
-    ls.end_line(c, vy, static_cast<double>(r + 1));
+    ls.end_line(c, vy);
     wave_lds_order();
     next = next + 1 == TH ? 0 : next + 1;
     slot = slot + 1 == TH ? 0 : slot + 1;
@@ -756,52 +814,67 @@ struct Gram {
 // Totals of the lane's part of its item from its walk: along columns (v_y is the
 // walked coordinate, steps of s, and v_x the lines' one) or, ROWS, along rows.
 template <int F, bool ROWS = false>
-__device__ __forceinline__ void gram_of_lane(const ColumnSums<F>& c, const LaneSums<F>& l, double s,
+__device__ __forceinline__ void gram_of_lane(const CellSums<F>& c, const LaneSums<F>& l, double s,
                                              Gram<F, double>& G) {
   G.SW = l.W;
   G.g0 = l.g;
-  G.Syy = c.Syy;
+  G.Syy = c.p.Syy;
   G.A0x = ROWS ? s * l.YW : l.XW;
   G.A0y = ROWS ? l.XW : s * l.YW;
-  G.Axx = ROWS ? s * s * l.YY : l.XX;
-  G.Ayy = ROWS ? l.XX : s * s * l.YY;
-  G.gx = ROWS ? s * l.Yg : l.Xg;
-  G.gy = ROWS ? l.Xg : s * l.Yg;
+  G.Axx = ROWS ? s * s * c.YY : l.XX;
+  G.Ayy = ROWS ? l.XX : s * s * c.YY;
+  G.gx = ROWS ? s * c.Yg : l.Xg;
+  G.gy = ROWS ? l.Xg : s * c.Yg;
   G.Axy = s * l.XY;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
     G.A0f[f] = l.f[f];
-    G.gf[f] = c.gf[f];
-    G.Axf[f] = ROWS ? s * l.Yf[f] : l.Xf[f];
-    G.Ayf[f] = ROWS ? l.Xf[f] : s * l.Yf[f];
+    G.gf[f] = c.p.gf[f];
+    G.Axf[f] = ROWS ? s * c.Yf[f] : l.Xf[f];
+    G.Ayf[f] = ROWS ? l.Xf[f] : s * c.Yf[f];
   }
 #pragma unroll
-  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
+  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.p.Aff[k];
 }
 
-// The same for one column or part of it, at v_x; its walk ended at e (steps of s).
+// The moments of one column or part of it; its walk ended at e.
 template <int F>
-__device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx, double s, double e,
-                                               Gram<F, double>& G) {
+struct ColumnMoments {
+  double Y, YY, Yg, Yf[F];
+  __device__ __forceinline__ ColumnMoments(const RunSums<F>& c, double e)
+      : Y(fma(e, c.W, -c.PW)), YY(fma(e * e, c.W, fma(-(2.0 * e + 1.0), c.PW, 2.0 * c.PPW))), Yg(fma(e, c.g, -c.Pg)) {
+#pragma unroll
+    for (int f = 0; f < F; ++f) Yf[f] = fma(e, c.f[f], -c.Pf[f]);
+  }
+  __device__ __forceinline__ ColumnMoments(const CellSums<F>& c, double) : Y(c.YW), YY(c.YY), Yg(c.Yg) {
+#pragma unroll
+    for (int f = 0; f < F; ++f) Yf[f] = c.Yf[f];
+  }
+};
+
+// The same for one column or part of it, at v_x.
+template <int F, class Sums>
+__device__ __forceinline__ void gram_of_column(const Sums& c, double vx, double s, double e, Gram<F, double>& G) {
+  const ColumnMoments<F> m(c, e);
   G.SW = c.W;
   G.g0 = c.g;
-  G.Syy = c.Syy;
+  G.Syy = c.p.Syy;
   G.A0x = vx * c.W;
   G.Axx = vx * G.A0x;
   G.gx = vx * c.g;
-  G.A0y = s * fma(e, c.W, -c.PW);
-  G.Ayy = s * s * fma(e * e, c.W, fma(-(2.0 * e + 1.0), c.PW, 2.0 * c.PPW));
+  G.A0y = s * m.Y;
+  G.Ayy = s * s * m.YY;
   G.Axy = vx * G.A0y;
-  G.gy = s * fma(e, c.g, -c.Pg);
+  G.gy = s * m.Yg;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
     G.A0f[f] = c.f[f];
-    G.gf[f] = c.gf[f];
+    G.gf[f] = c.p.gf[f];
     G.Axf[f] = vx * c.f[f];
-    G.Ayf[f] = s * fma(e, c.f[f], -c.Pf[f]);
+    G.Ayf[f] = s * m.Yf[f];
   }
 #pragma unroll
-  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.Aff[k];
+  for (int k = 0; k < Gram<F, double>::NA; ++k) G.Aff[k] = c.p.Aff[k];
 }
 
 // The Gram of the window of the lane's pixel.  The sums of each count of frames
@@ -814,7 +887,7 @@ __device__ __forceinline__ void gram_of_column(const ColumnSums<F>& c, double vx
 template <int F, bool F16>
 __device__ __forceinline__ void tile_gram(const TileGeom<F, F16>& g, float4* lds, Gram<F, double>& G) {
   auto whole = [&](auto frames) {
-    ColumnSums<F> c;
+    CellSums<F> c;
     LaneSums<F> ls;
     c.zero();
     ls.zero();
@@ -828,7 +901,7 @@ __device__ __forceinline__ void tile_gram(const TileGeom<F, F16>& g, float4* lds
   else if (MAX >= 2 && g.nt == 2) whole(std::integral_constant<int, MAX >= 2 ? 2 : 1>{});
   else if (MAX >= 2 && g.nt == 1) whole(std::integral_constant<int, 1>{});
   else {
-    ColumnSums<F> c;
+    CellSums<F> c;
     LaneSums<F> ls;
     c.zero();
     ls.zero();
@@ -916,20 +989,20 @@ __host__ __device__ constexpr int total_pos(int e) {
 // than L columns are left (q), each is cut into L / q parts of equal height, one
 // lane each, so that the last turn is as short as the lanes allow: at r = 9,
 // 16 lanes walk 19 rows of 16 columns and then 4 rows of the last 3 columns (5
-// lanes a column).  SINGLE: one turn of uncut columns (L / 2 < 2 r + 1 <= L, at
+// lanes a column).  kListSingle: one turn of uncut columns (L / 2 < 2 r + 1 <= L, at
 // most three frames).  With whole columns in every turn, sums kept in registers
 // between turns and so one row of loads ahead, lists of 65536 / 4096 items (one in
 // eight pixels of a wide image, F = 7, three frames) took 98 / 14 us at r = 3, 392 /
 // 39 at r = 8, 426 / 42 at r = 9 and 537 / 50 at r = 12; now 84 / 14, 282 / 29, 324 /
 // 30 and 500 / 46.  F = 10, r = 10, five frames: 1344 / 95, now 955 / 69.
-template <int F, int L, bool F16, bool SINGLE, class Fn>
+template <int F, int L, bool F16, int KIND, class Fn>
 __device__ __forceinline__ void walk_parts(const WalkGeom<F, F16>& g, int j, Fn&& fn) {
   // two rows ahead where they fit the registers (two waves per SIMD to F = 8, one
   // above): at F = 8, r = 10, five frames, 18000 items spilled to 303 us, 232 with one
-  constexpr int DEPTH = F == 12 || (F == 8 && !SINGLE) ? 1 : 2;
-  ColumnSums<F> c;
+  constexpr int DEPTH = F == 12 || (F == 8 && KIND != kListSingle) ? 1 : 2;
+  std::conditional_t<KIND == kListExact, CellSums<F>, RunSums<F>> c;
   Gram<F, double> got;
-  if constexpr (SINGLE) {
+  if constexpr (KIND == kListSingle) {
     const int dx = j - g.r;
     c.zero();
     if (g.nt == 3) walk_frames<F, F16, 3, DEPTH>(g, dx, 0, c);

@@ -10,8 +10,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 SHIM = """
 #include "esim_schedule.h"
-extern "C" void route(int W, int H, int F, int r, int tr, int cus, int* out) {
-  const esim::ClipRoute c = esim::clip_route(W, H, F, r, tr, cus);
+extern "C" void route(int W, int H, int F, int r, int tr, double ridge, int cus, int* out) {
+  const esim::ClipRoute c = esim::clip_route(W, H, F, r, tr, ridge, cus);
   out[0] = c.tile_lw, out[1] = c.tiles, out[2] = c.few, out[3] = c.kind;
 }
 extern "C" long long tiles(int W, int H, int lw) { return esim::tile_count(W, H, lw); }
@@ -42,9 +42,9 @@ def rules(tmp_path_factory):
         lds, tiles, member = so.lds, so.tiles, so.member
 
         @staticmethod
-        def route(W, H, F, r, tr):
+        def route(W, H, F, r, tr, ridge=1e-6):
             out = (ctypes.c_int * 4)()
-            so.route(W, H, F, r, tr, CUS, out)
+            so.route(W, H, F, r, tr, ctypes.c_double(ridge), CUS, out)
             return dict(zip(("lw", "tiles", "few", "kind"), out))
 
     return Rules
@@ -85,6 +85,6 @@ def test_dense_sets_cover_every_clip_once(rules):
     clip exactly once."""
     for tiles in (0, 1):
         for few in (0, 1):
-            for kind in range(2):
-                for sets in ((5, 6), (7, 8), (9, 10, 11, 12)):
+            for kind in range(3):
+                for sets in ((5, 6), (7, 8, 9), range(10, 15)):
                     assert sum(rules.member(s, tiles, few, kind) for s in sets) == 1
