@@ -17,18 +17,18 @@ struct esim_plan_s {
   int F = 0;
   bool f16 = false;
   std::vector<esim::ClipDev> host;
+  // Descriptors on the device: a table for each DenseSet (its clips' first groups),
+  // then one for the work lists of each ListKind, with the clips of other kinds empty,
+  // so that a launch skips their items.  dev: the first one, of all clips.
   esim::ClipDev* dev = nullptr;
-  // for work lists of clips of several ListKinds: the descriptors with the clips of
-  // the other kinds empty, so that a launch skips their items
-  esim::ClipDev* kind_dev[esim::kListKinds] = {};
+  esim::ClipDev* table(int k) const { return dev + static_cast<int64_t>(k) * nclips; }
   esim::Workspace ws{};
   void* ws_mem = nullptr;
   int64_t npix = 0;
   int64_t nblk = 0;
   int64_t wl_capacity = 0;
   std::vector<esim::ClipRoute> routes;
-  int64_t dense_groups[esim::kDenseSets] = {};
-  int64_t* first_group = nullptr;   // [kDenseSets][nclips] first dense group of each clip (device)
+  int64_t dense_groups[esim::kDenseSets] = {};   // of each set, over its clips
   int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles
   uint32_t kinds = 0;      // bit k: a clip of ListKind k
   int lanes_dense = 1;     // lanes per regression item, dense launches
@@ -115,10 +115,9 @@ int each_dense_set(esim_plan pl, int lanes, Fn&& fn) {
 
 esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
   esim::RegressArgs a{};
-  a.clips = pl->dev;
+  a.clips = pl->table(set);
   a.nclips = pl->nclips;
   a.t = t;
-  a.first_group = pl->first_group + static_cast<int64_t>(set) * pl->nclips;
   a.tile_units = esim::dense_tiles(set) ? pl->tile_units : 0;
   a.n_dense_groups = a.max_groups = pl->dense_groups[set];
   a.n_out = n_out;
@@ -132,7 +131,7 @@ esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
 esim::RegressArgs list_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
                             int L, int kind, bool only) {
   esim::RegressArgs a{};
-  a.clips = only ? pl->kind_dev[kind] : pl->dev;
+  a.clips = only ? pl->table(esim::kDenseSets + kind) : pl->dev;
   a.nclips = pl->nclips;
   a.t = t;
   a.items = worklist;
@@ -392,14 +391,8 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->nblk = blk;
     pl->wl_capacity = wl;
     int64_t seg = 0;
-    std::vector<int64_t> first(static_cast<size_t>(esim::kDenseSets) * nclips);
-    for (int c = 0; c < nclips; ++c) {
-      auto& cd = pl->host[c];
+    for (auto& cd : pl->host) {
       const esim::ClipRoute rt = esim::clip_route(cd.W, cd.H, cd.F, cd.r, cd.tr, cd.ridge, pl->shape.cus);
-      for (int set = 0; set < esim::kDenseSets; ++set) {
-        first[static_cast<size_t>(set) * nclips + c] = pl->dense_groups[set];
-        pl->dense_groups[set] += esim::dense_groups(set, rt, cd.W, cd.H);
-      }
       if (rt.tiles) pl->tile_units = std::max(pl->tile_units, esim::tile_wave_units(cd.F, cd.r, cd.tr, rt.tile_lw));
       cd.tile_lw = rt.tile_lw;
       cd.list_class = rt.kind == esim::kListSingle ? 0 : 1;
@@ -408,25 +401,31 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
       pl->routes.push_back(rt);
     }
     pl->split_seg = seg > 0 && seg < pix ? seg : -1;
+    std::vector<esim::ClipDev> tables;
+    for (int k = 0; k < esim::kDenseSets + esim::kListKinds; ++k)
+      for (int c = 0; c < nclips; ++c) {
+        esim::ClipDev cd = pl->host[c];
+        if (k < esim::kDenseSets) {
+          cd.first_group = pl->dense_groups[k];
+          pl->dense_groups[k] += esim::dense_groups(k, pl->routes[c], cd.W, cd.H);
+        } else if (pl->routes[c].kind != k - esim::kDenseSets) {
+          cd.HW = 0;
+        }
+        tables.push_back(cd);
+      }
 
     // device memory: descriptors + workspace
-    const size_t clip_bytes = sizeof(esim::ClipDev) * nclips;
+    const size_t clip_bytes = sizeof(esim::ClipDev) * tables.size();
     auto align = [](size_t v) { return (v + 255) & ~static_cast<size_t>(255); };
     size_t off = 0;
     const size_t o_clips = off;
     off = align(off + clip_bytes);
-    const bool mixed = (pl->kinds & (pl->kinds - 1)) != 0;
-    const size_t o_kinds = off;
-    const size_t kind_bytes = align(clip_bytes);
-    if (mixed) off += kind_bytes * esim::kListKinds;
     const size_t o_bcount = off;
     off = align(off + sizeof(int64_t) * blk);
     const size_t o_chunk = off;
     off = align(off + sizeof(int64_t) * ((blk + esim::kChunkBlocks - 1) / esim::kChunkBlocks));
     const size_t o_xcd = off;
     off = align(off + sizeof(int64_t) * esim::kDenseSets * (esim::kMaxXcds + 1));
-    const size_t o_first = off;
-    off = align(off + sizeof(int64_t) * first.size());
     const size_t o_flags = off;
     off = align(off + sizeof(uint64_t) * blk * esim::kWavesPerBlock);
     const size_t o_pol = off;
@@ -443,7 +442,6 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     pl->ws.bcount = reinterpret_cast<int64_t*>(m + o_bcount);
     pl->ws.chunk = reinterpret_cast<int64_t*>(m + o_chunk);
     pl->xcd_bounds = reinterpret_cast<int64_t*>(m + o_xcd);
-    pl->first_group = reinterpret_cast<int64_t*>(m + o_first);
     pl->ws.flags = reinterpret_cast<uint64_t*>(m + o_flags);
     pl->ws.pol = reinterpret_cast<uint64_t*>(m + o_pol);
     pl->ws.misc = reinterpret_cast<int64_t*>(m + o_misc);
@@ -454,14 +452,14 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     std::vector<int64_t> xb(esim::kDenseSets * (esim::kMaxXcds + 1), 0);
     for (int q = 0; q < esim::kDenseSets; ++q) {
       const int64_t groups = pl->dense_groups[q];
-      const int64_t* at = first.data() + static_cast<size_t>(q) * nclips;
+      const esim::ClipDev* at = tables.data() + static_cast<size_t>(q) * nclips;
       int64_t* row = xb.data() + q * (esim::kMaxXcds + 1);
       double total = 0.0;
       std::vector<double> wc(nclips);
       std::vector<int64_t> gc(nclips);
       for (int c = 0; c < nclips; ++c) {
         const auto& cd = pl->host[c];
-        gc[c] = (c + 1 < nclips ? at[c + 1] : groups) - at[c];
+        gc[c] = (c + 1 < nclips ? at[c + 1].first_group : groups) - at[c].first_group;
         wc[c] = static_cast<double>(2 * cd.r + 1) * (2 * cd.r + 1) * (2 * cd.tr + 1);
         total += wc[c] * static_cast<double>(gc[c]);
       }
@@ -474,7 +472,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
         for (int c = 0; c < nclips; ++c) {
           const double cw = wc[c] * static_cast<double>(gc[c]);
           if (cum + cw >= target) {
-            idx = at[c] +
+            idx = at[c].first_group +
                   std::min<int64_t>(gc[c], static_cast<int64_t>(std::ceil((target - cum) / wc[c])));
             break;
           }
@@ -483,19 +481,10 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
         row[x] = std::max(row[x - 1], idx);
       }
     }
-    e = hipMemcpy(pl->dev, pl->host.data(), clip_bytes, hipMemcpyHostToDevice);
-    for (int k = 0; mixed && k < esim::kListKinds && e == hipSuccess; ++k) {
-      std::vector<esim::ClipDev> of_kind = pl->host;
-      for (int c = 0; c < nclips; ++c)
-        if (pl->routes[c].kind != k) of_kind[c].HW = 0;
-      pl->kind_dev[k] = reinterpret_cast<esim::ClipDev*>(m + o_kinds + kind_bytes * k);
-      e = hipMemcpy(pl->kind_dev[k], of_kind.data(), clip_bytes, hipMemcpyHostToDevice);
-    }
+    e = hipMemcpy(pl->dev, tables.data(), clip_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(m + o_bcount, 0, off - o_bcount);
     if (e == hipSuccess)
       e = hipMemcpy(pl->xcd_bounds, xb.data(), sizeof(int64_t) * xb.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = hipMemcpy(pl->first_group, first.data(), sizeof(int64_t) * first.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
       (void)hipFree(pl->ws_mem);   // the upload's error is the one reported

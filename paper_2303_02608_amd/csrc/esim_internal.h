@@ -31,6 +31,7 @@ struct ClipDev {
   int64_t pix_off;         // first pixel in the concatenated pixel range
   int64_t blk_off;         // first kBlock-pixel block of the flag/scatter grid
   int64_t nblk;            // kBlock-pixel blocks of this clip
+  int64_t first_group;     // first wave-group of a dense launch (of the table's DenseSet)
   double C, h, ridge, kappa_fp64;
   double c2[ESIM_MAX_D];   // 1 / (h b_j)^2
   double sf[ESIM_MAX_D];   // 1 / (h b_j)
@@ -174,12 +175,11 @@ __device__ __forceinline__ int item_frame(int64_t it) { return static_cast<int>(
 // ---- launchers (host) -----------------------------------------------------
 
 struct RegressArgs {
-  const ClipDev* clips;
+  const ClipDev* clips;     // dense: the table of its DenseSet (clips outside have no groups)
   int32_t nclips;
   int32_t t;                // >= 0 uniform frame, < 0 frame from the item
   const int64_t* items;     // nullptr = dense
   const int32_t* count;
-  const int64_t* first_group;   // dense: [nclips] of its DenseSet (clips outside have no groups; device)
   int64_t n_dense_groups;   // dense: wave-groups over the set's clips
   int64_t max_groups;       // upper bound of groups (grid sizing)
   int64_t n_out;

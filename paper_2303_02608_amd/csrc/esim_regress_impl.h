@@ -76,8 +76,8 @@ __device__ __forceinline__ bool group_item(const RegressArgs& a, int64_t g, int 
     return list_item(a, idx, n_items, cl, pix, t);
   }
   for (int c = 1; c < a.nclips; ++c)
-    if (a.first_group[c] <= g) cl = c;
-  const int64_t p = (g - a.first_group[cl]) * G + slot;
+    if (a.clips[c].first_group <= g) cl = c;
+  const int64_t p = (g - a.clips[cl].first_group) * G + slot;
   const bool valid = p < a.clips[cl].HW && a.t < a.clips[cl].T;
   pix = valid ? p : 0;
   idx = a.clips[cl].pix_off + p;
@@ -398,11 +398,11 @@ regress_tile_kernel(RegressArgs a) {
     const int64_t g = queue.group(k);
     int cl = 0;
     for (int c = 1; c < a.nclips; ++c)
-      if (a.first_group[c] <= g) cl = c;
+      if (a.clips[c].first_group <= g) cl = c;
     const ClipDev& C = a.clips[cl];
     if (a.t >= C.T) continue;
     TileGeom<F, F16> geo;
-    make_tile(geo, C, static_cast<int>(g - a.first_group[cl]), a.t);
+    make_tile(geo, C, static_cast<int>(g - C.first_group), a.t);
     Gram<F, double> gm;
     tile_gram(geo, lds, gm);
     double M[P * (P + 1) / 2], th[P], rhs[P], anorm;
