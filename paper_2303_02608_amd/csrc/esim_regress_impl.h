@@ -185,11 +185,8 @@ __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, i
                                              int j, Fn&& fn, double wscale = 1.0) {
   group_rounds<F, F16>(a, valid, my_cl, my_pix, my_t, wscale,
                        [&](const ClipDev& C, const WalkGeom<F, F16>& geo, bool active, int64_t pix, int t) {
-    CellSums<F> c;
-    LaneSums<F> ls;
-    walk_window<F, L, F16>(geo, j, c, ls);
     Gram<F, double> got;
-    gram_of_lane(c, ls, geo.vy_step, got);
+    walk_gram<F, L, F16>(geo, j, got);
     fn(C, active, pix, t, got);
   });
 }

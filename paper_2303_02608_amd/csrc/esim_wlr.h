@@ -517,26 +517,6 @@ __device__ __forceinline__ void walk_frames(const WalkGeom<F, F16>& g, int dx, i
   }
 }
 
-// The columns j, j + L, ... of the lane's item, up to three frames at a time; the
-// totals go to c (entries without a coordinate) and ls.
-template <int F, int L, bool F16>
-__device__ __forceinline__ void walk_window(const WalkGeom<F, F16>& g, int j, CellSums<F>& c, LaneSums<F>& ls) {
-  c.zero();
-  ls.zero();
-#pragma unroll 1
-  for (int d0 = -g.r; d0 <= g.r; d0 += L) {
-    const double vx = static_cast<double>(d0 + j) * g.vx_step;
-#pragma unroll 1
-    for (int k0 = 0; k0 < g.nt; k0 += 3) {
-      const int left = g.nt - k0;
-      if (left >= 3) walk_frames<F, F16, 3>(g, d0 + j, k0, c);
-      else if (left == 2) walk_frames<F, F16, 2>(g, d0 + j, k0, c);
-      else walk_frames<F, F16, 1>(g, d0 + j, k0, c);
-      ls.end_line(c, vx);
-    }
-  }
-}
-
 // ---- dense windows from LDS ------------------------------------------------
 //
 // Every pixel of a frame, one lane per pixel: a wave owns a tile of 64 pixels
@@ -909,6 +889,35 @@ __device__ __forceinline__ void tile_gram(const TileGeom<F, F16>& g, float4* lds
     for (int k0 = 0; k0 < g.nt; ++k0) tile_frames<F, F16, 1>(g, lds, k0, c, ls);
     gram_of_lane<F, true>(c, ls, g.vx_step, G);
   }
+}
+
+// The Gram of the columns j, j + L, ... of the lane's item, read from memory.  The
+// sums of each count of frames have their own branch, as in tile_gram (kept across
+// the branches, every row spilled: F = 8, r = 12, five frames, half precision, 307200
+// pixels 14.2 ms, now 4.2; the condition output at F = 8, r = 5, 76800 pixels, one
+// frame 434 us, now 145).
+template <int F, int L, bool F16>
+__device__ __forceinline__ void walk_gram(const WalkGeom<F, F16>& g, int j, Gram<F, double>& G) {
+  auto walk = [&](auto frames, auto depth, int chunks) {
+    CellSums<F> c;
+    LaneSums<F> ls;
+    c.zero();
+    ls.zero();
+#pragma unroll 1
+    for (int d0 = -g.r; d0 <= g.r; d0 += L) {
+#pragma unroll 1
+      for (int k = 0; k < chunks; ++k)
+        walk_frames<F, F16, decltype(frames)::value, decltype(depth)::value>(g, d0 + j, k, c);
+      ls.end_line(c, static_cast<double>(d0 + j) * g.vx_step);
+    }
+    gram_of_lane(c, ls, g.vy_step, G);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  using Three = std::integral_constant<int, 3>;
+  if (g.nt == 3) walk(Three{}, One{}, 1);
+  else if (g.nt == 2) walk(Two{}, One{}, 1);
+  else walk(One{}, Two{}, g.nt);
 }
 
 // ---- lane sums that leave each total in one lane ---------------------------
