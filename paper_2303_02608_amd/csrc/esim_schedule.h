@@ -76,12 +76,25 @@ inline ClipRoute clip_route(int W, int H, int F, int r, int tr, double ridge, in
       c.tile_lw = lw;
       c.tiles = true;
     }
-  // A tile is a wave of 64 pixels: a frame of fewer tiles than the device has SIMDs
-  // leaves SIMDs idle for as long as one wave takes over its window, so it runs 16
-  // lanes per item (r = 7, three frames, F = 7: 4096 pixels 129 -> 19 us, 32768
-  // pixels 143 -> 77 us, 65536 pixels, a tile for each SIMD, 154 against 146 us,
-  // 131072 pixels 263 against 289 us).
-  c.few = tile_count(W, H, c.tile_lw) < 4ll * cus;
+  // A tile is a wave of 64 pixels whatever it covers.  On images narrower than about
+  // a tile's smallest width, packed lanes that read from memory do less: 131072 pixels,
+  // F = 7, r = 7, three frames: 4 columns 0.87 ms in tiles, 0.28 from memory; 8 columns
+  // 0.44 and 0.30; 20 columns, a cover of 0.62, 0.45 and 0.47.
+  c.tiles = c.tiles && 5 * static_cast<int64_t>(W) * H >= 3 * kWave * tile_count(W, H, c.tile_lw);
+  // A frame of fewer tiles than the device has SIMDs takes as long as one wave over
+  // its windows; 16 lanes per item take less up to a share of a tile per SIMD that
+  // grows with the window, whose solve the 16 lanes cost extra.  The tiles' time is
+  // reached at, of 65536 pixels (256 CUs), one frame or three: r = 1 0.14, r = 2
+  // 0.2-0.3, r = 3 0.3-0.4, r = 4 0.4, r = 5 0.5-0.55, r = 6 to 12 0.6-0.8 (F = 1 to
+  // 8, 12); F = 9 to 11, whose tiles load rows ahead: r = 3 0.25-0.3, r = 5 0.35-0.4,
+  // r = 6 and more 0.4-0.6.  (F = 7, r = 7, three frames: 4096 pixels 129 us in tiles,
+  // 18 on 16 lanes; 50176 pixels 131 and 135.  r = 3: 21 and 48 at 57600.)  Where
+  // windows are read from memory, 16 lanes are ahead up to a pixel per lane (F = 7,
+  // r = 33: 62500 pixels 1.30 and 1.00 ms).
+  const int64_t simds = 4ll * cus;
+  const int share = r < 6 ? r : 6;
+  c.few = c.tiles ? (F >= 9 && F <= 11 ? 14 : 10) * tile_count(W, H, c.tile_lw) < share * simds
+                  : static_cast<int64_t>(W) * H < kWave * simds;
   // 9 to 15 columns are one uncut turn of 16 lanes; narrower windows fill the lanes
   // better cut into parts (65536 items at r = 3: 84 us, uncut 98)
   c.kind = ridge < kExactRidge ? kListExact : r >= 4 && r <= 7 && tr <= 1 ? kListSingle : kListParts;
