@@ -66,3 +66,9 @@ def test_tiles_and_default_lists_stay_in_registers(kernels, F):
     assert _scratch(kernels, rf"regress_tile_kernelILi{F}E") == 0
     for kind in (0, 1):
         assert _scratch(kernels, rf"regress_list_kernelILi{F}ELi16ELb[01]ELi{kind}E") <= 48
+
+
+# (with an item's fields and best SURE held over the walks: 160 and 308 bytes)
+@pytest.mark.parametrize("F,limit", [(7, 80), (8, 240)])
+def test_bandwidth_lists(kernels, F, limit):
+    assert _scratch(kernels, rf"bandwidth_list_kernelILi{F}ELb[01]ELi1E") <= limit
