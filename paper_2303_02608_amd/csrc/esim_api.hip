@@ -127,7 +127,7 @@ esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
   return a;
 }
 
-// kind: ListKind of the instance (16 lanes); `only`: items of clips of that kind only.
+// kind: ListKind of the instance; `only`: items of clips of that kind only.
 esim::RegressArgs list_args(esim_plan pl, int32_t t, const int64_t* worklist, const int32_t* count, int64_t n_out,
                             int L, int kind, bool only) {
   esim::RegressArgs a{};
@@ -168,7 +168,7 @@ int launch_plan_regress(esim_plan pl, int32_t t, const int64_t* worklist, const 
     });
   const int L = kappa_f64 ? 1 : pl->lanes_list;
   kinds &= pl->kinds;
-  if (L != 16 || precision != ESIM_GRAM_F64 || kinds == 0)
+  if (L < 4 || precision != ESIM_GRAM_F64 || kinds == 0)
     return launch(list_args(pl, t, worklist, count, n_out, L, 0, false), L);
   // clips of several kinds: a launch for each, over the same list
   for (int k = 0; k < esim::kListKinds; ++k)

@@ -190,7 +190,7 @@ struct RegressArgs {
   int32_t update_state;     // write each item's model into its clip state (Sec. 2.2)
   const int64_t* xcd_bounds;  // dense multi-clip launches: [nxcd + 1] group bounds per XCD (device)
   int32_t nxcd;               // XCDs of the device (group-to-XCD mapping)
-  int32_t kind;               // 16 lanes per item: ListKind of the instance
+  int32_t kind;               // 4, 8 and 16 lanes per item: ListKind of the instance (4 and 8: exact or not)
   int32_t tile_units;         // dense tiles: 16-byte units of a wave's LDS (0: groups of lanes, no tiles)
 };
 
@@ -202,10 +202,12 @@ using AdjointFn = void (*)(AdjointArgs);
 struct BandwidthArgs;
 using BandwidthFn = void (*)(BandwidthArgs);
 
-// Regression kernels of one feature count: FP64 Gram [lanes 1, 2, 4, 8][f16] and 16 [ListKind][f16],
+// Regression kernels of one feature count: FP64 Gram [lanes 1, 2][f16], [lanes 4, 8][exact
+// moments][f16] and 16 lanes [ListKind][f16],
 // compensated FP32 [lanes 4, 16][f16] (null where not compiled).
 struct RegressTable {
-  KernelFn general[4][2] = {};
+  KernelFn lanes1_2[2][2] = {};
+  KernelFn lanes4_8[2][2][2] = {};
   KernelFn list[kListKinds][2] = {};
   KernelFn c32[2][2] = {};
   KernelFn kappa[2] = {};      // FP64 Gram with the condition estimate, one lane per item

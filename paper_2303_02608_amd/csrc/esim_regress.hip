@@ -43,9 +43,15 @@ namespace {
 
 KernelFn pick(int F, int lanes, int kind, bool f16) {
   const RegressTable* t = regress_table(F);
-  const int li = lanes == 1 ? 0 : lanes == 2 ? 1 : lanes == 4 ? 2 : lanes == 8 ? 3 : -1;
-  if (t && lanes == 16) return t->list[kind][f16];
-  return (t && li >= 0) ? t->general[li][f16] : nullptr;
+  if (!t) return nullptr;
+  switch (lanes) {
+    case 1:
+    case 2: return t->lanes1_2[lanes - 1][f16];
+    case 4:
+    case 8: return t->lanes4_8[lanes == 8][kind == kListExact][f16];
+    case 16: return t->list[kind][f16];
+    default: return nullptr;
+  }
 }
 
 KernelFn pick_c32(int F, int lanes, bool f16) {

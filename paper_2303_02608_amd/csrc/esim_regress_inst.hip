@@ -26,14 +26,18 @@ void list_kernels(RegressTable& t) {
 
 void ESIM_CAT(regress_table_, ESIM_REGRESS_F)(RegressTable& t) {
   constexpr int F = ESIM_REGRESS_F;
-  t.general[0][0] = regress_kernel<F, 1, false, false>;
-  t.general[0][1] = regress_kernel<F, 1, true, false>;
-  t.general[1][0] = regress_kernel<F, 2, false, false>;
-  t.general[1][1] = regress_kernel<F, 2, true, false>;
-  t.general[2][0] = regress_list_kernel<F, 4, false, kListExact>;
-  t.general[2][1] = regress_list_kernel<F, 4, true, kListExact>;
-  t.general[3][0] = regress_list_kernel<F, 8, false, kListExact>;
-  t.general[3][1] = regress_list_kernel<F, 8, true, kListExact>;
+  t.lanes1_2[0][0] = regress_kernel<F, 1, false, false>;
+  t.lanes1_2[0][1] = regress_kernel<F, 1, true, false>;
+  t.lanes1_2[1][0] = regress_kernel<F, 2, false, false>;
+  t.lanes1_2[1][1] = regress_kernel<F, 2, true, false>;
+  t.lanes4_8[0][0][0] = regress_list_kernel<F, 4, false, kListParts>;
+  t.lanes4_8[0][0][1] = regress_list_kernel<F, 4, true, kListParts>;
+  t.lanes4_8[0][1][0] = regress_list_kernel<F, 4, false, kListExact>;
+  t.lanes4_8[0][1][1] = regress_list_kernel<F, 4, true, kListExact>;
+  t.lanes4_8[1][0][0] = regress_list_kernel<F, 8, false, kListParts>;
+  t.lanes4_8[1][0][1] = regress_list_kernel<F, 8, true, kListParts>;
+  t.lanes4_8[1][1][0] = regress_list_kernel<F, 8, false, kListExact>;
+  t.lanes4_8[1][1][1] = regress_list_kernel<F, 8, true, kListExact>;
   list_kernels<F, kListParts>(t);
   list_kernels<F, kListSingle>(t);
   list_kernels<F, kListExact>(t);

@@ -126,11 +126,11 @@ constexpr bool dense_tiles(int set) { return set == kDenseTile || set == kDenseA
 constexpr int dense_set_lanes(int set) {
   return set < kDenseTile ? 1 << set : set >= kDense16 && set < kDenseAutoTile ? 16 : 1;
 }
-// ListKind of a set of 16 lanes per item.
+// ListKind of a set's instance (4 or 8 lanes per item by hand take every clip: exact).
 constexpr int dense_kind(int set) {
   return set >= kDenseFew && set < kDenseAutoTile ? set - kDenseFew
          : set >= kDense16 && set < kDenseFew     ? set - kDense16
-                                                  : 0;
+                                                  : static_cast<int>(kListExact);
 }
 
 // Groups of a clip's pixels in a dense launch: tiles, or 64 / L pixels.
