@@ -186,7 +186,7 @@ __device__ __forceinline__ void window_grams(const RegressArgs& a, bool valid, i
   group_rounds<F, F16>(a, valid, my_cl, my_pix, my_t, wscale,
                        [&](const ClipDev& C, const WalkGeom<F, F16>& geo, bool active, int64_t pix, int t) {
     Gram<F, double> got;
-    walk_gram<F, L, F16>(geo, j, got);
+    walk_gram<F, L, F16>(geo, j, a.items == nullptr, got);
     fn(C, active, pix, t, got);
   });
 }
@@ -262,7 +262,7 @@ __device__ __forceinline__ void park_group(const RegressArgs& a, bool valid, int
       // few sums, and many turns to add them over the lanes in: kept in registers
       // over the turns (F = 3, r = 3, 20000 items 14.1 -> 12.3 us; F = 10 694 -> 699)
       Gram<F, double> got;
-      walk_gram<F, L, F16>(geo, j, got);
+      walk_gram<F, L, F16>(geo, j, true, got);
       park(got, true);
     } else {
       walk_parts<F, L, F16, KIND>(geo, j, park);

@@ -895,9 +895,12 @@ __device__ __forceinline__ void tile_gram(const TileGeom<F, F16>& g, float4* lds
 // sums of each count of frames have their own branch, as in tile_gram (kept across
 // the branches, every row spilled: F = 8, r = 12, five frames, half precision, 307200
 // pixels 14.2 ms, now 4.2; the condition output at F = 8, r = 5, 76800 pixels, one
-// frame 434 us, now 145).
+// frame 434 us, now 145).  Frames one at a time with two rows ahead for scattered
+// items (lists), whose loads take longer than a cell's samples (20000 items, F = 10,
+// r = 7, three frames, one lane: 655 us, three frames at a time 813), for F above 10,
+// whose three frames at a time spill, and for more than three frames.
 template <int F, int L, bool F16>
-__device__ __forceinline__ void walk_gram(const WalkGeom<F, F16>& g, int j, Gram<F, double>& G) {
+__device__ __forceinline__ void walk_gram(const WalkGeom<F, F16>& g, int j, bool dense, Gram<F, double>& G) {
   auto walk = [&](auto frames, auto depth, int chunks) {
     CellSums<F> c;
     LaneSums<F> ls;
@@ -915,8 +918,9 @@ __device__ __forceinline__ void walk_gram(const WalkGeom<F, F16>& g, int j, Gram
   using One = std::integral_constant<int, 1>;
   using Two = std::integral_constant<int, 2>;
   using Three = std::integral_constant<int, 3>;
-  if (g.nt == 3) walk(Three{}, One{}, 1);
-  else if (g.nt == 2) walk(Two{}, One{}, 1);
+  constexpr bool CELLS = F < 11;           // two or three frames at a time
+  if (CELLS && dense && g.nt == 3) walk(std::conditional_t<CELLS, Three, One>{}, One{}, 1);
+  else if (CELLS && dense && g.nt == 2) walk(std::conditional_t<CELLS, Two, One>{}, One{}, 1);
   else walk(One{}, Two{}, g.nt);
 }
 

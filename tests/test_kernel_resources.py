@@ -53,7 +53,7 @@ def _scratch(kernels, pattern):
 # regress_kernel<F, L, f16, c32, kappa>, bandwidth_dense_kernel<F, f16>; the bytes before these kernels
 # kept one walk's sums over the branches of all frame counts (F = 12 half precision: 980)
 @pytest.mark.parametrize("F,lanes,dense,kappa", [(7, 208, 180, 830), (8, 416, 330, 1356), (10, 16, 64, 1460),
-                                                 (12, 440, 980, 2412)])
+                                                 (12, 980, 980, 2412)])
 def test_windows_from_memory(kernels, F, lanes, dense, kappa):
     for L in (1, 2):
         assert _scratch(kernels, rf"regress_kernelILi{F}ELi{L}ELb[01]ELb0ELb0E") <= lanes
