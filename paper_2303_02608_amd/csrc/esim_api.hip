@@ -401,6 +401,13 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
       pl->routes.push_back(rt);
     }
     pl->split_seg = seg > 0 && seg < pix ? seg : -1;
+    if (pl->tile_units) {
+      const hipError_t e = esim::allow_tile_lds(pl->F, pl->f16);
+      if (e != hipSuccess) {
+        delete pl;
+        return hip_check(e, "LDS of the dense tiles");
+      }
+    }
     std::vector<esim::ClipDev> tables;
     for (int k = 0; k < esim::kDenseSets + esim::kListKinds; ++k)
       for (int c = 0; c < nclips; ++c) {

@@ -220,6 +220,11 @@ struct RegressTable {
 hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, int lanes,
                           int blocks_per_cu, const DeviceShape& dev, hipStream_t s);
 const RegressTable* regress_table(int F);   // null outside 1..ESIM_MAX_F
+// Lets the tile kernels of (F, dtype) take up to kMaxTileLds of LDS on the current
+// device: the same value whatever the plan, so that plans and threads may do it again
+// at any time.  Once per plan, not at the launches, whose own size it would lower
+// under another thread's launch.
+hipError_t allow_tile_lds(int F, bool f16);
 // Launches a kernel over the groups of a (args: its one argument, which holds
 // a): `queue` with one block per CU of 4 regress_waves_per_simd waves that hand out their
 // share of the groups (GroupQueue), else blocks of four waves, at most

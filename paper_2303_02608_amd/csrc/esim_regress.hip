@@ -86,6 +86,17 @@ hipError_t launch_regress(const RegressArgs& a, int F, bool f16, int precision, 
                        a.tile_units || (!c32 && !a.kappa && lanes >= 4), std::min(blocks_per_cu, resident), dev, s);
 }
 
+hipError_t allow_tile_lds(int F, bool f16) {
+  const RegressTable* t = regress_table(F);
+  if (!t) return hipErrorInvalidValue;
+  for (const void* fn : {reinterpret_cast<const void*>(t->tile[f16]), reinterpret_cast<const void*>(t->bandwidth[0][f16])}) {
+    const hipError_t e =
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kMaxTileLds));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int F, bool queue,
                          int blocks_per_cu, const DeviceShape& dev, hipStream_t s) {
   const int waves = queue ? 4 * regress_waves_per_simd(F, false) : kWavesPerBlock;
@@ -94,11 +105,7 @@ hipError_t launch_groups(const void* fn, void* args, const RegressArgs& a, int F
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   blocks = (blocks + dev.xcds - 1) / dev.xcds * dev.xcds;   // a multiple of the XCDs (see GroupIter, GroupQueue)
-  const size_t lds = a.tile_units ? tile_block_bytes(F, a.tile_units) : 0;
-  if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-  }
+  const size_t lds = a.tile_units ? tile_block_bytes(F, a.tile_units) : 0;   // allow_tile_lds allows it
   void* argv[] = {args};
   const hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)),
                                        dim3(static_cast<unsigned>(kWave * waves)), argv, lds, s);
