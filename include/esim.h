@@ -199,11 +199,11 @@ int64_t esim_plan_pixel_offset(esim_plan plan, int32_t c);
 /* Schedule of the regression kernel (set by the autotuner, or by hand): the
  * lanes that share one regression item in dense launches and in work-list
  * launches (1, 2, 4, 8 or 16; more lanes = more, shorter wave tasks for sparse
- * lists) and the persistent blocks per CU (1..64; of the instances of 1 and 2
- * lanes that read windows from memory and of ESIM_GRAM_F32C, the others take one
- * block per CU).  Defaults 1, 16, 4 (4, 16, 4 with ESIM_GRAM_F32C); without a
- * schedule set, frames too small to fill the device with one lane per pixel take
- * 16 lanes per item.
+ * lists) and the persistent blocks per CU (1..64).  The blocks reach the FP64
+ * instances of 1 and 2 lanes that read windows from memory, up to the two that fit
+ * (F above 8: one); every other instance takes one block per CU.  Defaults 1, 16, 4
+ * (4, 16, 4 with ESIM_GRAM_F32C); without a schedule set, clips whose frames are too
+ * small to fill the device with one lane per pixel take 16 lanes per item.
  * Errors: E_UNSUPPORTED (lanes not compiled), E_INVAL. */
 int esim_plan_set_schedule(esim_plan plan, int32_t lanes_dense, int32_t lanes_list,
                            int32_t blocks_per_cu);

@@ -203,7 +203,10 @@ class Plan:
         self.offsets = [lib.esim_plan_pixel_offset(h, i) for i in range(n)]
         self.F = feats[0].shape[1]
         self.D = self.F + 2
-        self.schedule = (4, 16, 4)
+        # lanes per item (dense, lists) and blocks per CU; until one is set, small
+        # frames of the FP64 Gram take 16 lanes by themselves
+        self.schedule = (1 if params[0].precision == GRAM_F64 else 4, 16, 4)
+        self.schedule_set = False
 
     def __del__(self):
         h = getattr(self, "h", None)
@@ -215,6 +218,7 @@ class Plan:
         _check(load().esim_plan_set_schedule(self.h, lanes_dense, lanes_list, blocks_per_cu),
                "set_schedule")
         self.schedule = (lanes_dense, lanes_list, blocks_per_cu)
+        self.schedule_set = True
 
 
 class Events:
