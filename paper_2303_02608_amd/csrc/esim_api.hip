@@ -31,6 +31,7 @@ struct esim_plan_s {
   int64_t dense_groups[esim::kDenseSets] = {};   // of each set, over its clips
   int tile_units = 0;      // 16-byte units of a wave's LDS for dense tiles
   uint32_t kinds = 0;      // bit k: a clip of ListKind k
+  bool multi = false;      // a clip has the every-crossing rule
   int lanes_dense = 1;     // lanes per regression item, dense launches
   bool auto_dense = true;  // no schedule was set (FP64 Gram): clip_route's choice
   int lanes_list = 16;     // lanes per regression item, work-list launches
@@ -347,6 +348,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
         return fail(ESIM_E_INVAL, "multi_crossing must be 0 or 1");
       }
       cd.multi = p.multi_crossing;
+      pl->multi = pl->multi || p.multi_crossing;
       cd.HW = static_cast<int64_t>(k.W) * k.H;
       cd.pix_off = pix;
       cd.blk_off = blk;
@@ -639,7 +641,7 @@ int esim_events(esim_plan pl, int32_t t, int32_t mode, const int64_t* worklist, 
       return hip_check(esim::launch_flag_compact(pl->dev, pl->nclips, pl->nblk, t,
                                                  mode == ESIM_EXHAUSTIVE ? esim::kFlagExhaustive
                                                                          : esim::kFlagRaw,
-                                                 dl, alpha, pl->ws, nullptr, nullptr, &ed, s),
+                                                 dl, alpha, pl->ws, nullptr, nullptr, &ed, s, -1, pl->multi),
                        "events");
     }
     return fail(ESIM_E_INVAL, "bad mode");
@@ -712,12 +714,12 @@ int esim_step(esim_plan pl, int32_t t, int32_t mode, float* dl, esim_events_buf*
                                    nullptr, false, s);
       if (rc != ESIM_OK) return rc;
       return hip_check(esim::launch_flag_compact(pl->dev, pl->nclips, pl->nblk, t, esim::kFlagExhaustive, dl,
-                                                 pl->step_alpha, pl->ws, nullptr, nullptr, &ed, s),
+                                                 pl->step_alpha, pl->ws, nullptr, nullptr, &ed, s, -1, pl->multi),
                        "step(exhaustive)");
     }
     if (mode == ESIM_RAW)
       return hip_check(esim::launch_flag_compact(pl->dev, pl->nclips, pl->nblk, t, esim::kFlagRaw, dl,
-                                                 nullptr, pl->ws, nullptr, nullptr, &ed, s),
+                                                 nullptr, pl->ws, nullptr, nullptr, &ed, s, -1, pl->multi),
                        "step(raw)");
     return fail(ESIM_E_INVAL, "bad mode");
   } catch (...) {

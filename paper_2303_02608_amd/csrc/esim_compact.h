@@ -43,15 +43,17 @@ constexpr int64_t kDirectPrefixBlocks = 4096;
 // worklist[seg_b, seg_b + nB), each segment in ascending (clip, p) order;
 // count[0] = count[1] = nA, count[2] = count[3] = nB (count holds four).
 // The events keep their order, (clip, p) ascending over all clips.
+// multi: a clip has the every-crossing rule (in the modes that append events to ev).
 hipError_t launch_flag_compact(const ClipDev* clips, int nclips, int64_t nblk, int t, int mode,
                                float* dl, const float* alpha, const Workspace& ws, int64_t* worklist,
-                               int32_t* count, const EventsDev* ev, hipStream_t s, int64_t seg_b = -1);
+                               int32_t* count, const EventsDev* ev, hipStream_t s, int64_t seg_b = -1,
+                               bool multi = false);
 
 // The compaction after a flag kernel that has already filled ws (chunk totals
 // when needed, then the scatter), as in launch_flag_compact (no split).
 hipError_t launch_scatter(const ClipDev* clips, int nclips, int64_t nblk, int t, int mode,
                           const float* alpha, const Workspace& ws, int64_t* worklist, int32_t* count,
-                          const EventsDev* ev, hipStream_t s, int64_t seg_b = -1);
+                          const EventsDev* ev, hipStream_t s, int64_t seg_b = -1, bool multi = false);
 
 // State <- the models of the work-list items (alpha[i], beta[.., i]), feat_t
 // and t, without events (the step's explicit-threshold path).

@@ -13,7 +13,7 @@
 //                      block 0 records the event base.
 //   chunk_kernel       totals of chunks of kChunkBlocks block counts (only for
 //                      grids above kDirectPrefixBlocks blocks).
-//   scatter_kernel     one wave per flag block; its offset: the sum of the counts
+//   scatter_kernel     one wave per flag block (or word of one); its offset: the sum of the counts
 //                      of the blocks before it, read directly (or as chunk totals
 //                      plus the counts inside its chunk), with no inter-block
 //                      signalling; rank = offset + popcounts of
@@ -233,29 +233,42 @@ __global__ void __launch_bounds__(kBlock) chunk_kernel(Workspace ws, int64_t nbl
   if (threadIdx.x == 0) ws.chunk[c] = t;
 }
 
-// A wave takes a flag block, so that the sum of the counts before it is read once
-// for kWavesPerBlock of them, and its pixels' loads are in flight meanwhile.
-// Bound by latency (a frame without events, 1280 x 720: 4.6 us) and, where every
-// pixel has events, by their writes.
+// WORDS = kWavesPerBlock: a wave takes a flag block, so that the sum of the counts
+// before it is read once for kWavesPerBlock of them, and its pixels' loads are in
+// flight meanwhile.  WORDS = 1: a wave takes one 64-pixel word and a block a flag
+// block, for grids that leave the device idle otherwise; every crossing's events then
+// go round four times the waves.  Bound by latency (a frame without events, 1280 x
+// 720: 4.6 us) and, where every pixel has events, by the work and writes of each.
+//
+// Raw steps (flag and scatter), us, a flag block and a word per wave, and where the
+// lines lie: one event a pixel at most 64 x 64 7.0 and 6.5, 512 x 384 (768 flag
+// blocks) 7.7 and 7.7, 1024 x 768 11.7 and 14.5; every crossing, one event a pixel or
+// so, 64 x 64 9.8 and 7.9, 640 x 480 11.7 and 10.4, 800 x 600 (1875) 12.9 and 12.7,
+// 1024 x 768 15.3 and 17.5; twenty events a pixel, 640 x 480 23.9 and 16.4.
+constexpr int64_t kWordBlocks = 768, kWordBlocksMulti = 1875;
+
+template <int WORDS>
 __global__ void __launch_bounds__(kBlock)
 scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int t, int mode, Workspace ws,
                int chunked, const float* __restrict__ alpha, int64_t* __restrict__ worklist,
                int32_t* __restrict__ count, EventsDev ev, int64_t seg_b) {
   constexpr int64_t kLow = 0xFFFFFFFFll;
   constexpr int NW = kWavesPerBlock;          // waves of the block and 64-pixel words of a flag block
+  constexpr int PIX = WORDS * kWave;          // pixels of a wave
   const int lane = threadIdx.x & (kWave - 1);
   const int w = uni(static_cast<int>(threadIdx.x) / kWave);
-  const int64_t b0 = static_cast<int64_t>(blockIdx.x) * NW;
-  const int64_t b = b0 + w;                   // this wave's flag block
+  const int64_t b0 = static_cast<int64_t>(blockIdx.x) * (WORDS == 1 ? 1 : NW);
+  const int64_t b = WORDS == 1 ? b0 : b0 + w;                // this wave's flag block
+  const int w0 = WORDS == 1 ? w : 0;                         // and its first word in it
   const bool mine = b < nblk;
   const int cl = mine ? block_clip(clips, nclips, b) : 0;
   const ClipDev& C = clips[cl];
-  const int64_t p0 = (b - C.blk_off) * kBlock + lane;       // its first word's pixel
+  const int64_t p0 = (b - C.blk_off) * kBlock + w0 * kWave + lane;       // its first word's pixel
   const bool multi = C.multi && mode != kFlagThreshold;     // uniform: one clip per flag block
-  float L[NW], Lref[NW], Llast[NW];
-  uint64_t m[NW];
+  float L[WORDS], Lref[WORDS], Llast[WORDS];
+  uint64_t m[WORDS];
 #pragma unroll
-  for (int i = 0; i < NW; ++i) {
+  for (int i = 0; i < WORDS; ++i) {
     const int64_t p = p0 + i * kWave;
     L[i] = Lref[i] = Llast[i] = 0.0f;
     m[i] = 0;
@@ -264,15 +277,16 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
       Lref[i] = C.st_alpha[p];
       Llast[i] = C.st_last[p];
     }
-    if (mine && !multi) m[i] = ws.flags[b * NW + i];
+    if (mine && !multi) m[i] = ws.flags[b * NW + w0 + i];
   }
   int64_t packed = counts_before(ws, b0, chunked != 0);
   if (!mine) return;
-  for (int k = 0; k < w; ++k) packed += ws.bcount[b0 + k];
+  if constexpr (WORDS == NW)
+    for (int k = 0; k < w; ++k) packed += ws.bcount[b0 + k];
   const int64_t off0 = packed & kLow;         // flagged pixels before this flag block
   const int64_t offb0 = packed >> 32;         // of them in second-segment clips (split only)
   const int64_t base = ws.misc[0];
-  if (b == nblk - 1 && lane == 0) {
+  if (b == nblk - 1 && w0 == 0 && lane == 0) {
     const int64_t tp = packed + ws.bcount[b];
     const int64_t total = tp & kLow;
     if (count) {
@@ -293,14 +307,14 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
     // own: counts differ between neighbours, and a wave waited for its largest.
     // At 1.4 events a pixel (1280 x 720, 44 MB of reads and writes a frame, 9 us at
     // the copy rate) 15.6 us, each pixel's events in its own lane 22.4 (the four
-    // waves of a block sharing theirs 18.7; half as many instructions an event, no
-    // less than 15.6: the writes bound it).
-    __shared__ int first[NW][kBlock];         // events of the wave before each pixel's
-    __shared__ float3 level_of[NW][kBlock];   // L, L_ref, L_last
+    // waves of a block sharing theirs 18.7; half as many instructions an event left
+    // 15.6; whether the single stores of each event bound it has not been shown).
+    __shared__ int first[NW][PIX];            // events of the wave before each pixel's
+    __shared__ float3 level_of[NW][PIX];      // L, L_ref, L_last
     const double thr = uni(C.C), dt = uni(C.dt);
     int total = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
+    for (int i = 0; i < WORDS; ++i) {
       const int64_t p = p0 + i * kWave;
       const bool in = p < C.HW && t >= 1 && t < C.T;
       const double d = static_cast<double>(L[i]) - static_cast<double>(Lref[i]);
@@ -316,12 +330,19 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
       level_of[w][k] = make_float3(L[i], Lref[i], Llast[i]);
       total += __builtin_amdgcn_readlane(before + n, kWave - 1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
+    int64_t e0 = base + off0;
+    if constexpr (WORDS == 1) {               // the words before it in the flag block
+      __shared__ int events[NW];
+      if (lane == 0) events[w] = total;
+      __syncthreads();
+      for (int k = 0; k < w; ++k) e0 += events[k];
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+    }
     const uint32_t W = static_cast<uint32_t>(uni(static_cast<int>(C.W)));
-    const uint32_t pw = static_cast<uint32_t>(uni(static_cast<int>((b - C.blk_off) * kBlock)));
+    const uint32_t pw = static_cast<uint32_t>(uni(static_cast<int>((b - C.blk_off) * kBlock + w0 * kWave)));
     const uint32_t yw = pw / W, xw = pw - yw * W;               // of the wave's first pixel
-    const int64_t e0 = base + off0;
     int32_t* const ex = ev.x + e0;
     int32_t* const ey = ev.y + e0;
     int32_t* const et = ev.t + e0;
@@ -332,7 +353,7 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
     for (uint32_t i0 = lane; i0 < end; i0 += kAhead * kWave) {
       int k[kAhead] = {};                     // the last pixel with first <= i
 #pragma unroll
-      for (int o = kBlock / 2; o > 0; o >>= 1)
+      for (int o = PIX / 2; o > 0; o >>= 1)
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
           if (first[w][k[u] + o] <= static_cast<int>(i0 + u * kWave)) k[u] += o;
@@ -346,7 +367,7 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
         const double nth = static_cast<double>(static_cast<int>(i) - first[w][k[u]] + 1);
         const double level = static_cast<double>(l.y) + nth * (up ? thr : -thr);
         uint32_t x = xw + k[u], y = yw;
-        if (W >= kBlock) {                    // at most one row further
+        if (W >= PIX) {                       // at most one row further
           if (x >= W) {
             x -= W;
             ++y;
@@ -366,8 +387,12 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
     return;
   }
   int64_t rank0 = 0;                          // flagged pixels in the words before
+  if constexpr (WORDS == 1) {
+    if (m[0] == 0) return;
+    for (int k = 0; k < w; ++k) rank0 += __popcll(ws.flags[b * NW + k]);
+  }
 #pragma unroll
-  for (int i = 0; i < NW; ++i) {
+  for (int i = 0; i < WORDS; ++i) {
     if ((m[i] >> lane) & 1ull) {
       const int64_t p = p0 + i * kWave;
       const int64_t rank = rank0 + __popcll(m[i] & ((1ull << lane) - 1ull));
@@ -380,7 +405,7 @@ scatter_kernel(const ClipDev* __restrict__ clips, int nclips, int64_t nblk, int 
       if (ev.x) {
         const int64_t e = base + off;
         if (e < ev.capacity) {
-          const bool pos = (ws.pol[b * NW + i] >> lane) & 1ull;
+          const bool pos = (ws.pol[b * NW + w0 + i] >> lane) & 1ull;
           ev.x[e] = static_cast<int32_t>(static_cast<uint32_t>(p) % static_cast<uint32_t>(C.W));
           ev.y[e] = static_cast<int32_t>(static_cast<uint32_t>(p) / static_cast<uint32_t>(C.W));
           ev.t[e] = t;
@@ -514,17 +539,17 @@ hipError_t launch_log(const float* E, float* y, int64_t n, float eps, hipStream_
 
 hipError_t launch_flag_compact(const ClipDev* clips, int nclips, int64_t nblk, int t, int mode,
                                float* dl, const float* alpha, const Workspace& ws, int64_t* worklist,
-                               int32_t* count, const EventsDev* ev, hipStream_t s, int64_t seg_b) {
+                               int32_t* count, const EventsDev* ev, hipStream_t s, int64_t seg_b, bool multi) {
   int64_t* wl = mode == kFlagThreshold ? worklist : nullptr;
   if (!wl) seg_b = -1;
   hipLaunchKernelGGL(flag_kernel, dim3(static_cast<unsigned>(nblk)), dim3(kBlock), 0, s, clips, nclips,
                      t, mode, dl, alpha, ws, ev ? ev->count : nullptr, seg_b >= 0 ? 1 : 0);
-  return launch_scatter(clips, nclips, nblk, t, mode, alpha, ws, wl, count, ev, s, seg_b);
+  return launch_scatter(clips, nclips, nblk, t, mode, alpha, ws, wl, count, ev, s, seg_b, multi);
 }
 
 hipError_t launch_scatter(const ClipDev* clips, int nclips, int64_t nblk, int t, int mode,
                           const float* alpha, const Workspace& ws, int64_t* worklist, int32_t* count,
-                          const EventsDev* ev, hipStream_t s, int64_t seg_b) {
+                          const EventsDev* ev, hipStream_t s, int64_t seg_b, bool multi) {
   int64_t* wl = mode == kFlagThreshold ? worklist : nullptr;
   if (!wl) seg_b = -1;
   const int chunked = nblk > kDirectPrefixBlocks ? 1 : 0;
@@ -532,8 +557,11 @@ hipError_t launch_scatter(const ClipDev* clips, int nclips, int64_t nblk, int t,
     hipLaunchKernelGGL(chunk_kernel, dim3(static_cast<unsigned>((nblk + kChunkBlocks - 1) / kChunkBlocks)),
                        dim3(kBlock), 0, s, ws, nblk);
   EventsDev none{};
-  hipLaunchKernelGGL(scatter_kernel, dim3(static_cast<unsigned>((nblk + kWavesPerBlock - 1) / kWavesPerBlock)),
-                     dim3(kBlock), 0, s, clips, nclips, nblk, t, mode, ws, chunked, alpha, wl, wl ? count : nullptr, ev ? *ev : none, seg_b);
+  const bool words = nblk < (multi ? kWordBlocksMulti : kWordBlocks);
+  const int64_t blocks = words ? nblk : (nblk + kWavesPerBlock - 1) / kWavesPerBlock;
+  hipLaunchKernelGGL((words ? scatter_kernel<1> : scatter_kernel<kWavesPerBlock>), dim3(static_cast<unsigned>(blocks)),
+                     dim3(kBlock), 0, s, clips, nclips, nblk, t, mode, ws, chunked, alpha, wl, wl ? count : nullptr,
+                     ev ? *ev : none, seg_b);
   return hipGetLastError();
 }
 
