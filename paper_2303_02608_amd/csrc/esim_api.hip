@@ -122,7 +122,7 @@ esim::RegressArgs dense_args(esim_plan pl, int32_t t, int64_t n_out, int set) {
   a.tile_units = esim::dense_tiles(set) ? pl->tile_units : 0;
   a.n_dense_groups = a.max_groups = pl->dense_groups[set];
   a.n_out = n_out;
-  a.xcd_bounds = pl->nclips > 1 ? pl->xcd_bounds + (esim::kMaxXcds + 1) * set : nullptr;
+  a.xcd_bounds = pl->nclips > 1 && esim::dense_strides(set) ? pl->xcd_bounds + (esim::kMaxXcds + 1) * set : nullptr;
   a.nxcd = pl->shape.xcds;
   a.kind = esim::dense_kind(set);
   return a;
@@ -460,6 +460,7 @@ int esim_plan_create(const esim_clip* clips, const esim_params* params, const es
     const int nx = pl->shape.xcds;
     std::vector<int64_t> xb(esim::kDenseSets * (esim::kMaxXcds + 1), 0);
     for (int q = 0; q < esim::kDenseSets; ++q) {
+      if (!esim::dense_strides(q)) continue;
       const int64_t groups = pl->dense_groups[q];
       const esim::ClipDev* at = tables.data() + static_cast<size_t>(q) * nclips;
       int64_t* row = xb.data() + q * (esim::kMaxXcds + 1);

@@ -133,6 +133,12 @@ constexpr int dense_kind(int set) {
                                                   : static_cast<int>(kListExact);
 }
 
+// Sets that may run kernels whose blocks stride over the groups, XCD by XCD (1, 2, and
+// with the compensated Gram 4 and 16 lanes); the others hand their groups out.
+constexpr bool dense_strides(int set) {
+  return set < kDenseTile ? set != lanes_index(8) : dense_set_lanes(set) == 1 && !dense_tiles(set);
+}
+
 // Groups of a clip's pixels in a dense launch: tiles, or 64 / L pixels.
 inline int64_t dense_groups(int set, const ClipRoute& c, int W, int H) {
   if (!dense_member(set, c)) return 0;

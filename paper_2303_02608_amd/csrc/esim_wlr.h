@@ -84,16 +84,7 @@ __device__ __forceinline__ void make_geom(ItemGeom<F, F16, Real>& g, const ClipD
 // The loop takes two rows per iteration (see the loop for an odd row count).
 // Row offsets advance by uniform (SGPR) amounts; only the validity test and
 // the select are per lane.
-//
-// FULL: the caller guarantees that the window of every lane's item lies
-// entirely inside the image and the clip (|dx|, |dy| <= r and |dt| <= tr all
-// valid; lanes without an item carry the geometry of one that has).  Then no
-// row needs a validity test or an address select: a lane's column offset is
-// fixed for the pass, the row offset is uniform, and only the lane's own
-// weight switch (no item, or the idle column of a lane group wider than the
-// window) remains.
-template <int F, int L, bool F16, class Real, bool FULL = false, class PassBegin, class Sample,
-          class PassEnd>
+template <int F, int L, bool F16, class Real, class PassBegin, class Sample, class PassEnd>
 __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int j,
                                             PassBegin&& pass_begin, Sample&& sample,
                                             PassEnd&& pass_end) {
@@ -101,9 +92,7 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
   constexpr Real K = static_cast<Real>(kHalfLog2e);
   const int r = g.r;
   const int span = 2 * r + 1;
-  // FULL: every lane's window spans 2 tr + 1 frames (a uniform count, so the
-  // loop bounds and row offsets below stay scalar)
-  const int nt = FULL ? 2 * g.tr + 1 : g.dt_hi - g.dt_lo + 1;
+  const int nt = g.dt_hi - g.dt_lo + 1;
   const int nrows = nt * span;
   const int npass = (span + L - 1) / L;
   // per-lane valid row range of the item (rows inside the image)
@@ -112,8 +101,7 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
   const uint32_t FES = static_cast<uint32_t>(F) * g.HW * ES, HW4 = g.HW * 4u;
   for (int k = 0; k < npass; ++k) {
     const int dx = -r + j + k * L;
-    // FULL: an idle column reads the window's last column (weight 0)
-    const int col = g.px + (FULL ? min(dx, r) : dx);
+    const int col = g.px + dx;
     const bool col_ok = g.active && dx <= r && col >= 0 && col < g.W;
     const Real vx = static_cast<Real>(dx) * g.vx_step;
     const Real kx = K * vx * vx;
@@ -127,23 +115,6 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
                               static_cast<uint32_t>((g.py - r) * g.W + col)) * 4u;
     int ldt = 0, ldy = 0;          // next row to load, relative to (dt_lo, -r)
     auto load_row = [&](float& yv, float (&fv)[F]) -> bool {
-      if constexpr (FULL) {
-        // rows past the window (the pipeline's look-ahead) repeat the last
-        // row; their weights are never used
-        const bool in = ldt < nt;
-        const uint32_t lt = static_cast<uint32_t>(in ? ldt : nt - 1);
-        const uint32_t ly = static_cast<uint32_t>(in ? ldy : span - 1);
-        const uint32_t sof = lt * FES + ly * WES;
-        const uint32_t soy = lt * HW4 + ly * W4;
-        yv = ld_f32(g.ry, vy_base, soy);
-#pragma unroll
-        for (int f = 0; f < F; ++f) fv[f] = ld_feat<F16>(g.rf, vf_base, sof + f * g.HW * ES);
-        if (++ldy == span) {
-          ldy = 0;
-          ++ldt;
-        }
-        return col_ok;
-      }
       const int dy = ldy - r;
       const bool ok = (ldt <= g.dt_hi - g.dt_lo) & col_ok & (dy >= dy_lo) & (dy <= dy_hi);
       const uint32_t sof = static_cast<uint32_t>(ldt) * FES + static_cast<uint32_t>(ldy) * WES;
@@ -164,7 +135,7 @@ __device__ __forceinline__ void window_loop(const ItemGeom<F, F16, Real>& g, int
       int dt, dy;
       bool ok;
     };
-    int cdt = FULL ? -g.tr : g.dt_lo, cdy = -r;   // next row to weigh
+    int cdt = g.dt_lo, cdy = -r;   // next row to weigh
     auto weigh = [&](float yv, const float (&fv)[F], bool ok, Wt& o) {
       o.dy = cdy;
       o.dt = cdt;
@@ -782,12 +753,11 @@ struct Gram {
 #pragma unroll
     for (int k = 0; k < NA; ++k) st(Aff[k]);
   }
+  // Over one or two lanes (scatter_sum: more).
   template <int L>
   __device__ __forceinline__ void lane_sum() {
-    if constexpr (L >= 2) dpp_step<0xB1>();
-    if constexpr (L >= 4) dpp_step<0x4E>();
-    if constexpr (L >= 8) dpp_step<0x141>();
-    if constexpr (L >= 16) dpp_step<0x140>();
+    static_assert(L <= 2);
+    if constexpr (L == 2) dpp_step<0xB1>();
   }
 };
 
