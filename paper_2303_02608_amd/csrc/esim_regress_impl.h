@@ -11,9 +11,10 @@
 // Mapping.  Dense launches: one lane per pixel and a tile of 64 pixels per wave,
 // its window rows in LDS (regress_tile_kernel).  Work lists: 16 lanes per item,
 // one window column each, 4 items per wave (regress_list_kernel; 4 and 8 lanes
-// are compiled too).  Instances of 1 and 2 lanes per item (regress_kernel) read
-// their windows from memory: dense windows too wide for LDS, and the condition
-// output.  In all of them a coordinate is constant over a line of samples and the
+// are compiled too), and small dense frames.  Instances of 1 and 2 lanes per item
+// (regress_kernel) read their windows from memory: dense windows too wide for LDS,
+// images narrower than half a tile, and the condition output.  Which one a clip
+// takes follows from the clip alone (esim_schedule.h).  In all of them a coordinate is constant over a line of samples and the
 // other over a cell, and no entry with a coordinate factor is summed per sample
 // (esim_wlr.h): 87 VALU instructions per sample at F = 7 and three frames.
 //

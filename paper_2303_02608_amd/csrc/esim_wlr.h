@@ -8,8 +8,8 @@
 // ridge scaled to lambda / (h b_j)^2.
 //
 // The FP64 Gram's walks: walk_frames (columns of a lane, read from memory, for
-// lists and small frames) and tile_frames (a pixel per lane, windows from LDS, for
-// whole frames).  window_loop is the older loop of the compensated FP32 Gram, whose
+// lists, small frames and windows beyond LDS) and tile_frames (a pixel per lane,
+// windows from LDS, for whole frames).  window_loop is the older loop of the compensated FP32 Gram, whose
 // rounding depends on its order, and of the explicit threshold: the L lanes of an
 // item split the window columns (lane j takes dx = -r + j, -r + j + L, ...), and
 // the rows (dt, dy) of a column are software-pipelined in registers, loaded two
