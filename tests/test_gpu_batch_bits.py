@@ -14,13 +14,14 @@ from parity_util import say, to_dev
 pytestmark = pytest.mark.gpu
 
 # W, H, T, r, tr: small and large frames, windows of cut and of whole columns, of
-# five frames, and too wide for tiles
+# five frames, of 16-column tiles, and from memory (too wide for LDS; narrow images)
 SHAPES = {
     "sizes": [(240, 200, 3, 5, 1), (300, 260, 3, 5, 1), (64, 9, 2, 5, 0)],
     "radii": [(60, 50, 3, 3, 1), (240, 200, 3, 7, 1), (133, 140, 3, 9, 1)],
     "narrow": [(240, 200, 3, 3, 1), (52, 31, 3, 7, 1)],
     "frames": [(140, 130, 5, 5, 2), (240, 200, 5, 5, 1), (52, 31, 2, 5, 0)],
-    "no tiles": [(300, 260, 1, 5, 0), (300, 240, 1, 33, 0), (290, 250, 1, 6, 0)],
+    "tile widths": [(300, 260, 1, 5, 0), (300, 240, 1, 33, 0), (290, 250, 1, 6, 0)],
+    "memory": [(300, 260, 1, 5, 0), (300, 240, 1, 57, 0), (5, 14000, 1, 6, 0), (70, 60, 1, 8, 0)],
 }
 
 
