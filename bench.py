@@ -606,7 +606,7 @@ def workload_bandwidth(args, B, synth, Simulator):
         fl += len(HS) * regress_flops(omega_sizes(xs, ys, np.full(HW, t), W, H, T, r, tr), F).sum()
     ach = fl / (dms.sum() * 1e-3) / 1e12
     share = (counts.sum(dim=0).double() / (T * HW)).cpu().numpy()
-    out["dense_launch"] = {"kernel": f"bandwidth_kernel<F={F},f32>", "candidates": len(HS),
+    out["dense_launch"] = {"kernel": f"bandwidth_tile_kernel<F={F},f32>", "candidates": len(HS),
                            "avg_ms": round(float(dms.mean()), 4),
                            "roofline": {"bound": "alu", "achieved": round(ach, 3), "peak": PEAK_ALU_TFLOPS,
                                         "unit": "TFLOP/s", "frac": round(ach / PEAK_ALU_TFLOPS, 4),
